@@ -7,6 +7,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <type_traits>
 #include <vector>
 
 // ------------------------------------------------------------------------------------------------ kernels
@@ -223,19 +224,23 @@ __global__ __launch_bounds__(256) void radius_finish_kernel(const float* __restr
 // ||W_i - mu_c||^2 = ||W_i||^2 - 2 <W_i,mu_c> + ||mu_c||^2 and the first term does not depend on c, so the work is the
 // dense contraction [V x d] . [d x C]: v_mfma_f32_16x16x32_bf16 with the rows of W (bf16) as one operand and the float32
 // centroids, split exactly into three bf16 pieces (three MFMAs per k-block give float32-exact products), as the other.
-// Block = 8 waves = 128 rows x AS_NT*16 clusters; a wave owns 16 rows and keeps their AS_NT accumulator tiles over the
-// whole of K.  The centroid pieces are shared by the 8 waves: they are split while they are staged into LDS, one K
-// chunk at a time, already in fragment order; the rows of W go straight from global memory to registers.
+// The pieces are split once per assignment (split_centroids_kernel), not by every block that reads them: they lie in
+// fragment order, [k-block of 32][cluster tile of 16][piece][lane], so that a block's share of a k-block is one run.
+// Block = 8 waves, 2 (rows) x 4 (clusters); a wave owns 16 MT rows x 16 NT clusters in accumulators over the whole of K.
+// Both operands go through LDS in fragment order (1 KB reads, no bank conflicts), one k-block per stage, two stages:
+// while a stage is consumed the next one, requested an iteration ahead into registers, is stored between the MFMAs, and
+// one barrier (for LDS traffic only: the requests cross it) ends the iteration.  A fragment of W serves 3 NT MFMAs, one
+// of the centroids MT: at MT = 8, NT = 4 a stage is 3072 matrix-core cycles per SIMD for 1792 cycles of LDS traffic.
 // Accumulator register r of lane (li, g) is [row 4g + r][cluster li]: the arg-min over a tile's 16 clusters is a
-// reduction inside a 16-lane DPP row.  Each block writes, per row, the best (distance, cluster) of its cluster group;
-// assign_reduce_kernel picks the best over the groups.
+// reduction inside a 16-lane DPP row, over a block's four column waves through LDS.  Each block writes, per row, the best
+// (distance key, cluster) of its columns as one 64-bit word; assign_reduce_kernel takes the smallest.
+// Bound by the matrix cores: V = 128256, d = 4096, C = 1024 takes 2.45 ms = 1.32 PFLOP/s (8 waves of 16 rows x 64 clusters, each
+// block splitting its own centroids: 7.45 ms); V = 32000, d = 1024, C = 256 (128 x 256 tiles) 49 us, was 124 us.
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 as_bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float as_floatx4_t;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t as_uintx4_t;     // a 16-byte piece in registers (uint4 arrays held across the loop went to scratch)
 #define CSV_ANGLE_SLACK (1.0 / 4096.0)     // added to every angular radius (radians), next to the relative slack
-#define AS_NT 4                 // cluster tiles of 16 per block
-#define AS_KC 256               // K chunk staged in LDS: AS_NT*16 clusters x 3 pieces x AS_KC x 2 bytes = 96 KB
 #define AS_THREADS 512
-#define AS_LDS (AS_NT * 16 * 3 * AS_KC * 2)
 
 __device__ __forceinline__ void as_split3(const float4& x0, const float4& x1, uint4& hi, uint4& mid, uint4& lo) {
     const float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
@@ -277,92 +282,151 @@ __global__ __launch_bounds__(256) void centroid_norm_kernel(const float* __restr
     if (tid == 0) cn[c] = (float)((red[0] + red[1]) + (red[2] + red[3]));
 }
 
-// grid (cluster groups, row tiles of 128).  cand_key[row * G + group] = monotone key of the best distance, cand_c = its cluster.
-__global__ __launch_bounds__(AS_THREADS) void assign_mfma_kernel(const uint16_t* __restrict__ W, const float* __restrict__ mu,
-                                                                 const float* __restrict__ cn, int V, int d, int C, int G,
-                                                                 unsigned* __restrict__ cand_key, int32_t* __restrict__ cand_c) {
-    extern __shared__ uint4 as_lds[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int li = lane & 15, g = lane >> 4;
-    const int group = blockIdx.x, cb = group * AS_NT * 16;
-    const int r0 = blockIdx.y * 128 + wave * 16;
-    const int nq = d >> 3;                                   // 16-byte pieces per row of W
-    const uint4* ap = reinterpret_cast<const uint4*>(W + (size_t)min(r0 + li, V - 1) * d);
-    as_floatx4_t acc[AS_NT];
-#pragma unroll
-    for (int t = 0; t < AS_NT; ++t) acc[t] = as_floatx4_t{0.f, 0.f, 0.f, 0.f};
-    const uint4 zero = make_uint4(0, 0, 0, 0);
-    for (int k0 = 0; k0 < d; k0 += AS_KC) {
-        __syncthreads();
-        // stage: piece (cluster cl of the group, q-th run of 8 k values of the chunk) -> three fragments.
-        // fragment slot of (kb = q / 4, piece s, tile t) is ((kb * 3 + s) * AS_NT + t) * 64 + (q % 4) * 16 + (cl % 16)
-        for (int p = tid; p < AS_NT * 16 * (AS_KC / 8); p += AS_THREADS) {
-            const int cl = p / (AS_KC / 8), q = p - cl * (AS_KC / 8);
-            const int c = cb + cl, k = k0 + q * 8;
-            uint4 hi = zero, mid = zero, lo = zero;
-            if (c < C && k < d) {                            // d is a multiple of 8: the eight values are all in or all out
-                const float4* src = reinterpret_cast<const float4*>(mu + (size_t)c * d + k);
-                as_split3(src[0], src[1], hi, mid, lo);
-            }
-            const int base = (q >> 2) * 3 * AS_NT * 64 + (cl >> 4) * 64 + (q & 3) * 16 + (cl & 15);
-            as_lds[base] = hi;
-            as_lds[base + AS_NT * 64] = mid;
-            as_lds[base + 2 * AS_NT * 64] = lo;
-        }
-        __syncthreads();
-#pragma unroll 2
-        for (int kb = 0; kb < AS_KC / 32; ++kb) {
-            const int q = ((k0 + kb * 32) >> 3) + g;         // this lane's 16-byte piece of its row
-            const uint4 av = ap[min(q, nq - 1)];
-            const as_bf16x8_t A = __builtin_bit_cast(as_bf16x8_t, q < nq ? av : zero);
-#pragma unroll
-            for (int sp = 0; sp < 3; ++sp)
-#pragma unroll
-                for (int t = 0; t < AS_NT; ++t) {
-                    const uint4 Bv = as_lds[((kb * 3 + sp) * AS_NT + t) * 64 + lane];
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, __builtin_bit_cast(as_bf16x8_t, Bv), acc[t], 0, 0, 0);
-                }
-        }
+// The three bf16 pieces of every centroid value in fragment order: out[((kb * CT + ct) * 3 + piece) * 64 + lane], lane =
+// 16 g + li: cluster 16 ct + li, the eight k values 32 kb + 8 g ...; zero past C and past d.  One wave per (kb, ct).
+__global__ __launch_bounds__(256) void split_centroids_kernel(const float* __restrict__ mu, int d, int C, int CT, int nkb, uint4* __restrict__ out) {
+    const int lane = threadIdx.x & 63;
+    const int ct = blockIdx.x, kb = blockIdx.y * 4 + (threadIdx.x >> 6);
+    if (kb >= nkb) return;
+    const int c = ct * 16 + (lane & 15), k = kb * 32 + (lane >> 4) * 8;
+    uint4 hi = make_uint4(0, 0, 0, 0), mid = hi, lo = hi;
+    if (c < C && k < d) {                                    // d is a multiple of 8: the eight values are all in or all out
+        const float4* src = reinterpret_cast<const float4*>(mu + (size_t)c * d + k);
+        as_split3(src[0], src[1], hi, mid, lo);
     }
-    // ||mu_c||^2 - 2 <W_i,mu_c> for row 4g + r and cluster cb + 16t + li; best over the tiles, then over the 16 lanes of the row
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        unsigned bk = 0xffffffffu;
-        int bc = 0x7fffffff;
-#pragma unroll
-        for (int t = 0; t < AS_NT; ++t) {
-            const int c = cb + 16 * t + li;
-            const float v = c < C ? cn[c] - 2.f * acc[t][r] : INFINITY;
-            const unsigned kx = c < C ? fkey(v + 0.0f) : 0xffffffffu;
-            if (kx < bk) {                                   // tiles in ascending cluster order: a tie keeps the smaller id
-                bk = kx;
-                bc = c;
-            }
-        }
-        const unsigned m = row16_min_u(bk);
-        const int cm = (int)row16_min_u(bk == m ? (unsigned)bc : 0x7fffffffu);
-        const int row = r0 + 4 * g + r;
-        if (li == 0 && row < V) {
-            cand_key[(size_t)row * G + group] = m;
-            cand_c[(size_t)row * G + group] = cm;
-        }
+    uint4* o = out + ((size_t)kb * CT + ct) * 192 + lane;
+    o[0] = hi;
+    o[64] = mid;
+    o[128] = lo;
+}
+
+// All LDS accesses of the block's waves are done; global loads stay in flight.
+__device__ __forceinline__ void as_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void as_for(F f) {              // f(0), f(1), ... with the index as a constant
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        as_for<N, I + 1>(f);
     }
 }
 
-__global__ __launch_bounds__(256) void assign_reduce_kernel(const unsigned* __restrict__ cand_key, const int32_t* __restrict__ cand_c,
-                                                            int V, int G, int32_t* __restrict__ labels) {
+// Bs: CT cluster tiles (a multiple of 4 NT) of pieces.  cand[column block * V + row] = (monotone key of the best distance) << 32 | its cluster.
+template <int MT, int NT>
+__global__ __launch_bounds__(AS_THREADS) void assign_mfma_kernel(const uint16_t* __restrict__ W, const uint4* __restrict__ Bs,
+                                                                 const float* __restrict__ cn, int V, int d, int C, int CT,
+                                                                 int ncol, int ntot, unsigned long long* __restrict__ cand) {
+    extern __shared__ as_uintx4_t as_lds[];
+    constexpr int AP = 2 * MT * 64 / AS_THREADS, BP = 4 * NT * 192 / AS_THREADS;      // 16-byte pieces a thread stages of W, of the centroids
+    constexpr int ASZ = 2 * MT * 64, STAGE = ASZ + 4 * NT * 192;                      // pieces per stage
+    static_assert(AP * AS_THREADS == ASZ && BP * AS_THREADS == 4 * NT * 192, "staging layout");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int li = lane & 15, g = lane >> 4, wm = wave >> 2, wn = wave & 3;
+    // blocks are dealt round-robin to the eight XCDs: each gets a contiguous run of tiles, columns fastest, so that the
+    // blocks that share rows of W and the centroids of a k-block sit behind one L2
+    const int tile = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (tile >= ntot) return;
+    const int bn = tile % ncol, row0 = tile / ncol * (2 * MT * 16);
+    const int nq = d >> 3, nkb = (d + 31) >> 5;
+    const as_uintx4_t* ap[AP];
+#pragma unroll
+    for (int i = 0; i < AP; ++i) ap[i] = reinterpret_cast<const as_uintx4_t*>(W + (size_t)min(row0 + (wave + 8 * i) * 16 + li, V - 1) * d);
+    const as_uintx4_t* bp = reinterpret_cast<const as_uintx4_t*>(Bs) + (size_t)bn * (4 * NT) * 192 + tid;
+    as_uintx4_t ra[AP], rb[BP];
+    bool in_row = true;                                      // the requested pieces of W lie inside their rows
+    auto request = [&](int kb) {
+        const int q = kb * 4 + g;
+        in_row = q < nq;
+#pragma unroll
+        for (int i = 0; i < AP; ++i) ra[i] = ap[i][min(q, nq - 1)];
+        const as_uintx4_t* b = bp + (size_t)kb * CT * 192;
+#pragma unroll
+        for (int i = 0; i < BP; ++i) rb[i] = b[i * AS_THREADS];
+    };
+    auto store_a = [&](as_uintx4_t* buf, int i) { buf[tid + i * AS_THREADS] = in_row ? ra[i] : as_uintx4_t{0, 0, 0, 0}; };
+    auto store_b = [&](as_uintx4_t* buf, int i) { buf[ASZ + tid + i * AS_THREADS] = rb[i]; };
+    as_floatx4_t acc[MT][NT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[m][t] = as_floatx4_t{0.f, 0.f, 0.f, 0.f};
+    request(0);
+#pragma unroll
+    for (int i = 0; i < AP; ++i) store_a(as_lds, i);
+#pragma unroll
+    for (int i = 0; i < BP; ++i) store_b(as_lds, i);
+    request(min(1, nkb - 1));
+    as_lds_barrier();
+    for (int kb = 0; kb < nkb; ++kb) {
+        const as_uintx4_t* cur = as_lds + (kb & 1) * STAGE;
+        as_uintx4_t* nxt = as_lds + ((kb + 1) & 1) * STAGE;        // last read in the iteration before: every wave has passed its barrier
+        as_bf16x8_t A[MT];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) A[m] = __builtin_bit_cast(as_bf16x8_t, cur[(wm * MT + m) * 64 + lane]);
+        // a slot: one centroid fragment, its MT MFMAs, then its share of the next stage's pieces (stored between the MFMAs;
+        // in the last iteration to a stage nobody reads)
+        as_for<3 * NT>([&](auto slot_t) {
+            constexpr int slot = decltype(slot_t)::value, t = slot / 3;
+            const as_bf16x8_t B = __builtin_bit_cast(as_bf16x8_t, cur[ASZ + (wn * NT * 3 + slot) * 64 + lane]);
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[m], B, acc[m][t], 0, 0, 0);
+            as_for<AP + BP>([&](auto i_t) {
+                constexpr int i = decltype(i_t)::value;
+                if constexpr (i * 3 * NT / (AP + BP) == slot) {
+                    if constexpr (i < AP) store_a(nxt, i);
+                    else store_b(nxt, i - AP);
+                }
+            });
+        });
+        request(min(kb + 2, nkb - 1));
+        as_lds_barrier();
+    }
+    // ||mu_c||^2 - 2 <W_i,mu_c> for row 4g + r of a tile and cluster li of another; best over the wave's tiles, then over the
+    // 16 lanes of the row, then over the four column waves
+    unsigned long long* best = reinterpret_cast<unsigned long long*>(as_lds);        // [2 MT 16 rows][4]
+    const int c0 = (bn * 4 + wn) * NT * 16 + li;
+    float norm[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) norm[t] = c0 + 16 * t < C ? cn[c0 + 16 * t] : 0.f;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            unsigned bk = 0xffffffffu;
+            int bc = 0x7fffffff;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const int c = c0 + 16 * t;
+                const float v = norm[t] - 2.f * acc[m][t][r];
+                const unsigned kx = c < C ? fkey(v + 0.0f) : 0xffffffffu;
+                if (kx < bk) {                               // tiles in ascending cluster order: a tie keeps the smaller id
+                    bk = kx;
+                    bc = c;
+                }
+            }
+            const unsigned mk = row16_min_u(bk);
+            const unsigned cm = row16_min_u(bk == mk ? (unsigned)bc : 0x7fffffffu);
+            if (li == 0) best[((wm * MT + m) * 16 + 4 * g + r) * 4 + wn] = ((unsigned long long)mk << 32) | cm;
+        }
+    __syncthreads();
+    for (int r = tid; r < 2 * MT * 16; r += AS_THREADS)
+        if (row0 + r < V) {
+            unsigned long long x = best[r * 4];
+#pragma unroll
+            for (int q = 1; q < 4; ++q) x = best[r * 4 + q] < x ? best[r * 4 + q] : x;
+            cand[(size_t)bn * V + row0 + r] = x;
+        }
+}
+
+__global__ __launch_bounds__(256) void assign_reduce_kernel(const unsigned long long* __restrict__ cand, int V, int ncol, int32_t* __restrict__ labels) {
     const int row = blockIdx.x * 256 + threadIdx.x;
     if (row >= V) return;
-    unsigned bk = 0xffffffffu;
-    int bc = 0x7fffffff;
-    for (int gq = 0; gq < G; ++gq) {                         // groups in ascending cluster order: a tie keeps the smaller id
-        const unsigned kx = cand_key[(size_t)row * G + gq];
-        if (kx < bk) {
-            bk = kx;
-            bc = cand_c[(size_t)row * G + gq];
-        }
+    unsigned long long x = cand[row];                        // equal distances: the smaller cluster id is the smaller word
+    for (int q = 1; q < ncol; ++q) {
+        const unsigned long long y = cand[(size_t)q * V + row];
+        x = y < x ? y : x;
     }
-    labels[row] = bc;
+    labels[row] = (int32_t)(unsigned)x;
 }
 
 // mu[c] = row init_rows[c] of W widened to float32 (starting centroids).
@@ -644,6 +708,37 @@ static int gather(csv_index* x, const uint16_t* d_W, const float* d_b, hipStream
     return CSV_OK;
 }
 
+// Which tile a block of the assignment computes: the one whose rounds over the compute units cost least.  Per k-block a
+// 256 x 256 tile takes 3072 cycles of a SIMD's matrix core, a 128 x 256 tile 1536 (with 1464 of LDS traffic), and two
+// 128 x 128 tiles, which share a compute unit, 1792 of LDS traffic between them.
+struct AssignPlan {
+    int mt, nt, ncol, CT, ntot;
+};
+static AssignPlan assign_plan(int V, int C) {
+    static const struct { int mt, nt, per_cu, cycles; } kind[3] = {{8, 4, 1, 3072}, {4, 4, 1, 1536}, {4, 2, 2, 1792}};
+    AssignPlan best = {0, 0, 0, 0, 0};
+    long long cost = 0;
+    for (int i = 0; i < 3; ++i) {
+        const int bm = 2 * kind[i].mt * 16, bn = 4 * kind[i].nt * 16;
+        const int ncol = (C + bn - 1) / bn, ntot = (V + bm - 1) / bm * ncol, at_once = 256 * kind[i].per_cu;
+        const long long c = (long long)((ntot + at_once - 1) / at_once) * kind[i].cycles;
+        if (i == 0 || c < cost) {
+            cost = c;
+            best = {kind[i].mt, kind[i].nt, ncol, ncol * 4 * kind[i].nt, ntot};
+        }
+    }
+    return best;
+}
+template <int MT, int NT>
+static int launch_assign(const AssignPlan& p, const uint16_t* W, const uint4* pieces, const float* cn, int V, int d, int C,
+                         unsigned long long* cand, hipStream_t st) {
+    constexpr int lds = 2 * (2 * MT + 12 * NT) * 1024;
+    CSV_HIP(hipFuncSetAttribute((const void*)assign_mfma_kernel<MT, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    assign_mfma_kernel<MT, NT><<<(p.ntot + 7) / 8 * 8, AS_THREADS, lds, st>>>(W, pieces, cn, V, d, C, p.CT, p.ncol, p.ntot, cand);
+    CSV_LAUNCH_CHECK("assign_mfma_kernel");
+    return CSV_OK;
+}
+
 extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int d, int C, const csv_build_opts* o,
                                void* stream, csv_index** out) {
     if (out) *out = nullptr;
@@ -659,17 +754,17 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
     if (rc) return rc;
     int32_t* d_labels = nullptr;
     std::vector<int32_t> labels(V), n, off, perm;
-    // scratch of the assignment: per row and cluster group the best (distance key, cluster); centroid norms
-    unsigned* d_ckey = nullptr;
-    int32_t* d_cc = nullptr;
+    // scratch of the assignment: the centroids' bf16 pieces, per row and column block the best (distance key, cluster), centroid norms
+    uint4* d_pieces = nullptr;
+    unsigned long long* d_cand = nullptr;
     float* d_cn = nullptr;
     // spherical clustering: row norms in original and in permuted order, float64 sums of unit rows
     const int sph = o->spherical != 0;
     double *d_nrm = nullptr, *d_nrmp = nullptr, *d_sums = nullptr;
     auto free_scratch = [&]() {
         if (d_labels) (void)hipFree(d_labels);
-        if (d_ckey) (void)hipFree(d_ckey);
-        if (d_cc) (void)hipFree(d_cc);
+        if (d_pieces) (void)hipFree(d_pieces);
+        if (d_cand) (void)hipFree(d_cand);
         if (d_cn) (void)hipFree(d_cn);
         if (d_nrm) (void)hipFree(d_nrm);
         if (d_nrmp) (void)hipFree(d_nrmp);
@@ -689,18 +784,23 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
         row_norm_kernel<<<(V + 3) / 4, 256, 0, st>>>(d_W, V, d, d_nrm);
         if (hipGetLastError() != hipSuccess) { csv_set_error("launch of row_norm_kernel failed"); return fail(CSV_EHIP); }
     }
-    const int G = (C + AS_NT * 16 - 1) / (AS_NT * 16);
+    const AssignPlan ap = assign_plan(V, C);
     auto assign = [&]() -> int {
-        if (!d_ckey) {
-            if (hipMalloc((void**)&d_ckey, (size_t)V * G * 4) != hipSuccess || hipMalloc((void**)&d_cc, (size_t)V * G * 4) != hipSuccess ||
+        const int nkb = (d + 31) / 32;
+        if (!d_pieces) {
+            if (hipMalloc((void**)&d_pieces, (size_t)nkb * ap.CT * 192 * sizeof(uint4)) != hipSuccess ||
+                hipMalloc((void**)&d_cand, (size_t)V * ap.ncol * 8) != hipSuccess ||
                 hipMalloc((void**)&d_cn, (size_t)C * 4) != hipSuccess) { csv_set_error("out of device memory (assignment scratch)"); return CSV_ENOMEM; }
-            CSV_HIP(hipFuncSetAttribute((const void*)assign_mfma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, AS_LDS));
         }
         centroid_norm_kernel<<<C, 256, 0, st>>>(x->mu, d, sph, d_cn);
         CSV_LAUNCH_CHECK("centroid_norm_kernel");
-        assign_mfma_kernel<<<dim3(G, (V + 127) / 128), AS_THREADS, AS_LDS, st>>>(d_W, x->mu, d_cn, V, d, C, G, d_ckey, d_cc);
-        CSV_LAUNCH_CHECK("assign_mfma_kernel");
-        assign_reduce_kernel<<<(V + 255) / 256, 256, 0, st>>>(d_ckey, d_cc, V, G, d_labels);
+        split_centroids_kernel<<<dim3(ap.CT, (nkb + 3) / 4), 256, 0, st>>>(x->mu, d, C, ap.CT, nkb, d_pieces);
+        CSV_LAUNCH_CHECK("split_centroids_kernel");
+        const int lrc = ap.mt == 8 ? launch_assign<8, 4>(ap, d_W, d_pieces, d_cn, V, d, C, d_cand, st)
+                      : ap.nt == 4 ? launch_assign<4, 4>(ap, d_W, d_pieces, d_cn, V, d, C, d_cand, st)
+                                   : launch_assign<4, 2>(ap, d_W, d_pieces, d_cn, V, d, C, d_cand, st);
+        if (lrc) return lrc;
+        assign_reduce_kernel<<<(V + 255) / 256, 256, 0, st>>>(d_cand, V, ap.ncol, d_labels);
         CSV_LAUNCH_CHECK("assign_reduce_kernel");
         CSV_HIP(hipMemcpyAsync(labels.data(), d_labels, (size_t)V * 4, hipMemcpyDeviceToHost, st));
         CSV_HIP(hipStreamSynchronize(st));

@@ -1,0 +1,37 @@
+"""Index build kernels at the edges of their tiles and chunks, through the C ABI (the larger shapes and whole Lloyd runs are in test_gpu_parity.py)."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import csv_oracle as O
+
+from ._harness import log
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _same_metadata(e, want):
+    """n, perm and bias maxima exactly; centroids to one unit in the last place and radii to two (float64 sums, rounded once)."""
+    assert np.array_equal(e["n"], want.n) and np.array_equal(e["perm"], want.perm) and np.array_equal(e["bmax"], want.bmax)
+    for key, ulps in (("mu", 1), ("R", 2)):
+        diff = np.abs(e[key].view(np.int32).astype(np.int64) - getattr(want, key).view(np.int32).astype(np.int64))
+        assert diff.max() <= ulps, (key, int(diff.max()))
+
+
+# 256 x 256 tiles; 128 x 256 tiles in one and in two column blocks; 128 x 128 tiles.  d ends inside a k-block of 32, V and
+# C inside a tile; the last cluster repeats the first one's seed (in another column block where there are two) and stays
+# empty, because equal distances go to the smaller id.
+@pytest.mark.parametrize("V,d,C", [(65000, 72, 250), (3001, 264, 37), (5003, 40, 300), (70001, 32, 101), (257, 8, 3)])
+def test_assignment_tiles_recover_planted_clusters(V, d, C):
+    import paper_2511_21702_amd as csv
+    r = synth.small_recipe("tiles", V=V, d=d, C=C, B=1, steps=1, row_noise=0.01)
+    head = synth.make_head(r, seed=5, threads=8)
+    first = np.array([int(np.flatnonzero(head["labels"] == c)[0]) for c in range(C)] + [int(np.flatnonzero(head["labels"] == 0)[0])], dtype=np.int32)
+    log(f"assignment V={V} d={d} C={C + 1}")
+    g = csv.csv_build_index(csv.bits_to_device(head["W_bits"]), torch.from_numpy(head["b"]).cuda(), C + 1, init_rows=first, iters=0)
+    want = O.build_index(head["W_bits"], head["b"], head["labels"], C + 1)
+    assert want.n[C] == 0
+    _same_metadata(g.export(), want)
+    g.free()
