@@ -24,21 +24,222 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const uint16_t* __rest
     if (threadIdx.x == 0) bp[r] = b ? b[src] : 0.f;
 }
 
-// mu_c = mean of the cluster's rows, accumulated in float64 row by row, stored as float32.
-// An empty cluster keeps its centroid (Lloyd) or is zeroed (final metadata).
-__global__ __launch_bounds__(256) void centroid_kernel(const uint16_t* __restrict__ Wp, const int32_t* __restrict__ off, int d,
-                                                       int zero_empty, float* __restrict__ mu) {
-    const int c = blockIdx.x;
+// ------------------------------------------------------------------------------------------------ labels -> layout
+// Sizes, offsets and the permutation from the labels (clusters in id order, tokens by ascending id inside a cluster), on
+// the device: the build of an index then has no copy to the host and no wait between its iterations.  A stable counting
+// sort: one wave per LAY_TOKENS tokens counts its labels, the counts are summed up per cluster over the waves, and the same
+// wave places its tokens in order.  All of it is latency (V = 128256, C = 1024: four launches, 40 us in all; the copy of the labels, the host's
+// sort and three copies back took 0.4 ms).
+#define LAY_TOKENS 512
+// hist[wave][c] = its tokens of cluster c.  cand != NULL: the labels are made here, as the smallest word over the
+// assignment's column blocks (equal distances: the smaller cluster id is the smaller word).
+__global__ __launch_bounds__(64) void label_hist_kernel(const unsigned long long* __restrict__ cand, int ncol, int32_t* __restrict__ labels, int V,
+                                                        int C, int32_t* __restrict__ hist) {
+    extern __shared__ int32_t lay_cnt[];
+    const int lane = threadIdx.x, base = blockIdx.x * LAY_TOKENS;
+    for (int c = lane; c < C; c += 64) lay_cnt[c] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < LAY_TOKENS / 64; ++i) {
+        const int t = base + lane + 64 * i;
+        if (t < V) {
+            int l;
+            if (cand) {
+                unsigned long long x = cand[t];
+                for (int q = 1; q < ncol; ++q) {
+                    const unsigned long long y = cand[(size_t)q * V + t];
+                    x = y < x ? y : x;
+                }
+                l = (int)(unsigned)x;
+                labels[t] = l;
+            } else {
+                l = labels[t];
+            }
+            atomicAdd(&lay_cnt[l], 1);
+        }
+    }
+    __syncthreads();
+    for (int c = lane; c < C; c += 64) hist[(size_t)blockIdx.x * C + c] = lay_cnt[c];
+}
+
+// hist[w][c] becomes the tokens of cluster c before wave w; n[c] their number.  64 clusters per block, a segment of the waves per wave.
+__global__ __launch_bounds__(512) void layout_scan_kernel(int32_t* __restrict__ hist, int nw, int C, int32_t* __restrict__ n) {
+    __shared__ int32_t seg_sum[8][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = blockIdx.x * 64 + lane;
+    const int seg = (nw + 7) / 8, w0 = min(nw, wave * seg), w1 = min(nw, w0 + seg);
+    int sum = 0;
+    if (c < C)
+#pragma unroll 8
+        for (int w = w0; w < w1; ++w) sum += hist[(size_t)w * C + c];
+    seg_sum[wave][lane] = sum;
+    __syncthreads();
+    int run = 0, total = 0;
+    for (int q = 0; q < 8; ++q) {
+        if (q < wave) run += seg_sum[q][lane];
+        total += seg_sum[q][lane];
+    }
+    if (c >= C) return;
+#pragma unroll 8
+    for (int w = w0; w < w1; ++w) {
+        const int x = hist[(size_t)w * C + c];
+        hist[(size_t)w * C + c] = run;
+        run += x;
+    }
+    if (wave == 0) n[c] = total;
+}
+
+// off, and the list of row chunks of the centroid and distance passes: chunks[i] = {cluster, first permuted row}, coff[c] =
+// first chunk of cluster c, coff[C] = their number.  One block.
+#define CHUNK_ROWS 128
+__global__ __launch_bounds__(1024) void layout_offsets_kernel(const int32_t* __restrict__ n, int C, int32_t* __restrict__ off,
+                                                              int32_t* __restrict__ coff, int2* __restrict__ chunks) {
+    __shared__ int32_t ws[2][16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int per = (C + 1023) / 1024, c0 = min(C, tid * per), c1 = min(C, c0 + per);
+    int rows = 0, nch = 0;
+    for (int c = c0; c < c1; ++c) {
+        rows += n[c];
+        nch += (n[c] + CHUNK_ROWS - 1) / CHUNK_ROWS;
+    }
+    int x = rows, y = nch;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int xx = __shfl_up(x, o, CSV_WAVE), yy = __shfl_up(y, o, CSV_WAVE);
+        if (lane >= o) {
+            x += xx;
+            y += yy;
+        }
+    }
+    if (lane == 63) {
+        ws[0][wave] = x;
+        ws[1][wave] = y;
+    }
+    __syncthreads();
+    x -= rows;
+    y -= nch;
+    for (int q = 0; q < wave; ++q) {
+        x += ws[0][q];
+        y += ws[1][q];
+    }
+    for (int c = c0; c < c1; ++c) {
+        off[c] = x;
+        coff[c] = y;
+        for (int r = 0; r < n[c]; r += CHUNK_ROWS) chunks[y++] = make_int2(c, x + r);
+        x += n[c];
+    }
+    if (c1 == C && c0 < C) {
+        off[C] = x;
+        coff[C] = y;
+    }
+}
+
+__global__ __launch_bounds__(64) void layout_scatter_kernel(const int32_t* __restrict__ labels, const int32_t* __restrict__ hist,
+                                                            const int32_t* __restrict__ off, int V, int C, int label_bits,
+                                                            int32_t* __restrict__ perm) {
+    extern __shared__ int32_t lay_cnt[];                     // next permuted row of each cluster
+    const int lane = threadIdx.x, base = blockIdx.x * LAY_TOKENS;
+    for (int c = lane; c < C; c += 64) lay_cnt[c] = off[c] + hist[(size_t)blockIdx.x * C + c];
+    __syncthreads();
+    for (int i = 0; i < LAY_TOKENS / 64; ++i) {
+        const int t = base + lane + 64 * i;
+        const bool in = t < V;
+        const int l = in ? labels[t] : 0;
+        unsigned long long same = __ballot(in);              // the lanes with this lane's label
+        for (int bit = 0; bit < label_bits; ++bit) {
+            const bool one = (l >> bit) & 1;
+            const unsigned long long m = __ballot(one);
+            same &= one ? m : ~m;
+        }
+        const int before = __popcll(same & ((1ull << lane) - 1ull));
+        const int pos = lay_cnt[l] + before;
+        __syncthreads();                                     // every lane has read its counter
+        if (in) {
+            perm[pos] = t;
+            if (before == 0) lay_cnt[l] = pos + __popcll(same);
+        }
+        __syncthreads();
+    }
+}
+
+// ------------------------------------------------------------------------------------------------ centroids
+// Sums of the rows of W of one chunk (at most CHUNK_ROWS rows of one cluster, read through the permutation: the gathered
+// copy is made once, after the last iteration), in float64.  Block = 4 waves x 512 columns; a wave takes every fourth
+// row, eight rows requested at once; the waves' sums are added in wave order.  A cluster of one chunk is finished here, the
+// chunks of a larger one leave partial sums for centroid_finish_kernel, so a cluster of any size is spread over the device.
+// Bound by reading W: 215 us at V = 128256, d = 4096 = 4.9 TB/s.  (One thread per column going down all rows of a cluster: 1.7 ms at V = 128256, d = 4096 with clusters of
+// up to 2900 rows, plus 0.38 ms for a gathered copy per iteration.)
+// UNIT (spherical clustering): rows are divided by their norm nrm[token], the sums themselves go to out_sum.
+template <bool UNIT>
+__global__ __launch_bounds__(256) void centroid_chunk_kernel(const uint16_t* __restrict__ W, const int32_t* __restrict__ perm, const int32_t* __restrict__ off,
+                                                             const int32_t* __restrict__ coff, const int2* __restrict__ chunks, int d, int C,
+                                                             const double* __restrict__ nrm, float* __restrict__ mu, double* __restrict__ out_sum,
+                                                             double* __restrict__ part) {
+    __shared__ double red[4][8][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, chunk = blockIdx.x;
+    if (chunk >= coff[C]) return;
+    const int c = chunks[chunk].x, r0 = chunks[chunk].y;
+    const int first = off[c], last = off[c + 1], rows = min(CHUNK_ROWS, last - r0);
+    const int piece = blockIdx.y * 64 + lane, np = d >> 3;
+    const int mine = (rows - wave + 3) / 4;                  // rows r0 + wave, r0 + wave + 4, ...
+    const int token = lane < mine ? perm[r0 + wave + 4 * lane] : 0;
+    double acc[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = 0.0;
+    const uint4* w = reinterpret_cast<const uint4*>(W) + min(piece, np - 1);
+    auto add = [&](const uint4& x, int tok) {
+        const double nr = UNIT ? nrm[tok] : 1.0;
+        const uint32_t xs[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const double v = (double)__uint_as_float(e & 1 ? xs[e >> 1] & 0xffff0000u : xs[e >> 1] << 16);
+            acc[e] += UNIT && nr > 0.0 ? v / nr : v;
+        }
+    };
+    int i = 0;
+    for (; i + 8 <= mine; i += 8) {
+        uint4 x[8];
+        int tk[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            tk[q] = __builtin_amdgcn_readlane(token, i + q);
+            x[q] = w[(size_t)tk[q] * np];
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) add(x[q], tk[q]);
+    }
+    for (; i < mine; ++i) {
+        const int tk = __builtin_amdgcn_readlane(token, i);
+        add(w[(size_t)tk * np], tk);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) red[wave][e][lane] = acc[e];
+    __syncthreads();
+    if (piece >= np) return;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int e = 2 * wave + q, col = piece * 8 + e;
+        const double sum = ((red[0][e][lane] + red[1][e][lane]) + red[2][e][lane]) + red[3][e][lane];
+        if (last - first > CHUNK_ROWS) part[(size_t)chunk * d + col] = sum;
+        else if (UNIT) out_sum[(size_t)c * d + col] = sum;
+        else mu[(size_t)c * d + col] = (float)(sum / (double)rows);
+    }
+}
+
+// Clusters of several chunks: the partial sums, in chunk order.  An empty cluster keeps its centroid (Lloyd) or is zeroed
+// (final metadata; direction_finish_kernel does that for directions).
+template <bool UNIT>
+__global__ __launch_bounds__(256) void centroid_finish_kernel(const int32_t* __restrict__ off, const int32_t* __restrict__ coff, int d, int zero_empty,
+                                                              const double* __restrict__ part, float* __restrict__ mu, double* __restrict__ out_sum) {
+    const int c = blockIdx.x, n = off[c + 1] - off[c];
     const int col = blockIdx.y * 256 + threadIdx.x;
     if (col >= d) return;
-    const int r0 = off[c], r1 = off[c + 1];
-    if (r1 == r0) {
-        if (zero_empty) mu[(size_t)c * d + col] = 0.f;
-        return;
-    }
+    if (n == 0 && zero_empty && !UNIT) mu[(size_t)c * d + col] = 0.f;
+    if (n <= CHUNK_ROWS) return;
     double sum = 0.0;
-    for (int r = r0; r < r1; ++r) sum += (double)__uint_as_float((uint32_t)Wp[(size_t)r * d + col] << 16);
-    mu[(size_t)c * d + col] = (float)(sum / (double)(r1 - r0));
+#pragma unroll 4
+    for (int q = coff[c]; q < coff[c + 1]; ++q) sum += part[(size_t)q * d + col];
+    if (UNIT) out_sum[(size_t)c * d + col] = sum;
+    else mu[(size_t)c * d + col] = (float)(sum / (double)n);
 }
 
 __device__ __forceinline__ double wave_sum_d(double v) {
@@ -49,40 +250,58 @@ __device__ __forceinline__ double wave_sum_d(double v) {
 
 // R_c = max_i ||W_i - mu_c||_2 to the stored float32 centroid, in float64; stored radius
 // roundup_f32(R_c (1+rho) + rho ||mu_c||); bias maximum; ln n_c.
-// Pass 1, one wave per permuted row (so a cluster of any size is spread over the whole device): squared distance in
-// float64, folded into d2max[c] with an integer atomic max (non-negative doubles order like their bit patterns).
-__global__ __launch_bounds__(256) void row_dist_kernel(const uint16_t* __restrict__ Wp, const int32_t* __restrict__ off,
-                                                       const float* __restrict__ mu, int V, int d, int C,
-                                                       unsigned long long* __restrict__ d2max, double* __restrict__ d2row) {
-    const int lane = threadIdx.x & 63;
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (r >= V) return;
-    int lo = 0, hi = C;                       // cluster of the row: largest c with off[c] <= r
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (off[mid] <= r) lo = mid; else hi = mid;
-    }
-    const uint4* w = reinterpret_cast<const uint4*>(Wp + (size_t)r * d);
-    const float4* m = reinterpret_cast<const float4*>(mu + (size_t)lo * d);
-    double acc = 0.0;
-    for (int q = lane; q < (d >> 3); q += 64) {
-        const uint4 x = w[q];
-        const float4 m0 = m[2 * q], m1 = m[2 * q + 1];
-        const uint32_t xs[4] = {x.x, x.y, x.z, x.w};
-        const float ms[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
+// Pass 1, together with the gathered copy W'[r] = W[perm[r]], b'[r] = b[perm[r]] (0 without bias), so that W is read once:
+// one block per chunk, one wave per row: squared distance in float64, folded into d2max[c] with an integer atomic max
+// (non-negative doubles order like their bit patterns).  A row passes through the wave in batches of four 128-bit loads.
+// Bound by reading W and writing W': V = 128256, d = 4096 in 495 us (separate passes: 380 + 305 us).
+__global__ __launch_bounds__(256) void gather_dist_kernel(const uint16_t* __restrict__ W, const float* __restrict__ b, const int32_t* __restrict__ perm,
+                                                          const int32_t* __restrict__ off, const int32_t* __restrict__ coff, const int2* __restrict__ chunks,
+                                                          const float* __restrict__ mu, int d, int C, uint16_t* __restrict__ Wp, float* __restrict__ bp,
+                                                          unsigned long long* __restrict__ d2max, double* __restrict__ d2row) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, chunk = blockIdx.x >> 2;
+    if (chunk >= coff[C]) return;
+    const int c = chunks[chunk].x, r0 = chunks[chunk].y, r1 = min(r0 + CHUNK_ROWS, off[c + 1]), np = d >> 3;
+    const float4* m = reinterpret_cast<const float4*>(mu + (size_t)c * d);
+    double most = 0.0;
+    // a quarter of the chunk's rows per block, every fourth of those per wave
+    for (int r = r0 + (blockIdx.x & 3) * 4 + wave; r < r1; r += 16) {
+        const int src = perm[r];
+        const uint4* w = reinterpret_cast<const uint4*>(W + (size_t)src * d);
+        uint4* o = reinterpret_cast<uint4*>(Wp + (size_t)r * d);
+        double acc = 0.0;
+        for (int q0 = lane; q0 < np; q0 += 256) {
+            uint4 x[4];
+            float4 m0[4], m1[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const double d0 = (double)__uint_as_float(xs[e] << 16) - (double)ms[2 * e];
-            const double d1 = (double)__uint_as_float(xs[e] & 0xffff0000u) - (double)ms[2 * e + 1];
-            acc = fma(d0, d0, acc);
-            acc = fma(d1, d1, acc);
+            for (int i = 0; i < 4; ++i) {
+                const int q = min(q0 + 64 * i, np - 1);
+                x[i] = w[q];
+                m0[i] = m[2 * q];
+                m1[i] = m[2 * q + 1];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (q0 + 64 * i >= np) break;
+                o[q0 + 64 * i] = x[i];
+                const uint32_t xs[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
+                const float ms[8] = {m0[i].x, m0[i].y, m0[i].z, m0[i].w, m1[i].x, m1[i].y, m1[i].z, m1[i].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const double d0 = (double)__uint_as_float(xs[e] << 16) - (double)ms[2 * e];
+                    const double d1 = (double)__uint_as_float(xs[e] & 0xffff0000u) - (double)ms[2 * e + 1];
+                    acc = fma(d0, d0, acc);
+                    acc = fma(d1, d1, acc);
+                }
+            }
+        }
+        acc = wave_sum_d(acc);
+        most = fmax(most, acc);
+        if (lane == 0) {
+            bp[r] = b ? b[src] : 0.f;
+            if (d2row) d2row[r] = acc;      // squared distance of every row, for the bias table
         }
     }
-    acc = wave_sum_d(acc);
-    if (lane == 0) {
-        atomicMax(&d2max[lo], (unsigned long long)__double_as_longlong(acc));
-        if (d2row) d2row[r] = acc;          // squared distance of every row, for the bias table
-    }
+    if (lane == 0) atomicMax(&d2max[c], (unsigned long long)__double_as_longlong(most));
 }
 
 // Top-m bias table of one cluster (one block per cluster): the m-1 rows with the largest bias (equal biases: the
@@ -233,7 +452,7 @@ __global__ __launch_bounds__(256) void radius_finish_kernel(const float* __restr
 // of the centroids MT: at MT = 8, NT = 4 a stage is 3072 matrix-core cycles per SIMD for 1792 cycles of LDS traffic.
 // Accumulator register r of lane (li, g) is [row 4g + r][cluster li]: the arg-min over a tile's 16 clusters is a
 // reduction inside a 16-lane DPP row, over a block's four column waves through LDS.  Each block writes, per row, the best
-// (distance key, cluster) of its columns as one 64-bit word; assign_reduce_kernel takes the smallest.
+// (distance key, cluster) of its columns as one 64-bit word; label_hist_kernel takes the smallest.
 // Bound by the matrix cores: V = 128256, d = 4096, C = 1024 takes 2.45 ms = 1.32 PFLOP/s (8 waves of 16 rows x 64 clusters, each
 // block splitting its own centroids: 7.45 ms); V = 32000, d = 1024, C = 256 (128 x 256 tiles) 49 us, was 124 us.
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 as_bf16x8_t;
@@ -418,17 +637,6 @@ __global__ __launch_bounds__(AS_THREADS) void assign_mfma_kernel(const uint16_t*
         }
 }
 
-__global__ __launch_bounds__(256) void assign_reduce_kernel(const unsigned long long* __restrict__ cand, int V, int ncol, int32_t* __restrict__ labels) {
-    const int row = blockIdx.x * 256 + threadIdx.x;
-    if (row >= V) return;
-    unsigned long long x = cand[row];                        // equal distances: the smaller cluster id is the smaller word
-    for (int q = 1; q < ncol; ++q) {
-        const unsigned long long y = cand[(size_t)q * V + row];
-        x = y < x ? y : x;
-    }
-    labels[row] = (int32_t)(unsigned)x;
-}
-
 // mu[c] = row init_rows[c] of W widened to float32 (starting centroids).
 __global__ __launch_bounds__(256) void init_centroid_kernel(const uint16_t* __restrict__ W, const int32_t* __restrict__ rows,
                                                             int d, float* __restrict__ mu) {
@@ -470,22 +678,6 @@ __global__ __launch_bounds__(256) void init_direction_kernel(const uint16_t* __r
         const double v = (double)__uint_as_float((uint32_t)w[j] << 16);
         mu[(size_t)c * d + j] = (float)(nr > 0.0 ? v / nr : v);
     }
-}
-
-// sums[c][col] = sum over the cluster's rows of W'[r][col] / ||W'[r]||, float64, row by row (nrm in permuted order).
-__global__ __launch_bounds__(256) void direction_sum_kernel(const uint16_t* __restrict__ Wp, const int32_t* __restrict__ off,
-                                                            const double* __restrict__ nrm, int d, double* __restrict__ sums) {
-    const int c = blockIdx.x;
-    const int col = blockIdx.y * 256 + threadIdx.x;
-    if (col >= d) return;
-    const int r0 = off[c], r1 = off[c + 1];
-    double sum = 0.0;
-    for (int r = r0; r < r1; ++r) {
-        const double nr = nrm[r];
-        const double v = (double)__uint_as_float((uint32_t)Wp[(size_t)r * d + col] << 16);
-        sum += nr > 0.0 ? v / nr : v;
-    }
-    sums[(size_t)c * d + col] = sum;
 }
 
 // mu[c] = sums[c] / ||sums[c]|| as float32; an empty cluster keeps its direction (Lloyd) or is zeroed (final metadata).
@@ -677,22 +869,6 @@ extern "C" int csv_index_use_bf16_centroids(csv_index* x, void* stream) {
     return store_centroids_bf16(x, 1, (hipStream_t)stream);
 }
 
-// labels -> sizes, offsets and the permutation (clusters in id order, tokens by ascending id inside a cluster)
-static int layout_from_labels(const int32_t* labels, int V, int C, std::vector<int32_t>& n, std::vector<int32_t>& off,
-                              std::vector<int32_t>& perm) {
-    n.assign(C, 0);
-    for (int i = 0; i < V; ++i) {
-        if (labels[i] < 0 || labels[i] >= C) { csv_set_error("label %d of token %d outside 0..C-1", labels[i], i); return CSV_EINVAL; }
-        n[labels[i]]++;
-    }
-    off.assign(C + 1, 0);
-    for (int c = 0; c < C; ++c) off[c + 1] = off[c] + n[c];
-    perm.resize(V);
-    std::vector<int32_t> cur(off.begin(), off.end() - 1);
-    for (int i = 0; i < V; ++i) perm[cur[labels[i]]++] = i;
-    return CSV_OK;
-}
-
 static int upload_layout(csv_index* x, const std::vector<int32_t>& n, const std::vector<int32_t>& off,
                          const std::vector<int32_t>& perm, hipStream_t st) {
     CSV_HIP(hipMemcpyAsync(x->n, n.data(), (size_t)x->C * 4, hipMemcpyHostToDevice, st));
@@ -752,111 +928,100 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
     csv_index* x = nullptr;
     rc = csv_index_alloc(V, d, C, &x);
     if (rc) return rc;
-    int32_t* d_labels = nullptr;
-    std::vector<int32_t> labels(V), n, off, perm;
-    // scratch of the assignment: the centroids' bf16 pieces, per row and column block the best (distance key, cluster), centroid norms
-    uint4* d_pieces = nullptr;
-    unsigned long long* d_cand = nullptr;
-    float* d_cn = nullptr;
-    // spherical clustering: row norms in original and in permuted order, float64 sums of unit rows
-    const int sph = o->spherical != 0;
-    double *d_nrm = nullptr, *d_nrmp = nullptr, *d_sums = nullptr;
-    auto free_scratch = [&]() {
-        if (d_labels) (void)hipFree(d_labels);
-        if (d_pieces) (void)hipFree(d_pieces);
-        if (d_cand) (void)hipFree(d_cand);
-        if (d_cn) (void)hipFree(d_cn);
-        if (d_nrm) (void)hipFree(d_nrm);
-        if (d_nrmp) (void)hipFree(d_nrmp);
-        if (d_sums) (void)hipFree(d_sums);
+    // One scratch allocation for the whole build: labels, the layout's counts and chunk list, partial centroid sums, the
+    // assignment's pieces, candidates and norms, squared distances; for spherical clustering row norms and sums of unit rows.
+    const int sph = o->spherical != 0, bt_m = o->bias_table_m >= 2 ? o->bias_table_m : 0;
+    const bool assigns = !o->h_init_labels || o->iters > 0;
+    const int nkb = (d + 31) / 32, nw = (V + LAY_TOKENS - 1) / LAY_TOKENS, max_chunks = V / CHUNK_ROWS + C;
+    const AssignPlan ap = assign_plan(V, C);
+    char* arena = nullptr;
+    size_t used = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = used;
+        used += (bytes + 255) / 256 * 256;
+        return at;
     };
+    const size_t o_labels = take((size_t)V * 4), o_hist = take((size_t)nw * C * 4), o_coff = take((size_t)(C + 1) * 4), o_chunks = take((size_t)max_chunks * sizeof(int2)),
+                 o_part = take((size_t)max_chunks * d * 8), o_pieces = take(assigns ? (size_t)nkb * ap.CT * 192 * sizeof(uint4) : 0),
+                 o_cand = take(assigns ? (size_t)V * ap.ncol * 8 : 0), o_cn = take((size_t)C * 4), o_d2max = take((size_t)C * 8),
+                 o_d2row = take(bt_m ? (size_t)V * 8 : 0), o_nrm = take(sph ? (size_t)V * 8 : 0), o_sums = take(sph ? (size_t)C * d * 8 : 0),
+                 o_ext = take(sph ? (size_t)3 * C * 8 : 0);
     auto fail = [&](int code) {
-        free_scratch();
+        if (arena) {
+            (void)hipStreamSynchronize(st);
+            (void)hipFree(arena);
+        }
         csv_index_free(x);
         return code;
     };
-    if (hipMalloc((void**)&d_labels, (size_t)V * 4) != hipSuccess) { csv_set_error("label buffer allocation failed"); return fail(CSV_ENOMEM); }
-    const dim3 cgrid(C, (d + 255) / 256);
+    if (sph && (o->centroid_bf16 || bt_m)) { csv_set_error("spherical clustering takes neither bf16 centroids nor a bias table"); return fail(CSV_EINVAL); }
+    if (hipMalloc((void**)&arena, used) != hipSuccess) { csv_set_error("out of device memory (index build scratch, %zu bytes)", used); return fail(CSV_ENOMEM); }
+    int32_t *d_labels = (int32_t*)(arena + o_labels), *d_hist = (int32_t*)(arena + o_hist), *d_coff = (int32_t*)(arena + o_coff);
+    int2* d_chunks = (int2*)(arena + o_chunks);
+    double *d_part = (double*)(arena + o_part), *d_nrm = (double*)(arena + o_nrm), *d_sums = (double*)(arena + o_sums), *d_d2row = bt_m ? (double*)(arena + o_d2row) : nullptr;
+    uint4* d_pieces = (uint4*)(arena + o_pieces);
+    float* d_cn = (float*)(arena + o_cn);
+    unsigned long long *d_cand = (unsigned long long*)(arena + o_cand), *d_d2max = (unsigned long long*)(arena + o_d2max), *d_ext = (unsigned long long*)(arena + o_ext);
     if (sph) {
-        if (o->centroid_bf16 || o->bias_table_m >= 2) { csv_set_error("spherical clustering takes neither bf16 centroids nor a bias table"); return fail(CSV_EINVAL); }
-        if (hipMalloc((void**)&d_nrm, (size_t)V * 8) != hipSuccess || hipMalloc((void**)&d_nrmp, (size_t)V * 8) != hipSuccess ||
-            hipMalloc((void**)&d_sums, (size_t)C * d * 8) != hipSuccess) { csv_set_error("out of device memory (spherical clustering scratch)"); return fail(CSV_ENOMEM); }
         row_norm_kernel<<<(V + 3) / 4, 256, 0, st>>>(d_W, V, d, d_nrm);
         if (hipGetLastError() != hipSuccess) { csv_set_error("launch of row_norm_kernel failed"); return fail(CSV_EHIP); }
     }
-    const AssignPlan ap = assign_plan(V, C);
     auto assign = [&]() -> int {
-        const int nkb = (d + 31) / 32;
-        if (!d_pieces) {
-            if (hipMalloc((void**)&d_pieces, (size_t)nkb * ap.CT * 192 * sizeof(uint4)) != hipSuccess ||
-                hipMalloc((void**)&d_cand, (size_t)V * ap.ncol * 8) != hipSuccess ||
-                hipMalloc((void**)&d_cn, (size_t)C * 4) != hipSuccess) { csv_set_error("out of device memory (assignment scratch)"); return CSV_ENOMEM; }
-        }
         centroid_norm_kernel<<<C, 256, 0, st>>>(x->mu, d, sph, d_cn);
         CSV_LAUNCH_CHECK("centroid_norm_kernel");
         split_centroids_kernel<<<dim3(ap.CT, (nkb + 3) / 4), 256, 0, st>>>(x->mu, d, C, ap.CT, nkb, d_pieces);
         CSV_LAUNCH_CHECK("split_centroids_kernel");
-        const int lrc = ap.mt == 8 ? launch_assign<8, 4>(ap, d_W, d_pieces, d_cn, V, d, C, d_cand, st)
-                      : ap.nt == 4 ? launch_assign<4, 4>(ap, d_W, d_pieces, d_cn, V, d, C, d_cand, st)
-                                   : launch_assign<4, 2>(ap, d_W, d_pieces, d_cn, V, d, C, d_cand, st);
-        if (lrc) return lrc;
-        assign_reduce_kernel<<<(V + 255) / 256, 256, 0, st>>>(d_cand, V, ap.ncol, d_labels);
-        CSV_LAUNCH_CHECK("assign_reduce_kernel");
-        CSV_HIP(hipMemcpyAsync(labels.data(), d_labels, (size_t)V * 4, hipMemcpyDeviceToHost, st));
-        CSV_HIP(hipStreamSynchronize(st));
-        return CSV_OK;
+        return ap.mt == 8 ? launch_assign<8, 4>(ap, d_W, d_pieces, d_cn, V, d, C, d_cand, st)
+             : ap.nt == 4 ? launch_assign<4, 4>(ap, d_W, d_pieces, d_cn, V, d, C, d_cand, st)
+                          : launch_assign<4, 2>(ap, d_W, d_pieces, d_cn, V, d, C, d_cand, st);
     };
+    bool assigned = false;               // the labels are the assignment's candidates (else: the caller's)
+    std::vector<int32_t> seed;
     if (o->h_init_labels) {
-        memcpy(labels.data(), o->h_init_labels, (size_t)V * 4);
+        for (int i = 0; i < V; ++i)
+            if (o->h_init_labels[i] < 0 || o->h_init_labels[i] >= C) { csv_set_error("label %d of token %d outside 0..C-1", o->h_init_labels[i], i); return fail(CSV_EINVAL); }
+        if (hipMemcpyAsync(d_labels, o->h_init_labels, (size_t)V * 4, hipMemcpyHostToDevice, st) != hipSuccess) { csv_set_error("copy of the labels failed"); return fail(CSV_EHIP); }
     } else {
         // seeding rule when the caller names no rows: C tokens evenly spread over the vocabulary, token floor(c V / C)
-        std::vector<int32_t> seed(C);
+        seed.resize(C);
         for (int c = 0; c < C; ++c) seed[c] = o->h_init_rows ? o->h_init_rows[c] : (int32_t)((long long)c * V / C);
         for (int c = 0; c < C; ++c)
             if (seed[c] < 0 || seed[c] >= V) { csv_set_error("init row %d outside 0..V-1", seed[c]); return fail(CSV_EINVAL); }
         // x->n doubles as the staging buffer for the starting rows
-        if (hipMemcpy(x->n, seed.data(), (size_t)C * 4, hipMemcpyHostToDevice) != hipSuccess) { csv_set_error("copy of init rows failed"); return fail(CSV_EHIP); }
+        if (hipMemcpyAsync(x->n, seed.data(), (size_t)C * 4, hipMemcpyHostToDevice, st) != hipSuccess) { csv_set_error("copy of init rows failed"); return fail(CSV_EHIP); }
         if (sph) init_direction_kernel<<<C, 256, 0, st>>>(d_W, x->n, d_nrm, d, x->mu);
         else init_centroid_kernel<<<C, 256, 0, st>>>(d_W, x->n, d, x->mu);
         if ((rc = assign())) return fail(rc);
+        assigned = true;
     }
+    int label_bits = 1;
+    while ((1 << label_bits) < C) ++label_bits;
     for (int it = 0;; ++it) {
-        if ((rc = layout_from_labels(labels.data(), V, C, n, off, perm))) return fail(rc);
-        if ((rc = upload_layout(x, n, off, perm, st))) return fail(rc);
-        if ((rc = gather(x, d_W, d_b, st))) return fail(rc);
         const bool last = it == o->iters;
+        label_hist_kernel<<<nw, 64, (size_t)C * 4, st>>>(assigned ? d_cand : nullptr, ap.ncol, d_labels, V, C, d_hist);
+        layout_scan_kernel<<<(C + 63) / 64, 512, 0, st>>>(d_hist, nw, C, x->n);
+        layout_offsets_kernel<<<1, 1024, 0, st>>>(x->n, C, x->off, d_coff, d_chunks);
+        layout_scatter_kernel<<<nw, 64, (size_t)C * 4, st>>>(d_labels, d_hist, x->off, V, C, label_bits, x->perm);
+        const dim3 kgrid(max_chunks, (d + 511) / 512), fgrid(C, (d + 255) / 256);
         if (sph) {
-            row_norm_kernel<<<(V + 3) / 4, 256, 0, st>>>(x->Wp, V, d, d_nrmp);
-            direction_sum_kernel<<<cgrid, 256, 0, st>>>(x->Wp, x->off, d_nrmp, d, d_sums);
+            centroid_chunk_kernel<true><<<kgrid, 256, 0, st>>>(d_W, x->perm, x->off, d_coff, d_chunks, d, C, d_nrm, x->mu, d_sums, d_part);
+            centroid_finish_kernel<true><<<fgrid, 256, 0, st>>>(x->off, d_coff, d, 0, d_part, x->mu, d_sums);
             direction_finish_kernel<<<C, 256, 0, st>>>(d_sums, x->off, d, last ? 1 : 0, x->mu);
         } else {
-            centroid_kernel<<<cgrid, 256, 0, st>>>(x->Wp, x->off, d, last ? 1 : 0, x->mu);
+            centroid_chunk_kernel<false><<<kgrid, 256, 0, st>>>(d_W, x->perm, x->off, d_coff, d_chunks, d, C, nullptr, x->mu, nullptr, d_part);
+            centroid_finish_kernel<false><<<fgrid, 256, 0, st>>>(x->off, d_coff, d, last ? 1 : 0, d_part, x->mu, nullptr);
         }
         if (hipGetLastError() != hipSuccess) { csv_set_error("launch of the centroid kernels failed"); return fail(CSV_EHIP); }
         if (last) break;
         if ((rc = assign())) return fail(rc);
-    }
-    {
-        int nmax = 1;
-        for (int c = 0; c < C; ++c) nmax = n[c] > nmax ? n[c] : nmax;
-        x->ln_nmax = (float)log((double)nmax);
-        x->n_max = nmax;
+        assigned = true;
     }
     if (o->centroid_bf16 && (rc = store_centroids_bf16(x, 0, st))) return fail(rc);
-    unsigned long long* d_d2max = nullptr;
-    double* d_d2row = nullptr;
-    const int bt_m = o->bias_table_m >= 2 ? o->bias_table_m : 0;
-    if (hipMalloc((void**)&d_d2max, (size_t)C * 8) != hipSuccess) { csv_set_error("out of device memory (radius scratch)"); return fail(CSV_ENOMEM); }
-    if (bt_m && (hipMalloc((void**)&d_d2row, (size_t)V * 8) != hipSuccess || hipMalloc((void**)&x->bt, (size_t)C * bt_m * sizeof(float2)) != hipSuccess)) {
-        (void)hipFree(d_d2max);
-        if (d_d2row) (void)hipFree(d_d2row);
-        csv_set_error("out of device memory (bias table)");
-        return fail(CSV_ENOMEM);
-    }
+    if (bt_m && hipMalloc((void**)&x->bt, (size_t)C * bt_m * sizeof(float2)) != hipSuccess) { csv_set_error("out of device memory (bias table)"); return fail(CSV_ENOMEM); }
     x->bt_m = bt_m;
     bool launched = hipMemsetAsync(d_d2max, 0, (size_t)C * 8, st) == hipSuccess;
     if (launched) {
-        row_dist_kernel<<<(V + 3) / 4, 256, 0, st>>>(x->Wp, x->off, x->mu, V, d, C, d_d2max, d_d2row);
+        gather_dist_kernel<<<max_chunks * 4, 256, 0, st>>>(d_W, d_b, x->perm, x->off, d_coff, d_chunks, x->mu, d, C, x->Wp, x->bp, d_d2max, d_d2row);
         launched = hipGetLastError() == hipSuccess;
     }
     if (launched && bt_m) {
@@ -868,29 +1033,34 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
         launched = hipGetLastError() == hipSuccess;
     }
     if (launched) launched = csv_index_pack_cmeta(x, st) == CSV_OK;
-    unsigned long long* d_ext = nullptr;
+    std::vector<unsigned long long> ext0;
     if (launched && sph) {          // angular metadata in place of the Euclidean radius (which stays unused)
-        std::vector<unsigned long long> init((size_t)3 * C);
+        ext0.resize((size_t)3 * C);
         for (int c = 0; c < C; ++c) {
-            init[3 * c] = ~0ull;
-            init[3 * c + 1] = 0ull;
-            init[3 * c + 2] = ~0ull;
+            ext0[3 * c] = ~0ull;
+            ext0[3 * c + 1] = 0ull;
+            ext0[3 * c + 2] = ~0ull;
         }
-        launched = hipMalloc((void**)&d_ext, (size_t)3 * C * 8) == hipSuccess && hipMalloc((void**)&x->ang, (size_t)C * sizeof(float4)) == hipSuccess &&
-                   hipMemcpy(d_ext, init.data(), (size_t)3 * C * 8, hipMemcpyHostToDevice) == hipSuccess;
+        launched = hipMalloc((void**)&x->ang, (size_t)C * sizeof(float4)) == hipSuccess &&
+                   hipMemcpyAsync(d_ext, ext0.data(), (size_t)3 * C * 8, hipMemcpyHostToDevice, st) == hipSuccess;
         if (launched) {
             row_angle_kernel<<<(V + 3) / 4, 256, 0, st>>>(x->Wp, x->off, x->mu, V, d, C, d_ext);
             angular_finish_kernel<<<(C + 255) / 256, 256, 0, st>>>(x->off, C, (double)o->radius_slack, CSV_ANGLE_SLACK, d_ext, x->ang);
             launched = hipGetLastError() == hipSuccess;
         }
     }
+    std::vector<int32_t> n(C);
+    if (launched) launched = hipMemcpyAsync(n.data(), x->n, (size_t)C * 4, hipMemcpyDeviceToHost, st) == hipSuccess;
     const bool synced = hipStreamSynchronize(st) == hipSuccess;
-    if (d_ext) (void)hipFree(d_ext);
-    (void)hipFree(d_d2max);
-    if (d_d2row) (void)hipFree(d_d2row);
     if (!launched) { csv_set_error("launch of the radius kernels failed"); return fail(CSV_EHIP); }
     if (!synced) { csv_set_error("index build failed on the device: %s", hipGetErrorString(hipGetLastError())); return fail(CSV_EHIP); }
-    free_scratch();
+    {
+        int nmax = 1;
+        for (int c = 0; c < C; ++c) nmax = n[c] > nmax ? n[c] : nmax;
+        x->ln_nmax = (float)log((double)nmax);
+        x->n_max = nmax;
+    }
+    (void)hipFree(arena);
     *out = x;
     return CSV_OK;
 }

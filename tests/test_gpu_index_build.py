@@ -35,3 +35,34 @@ def test_assignment_tiles_recover_planted_clusters(V, d, C):
     assert want.n[C] == 0
     _same_metadata(g.export(), want)
     g.free()
+
+
+# Cluster sizes around a chunk of 128 rows (and around several), empty clusters at both ends, V around a wave's 512 tokens, columns around
+# a block's 512, C around the 64 clusters of a scan block and the largest C.
+@pytest.mark.parametrize("sizes,d", [([0, 1, 127, 128, 129, 0, 255, 256, 257, 3000, 0], 520), ([512], 8), ([511], 512), ([200, 313], 1032),
+                                     ([3] * 63, 16), ([5] * 64 + [0], 16), ([4] * 65, 24), ([1] * 8000 + [0] * 191 + [700], 8)])
+@pytest.mark.parametrize("spherical", [False, True])
+def test_layout_and_centroids_from_labels(sizes, d, spherical):
+    import paper_2511_21702_amd as csv
+    C, V = len(sizes), sum(sizes)
+    rng = np.random.default_rng(V + d)
+    labels = rng.permutation(np.repeat(np.arange(C, dtype=np.int32), sizes))
+    W = synth.f32_to_bf16_bits(rng.normal(0, 1, (V, d)).astype(np.float32))
+    b = rng.normal(0, 0.1, V).astype(np.float32)
+    log(f"layout V={V} d={d} C={C} spherical={spherical}")
+    g = csv.csv_build_index(csv.bits_to_device(W), torch.from_numpy(b).cuda(), C, init_labels=labels, iters=0, spherical=spherical)
+    e = g.export()
+    if not spherical:
+        _same_metadata(e, O.build_index(W, b, labels, C))
+    else:
+        want = O.build_index_angular(W, b, labels, C)
+        assert np.array_equal(e["n"], want.n) and np.array_equal(e["perm"], want.perm) and np.array_equal(e["bmax"], want.bmax)
+        assert np.abs(e["mu"] - want.mu).max() <= 2.0 ** -23                     # unit directions, float64 sums rounded once
+    # the gathered copy: dense logits of a one-hot hidden state are one column of W plus the bias, in token order
+    ws = csv.CsvWorkspace(g, 1, max(1, V // 4))
+    h = np.zeros((1, d), np.uint16)
+    h[0, d - 3] = 0x3F80                                                         # 1.0
+    out = csv.csv_full_logits(ws, g, csv.bits_to_device(h)).cpu().numpy()[0]
+    assert np.array_equal(out, synth.bf16_bits_to_f32(W)[:, d - 3] + b)
+    ws.free()
+    g.free()
