@@ -262,7 +262,7 @@ __global__ __launch_bounds__(256) void gather_dist_kernel(const uint16_t* __rest
     if (chunk >= coff[C]) return;
     const int c = chunks[chunk].x, r0 = chunks[chunk].y, r1 = min(r0 + CHUNK_ROWS, off[c + 1]), np = d >> 3;
     const float4* m = reinterpret_cast<const float4*>(mu + (size_t)c * d);
-    double most = 0.0;
+    unsigned long long most = 0ull;                          // bit pattern: a row with NaN or infinity keeps its cluster's radius from being finite
     // a quarter of the chunk's rows per block, every fourth of those per wave
     for (int r = r0 + (blockIdx.x & 3) * 4 + wave; r < r1; r += 16) {
         const int src = perm[r];
@@ -295,13 +295,14 @@ __global__ __launch_bounds__(256) void gather_dist_kernel(const uint16_t* __rest
             }
         }
         acc = wave_sum_d(acc);
-        most = fmax(most, acc);
+        const unsigned long long bits = (unsigned long long)__double_as_longlong(acc);
+        most = bits > most ? bits : most;
         if (lane == 0) {
             bp[r] = b ? b[src] : 0.f;
             if (d2row) d2row[r] = acc;      // squared distance of every row, for the bias table
         }
     }
-    if (lane == 0) atomicMax(&d2max[c], (unsigned long long)__double_as_longlong(most));
+    if (lane == 0) atomicMax(&d2max[c], most);
 }
 
 // Top-m bias table of one cluster (one block per cluster): the m-1 rows with the largest bias (equal biases: the

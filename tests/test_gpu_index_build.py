@@ -66,3 +66,18 @@ def test_layout_and_centroids_from_labels(sizes, d, spherical):
     assert np.array_equal(out, synth.bf16_bits_to_f32(W)[:, d - 3] + b)
     ws.free()
     g.free()
+
+
+def test_a_row_that_is_not_finite_leaves_no_finite_radius():
+    """The infinite row's distance to its (infinite) centroid is not a number, the other rows' are infinite: the radius is the former."""
+    import paper_2511_21702_amd as csv
+    V, d, C = 600, 64, 3
+    rng = np.random.default_rng(7)
+    labels = np.arange(V, dtype=np.int32) % C
+    W = synth.f32_to_bf16_bits(rng.normal(0, 1, (V, d)).astype(np.float32))
+    W[301, 5] = 0x7F80                                                           # +inf, in cluster 1
+    log("radius of a cluster with an infinite row")
+    g = csv.csv_build_index(csv.bits_to_device(W), None, C, init_labels=labels, iters=0)
+    R = g.export()["R"]
+    assert np.isnan(R[1]) and np.isfinite(R[[0, 2]]).all()
+    g.free()
