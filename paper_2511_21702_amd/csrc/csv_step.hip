@@ -2443,21 +2443,26 @@ __device__ __forceinline__ void full_mfma_device(const FullArgs& f, int n, int s
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) A[kb][tw][jj] = ap[tw][min(sb * 16 + jj * 4 + g, nq - 1)];
         };
+        // Groups start at different chunks and wrap around: in step, all the blocks' rows would ask for the same columns at
+        // the same time, and with rows of a power of two in length those sit behind few of the memory channels (16 sequences at
+        // d = 8192, V = 128256: 404 -> 371 us; 5 to 8 at d = 4096: 228 -> 186 us; d = 4608 and 5120: no difference).
+        const int rot = grp % nchunk;
+        auto at = [&](int c) { return c + rot < nchunk ? c + rot : c + rot - nchunk; };
         auto stage_q = [&](int c, int s) {
             const int kbjj = wave / NT + (NW / NT) * s;
             return (c * MFMA_PIPE + (kbjj >> 2)) * 16 + (kbjj & 3) * 4 + g;
         };
         auto stage_load = [&](int c) {
 #pragma unroll
-            for (int s = 0; s < SPT; ++s) sreg[s] = st_h[min(stage_q(c, s), nq - 1)];
+            for (int s = 0; s < SPT; ++s) sreg[s] = st_h[min(stage_q(at(c), s), nq - 1)];
         };
         auto stage_store = [&](uint4* buf, int c) {
 #pragma unroll
-            for (int s = 0; s < SPT; ++s) buf[tid + MFMA_THREADS * s] = keep_if(st_on && stage_q(c, s) < nq, sreg[s]);
+            for (int s = 0; s < SPT; ++s) buf[tid + MFMA_THREADS * s] = keep_if(st_on && stage_q(at(c), s) < nq, sreg[s]);
         };
         stage_load(0);
 #pragma unroll
-        for (int kb = 0; kb < MFMA_PIPE; ++kb) load_A(kb, kb);
+        for (int kb = 0; kb < MFMA_PIPE; ++kb) load_A(kb, at(0) * MFMA_PIPE + kb);
         stage_store(lds, 0);
         lds_barrier();
         // The last chunk is a copy of the loop body without the requests for a next one: with the requests under a
@@ -2480,7 +2485,7 @@ __device__ __forceinline__ void full_mfma_device(const FullArgs& f, int n, int s
                                                                                  __builtin_bit_cast(bf16x8_t, A[kb][tw][jj]), acc[tw][t], 0, 0, 0);
                     }
                 __builtin_amdgcn_sched_barrier(0);
-                if (more) load_A(kb, (c + 1) * MFMA_PIPE + kb);
+                if (more) load_A(kb, at(c + 1) * MFMA_PIPE + kb);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (more) stage_store(lds + ((c + 1) & 1) * CH, c + 1);
