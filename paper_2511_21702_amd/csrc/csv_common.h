@@ -15,6 +15,7 @@ struct csv_index {
     uint16_t* Wp;    // [V*d] bf16, rows permuted so that every cluster is a contiguous range
     float* bp;       // [V]   permuted bias (zeros when the head has none)
     int32_t* perm;   // [V]   permuted row -> original token id
+    int32_t* inv;    // [V]   original token id -> permuted row
     float* mu;       // [C*d] centroids, float32
     uint16_t* mu16;  // [C*d] the same centroids as bf16 when they are stored rounded (NULL otherwise); mu then holds
                      //       the rounded values too
@@ -353,4 +354,4 @@ __device__ __forceinline__ float lse_value(LseAcc a) { return a.s == 0.f ? -INFI
 
 // ---------------------------------------------------------------------------------------------- internal entry points
 int csv_index_alloc(int V, int d, int C, csv_index** out);
-int csv_index_pack_cmeta(csv_index* x, hipStream_t st);   // fills cmeta from off and lnn (both final)
+int csv_index_pack_tables(csv_index* x, hipStream_t st);   // fills cmeta from off and lnn, and inv from perm (all final)

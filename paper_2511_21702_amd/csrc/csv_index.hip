@@ -768,17 +768,18 @@ __global__ __launch_bounds__(256) void angular_finish_kernel(const int32_t* __re
     ang[c] = make_float4(ct, st, up(nmax * (1.0 + slack)), down(nmin * (1.0 - slack)));
 }
 
-// cmeta[c] = {off[c], off[c+1] - off[c], bits of ln n_c, 0}
-__global__ __launch_bounds__(256) void pack_cmeta_kernel(const int32_t* __restrict__ off, const float* __restrict__ lnn, int C,
-                                                         int4* __restrict__ cmeta) {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c < C) cmeta[c] = make_int4(off[c], off[c + 1] - off[c], __float_as_int(lnn[c]), 0);
+// cmeta[c] = {off[c], off[c+1] - off[c], bits of ln n_c, 0};  inv[perm[r]] = r
+__global__ __launch_bounds__(256) void pack_tables_kernel(const int32_t* __restrict__ off, const float* __restrict__ lnn, const int32_t* __restrict__ perm,
+                                                          int C, int V, int4* __restrict__ cmeta, int32_t* __restrict__ inv) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < C) cmeta[i] = make_int4(off[i], off[i + 1] - off[i], __float_as_int(lnn[i]), 0);
+    if (i < V) inv[perm[i]] = i;
 }
 
 // ------------------------------------------------------------------------------------------------ host side
-int csv_index_pack_cmeta(csv_index* x, hipStream_t st) {
-    pack_cmeta_kernel<<<(x->C + 255) / 256, 256, 0, st>>>(x->off, x->lnn, x->C, x->cmeta);
-    CSV_LAUNCH_CHECK("pack_cmeta_kernel");
+int csv_index_pack_tables(csv_index* x, hipStream_t st) {          // C <= V
+    pack_tables_kernel<<<(x->V + 255) / 256, 256, 0, st>>>(x->off, x->lnn, x->perm, x->C, x->V, x->cmeta, x->inv);
+    CSV_LAUNCH_CHECK("pack_tables_kernel");
     return CSV_OK;
 }
 
@@ -794,7 +795,7 @@ int csv_index_alloc(int V, int d, int C, csv_index** out) {
     x->V = V; x->d = d; x->C = C;
     hipError_t e = hipGetDevice(&x->device);
     auto A = [&](void** p, size_t bytes) { if (e == hipSuccess) e = hipMalloc(p, bytes); };
-    A((void**)&x->Wp, (size_t)V * d * 2); A((void**)&x->bp, (size_t)V * 4); A((void**)&x->perm, (size_t)V * 4);
+    A((void**)&x->Wp, (size_t)V * d * 2); A((void**)&x->bp, (size_t)V * 4); A((void**)&x->perm, (size_t)V * 4); A((void**)&x->inv, (size_t)V * 4);
     A((void**)&x->mu, (size_t)C * d * 4); A((void**)&x->R, (size_t)C * 4); A((void**)&x->bmax, (size_t)C * 4);
     A((void**)&x->n, (size_t)C * 4); A((void**)&x->off, (size_t)(C + 1) * 4); A((void**)&x->lnn, (size_t)C * 4);
     A((void**)&x->cmeta, (size_t)C * sizeof(int4));
@@ -809,7 +810,7 @@ int csv_index_alloc(int V, int d, int C, csv_index** out) {
 
 extern "C" void csv_index_free(csv_index* x) {
     if (!x) return;
-    void* ptrs[] = {x->Wp, x->bp, x->perm, x->mu, x->mu16, x->R, x->bmax, x->n, x->off, x->lnn, x->cmeta, x->bt, x->ang};
+    void* ptrs[] = {x->Wp, x->bp, x->perm, x->inv, x->mu, x->mu16, x->R, x->bmax, x->n, x->off, x->lnn, x->cmeta, x->bt, x->ang};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     free(x);
@@ -1033,7 +1034,7 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
         radius_finish_kernel<<<C, 256, 0, st>>>(x->bp, x->off, x->mu, d, (double)o->radius_slack, d_d2max, x->R, x->bmax, x->lnn);
         launched = hipGetLastError() == hipSuccess;
     }
-    if (launched) launched = csv_index_pack_cmeta(x, st) == CSV_OK;
+    if (launched) launched = csv_index_pack_tables(x, st) == CSV_OK;
     std::vector<unsigned long long> ext0;
     if (launched && sph) {          // angular metadata in place of the Euclidean radius (which stays unused)
         ext0.resize((size_t)3 * C);
@@ -1104,7 +1105,7 @@ extern "C" int csv_index_from_arrays(const uint16_t* d_W, const float* d_b, int 
     if (e != hipSuccess) { csv_set_error("metadata upload failed: %s", hipGetErrorString(e)); return fail(CSV_EHIP); }
     if ((rc = upload_layout(x, n, off, perm, st))) return fail(rc);
     if ((rc = gather(x, d_W, d_b, st))) return fail(rc);
-    if ((rc = csv_index_pack_cmeta(x, st))) return fail(rc);
+    if ((rc = csv_index_pack_tables(x, st))) return fail(rc);
     if (hipStreamSynchronize(st) != hipSuccess) { csv_set_error("index import failed on the device"); return fail(CSV_EHIP); }
     *out = x;
     return CSV_OK;

@@ -2311,8 +2311,9 @@ struct FullArgs {
     const int32_t* list;    // sequences to score
     const int32_t* n_ptr;   // device count of entries in list, or NULL
     int n_fixed;            // count when n_ptr is NULL
-    float* out;             // [slot*out_stride + row]
+    float* out;             // [slot*out_stride + row*row_stride]
     long long out_stride;
+    int row_stride;         // 1, or (MFMA product) the number of sequences with out_stride = 1: a row's logits side by side
     int scatter;            // 1: write at the original token id instead of the permuted row
 };
 
@@ -2499,13 +2500,18 @@ __device__ __forceinline__ void full_mfma_device(const FullArgs& f, int n, int s
             if (row < f.V) {
                 const float bias = f.bp[row];
                 const size_t col = f.scatter ? (size_t)f.perm[row] : (size_t)row;
+                float* dst = f.out + col * f.row_stride;
 #pragma unroll
-                for (int t = 0; t < NT; ++t)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int sq = seq0 + t * 16 + 4 * g + r;
-                        if (sq < n) f.out[(size_t)sq * f.out_stride + col] = acc[tw][t][r] + bias;
+                for (int t = 0; t < NT; ++t) {
+                    const int sq = seq0 + t * 16 + 4 * g;
+                    if (f.row_stride > 1 && (n & 3) == 0) {       // four sequences of a row: one 16-byte store
+                        if (sq < n) *reinterpret_cast<float4*>(dst + sq) = make_float4(acc[tw][t][0] + bias, acc[tw][t][1] + bias, acc[tw][t][2] + bias, acc[tw][t][3] + bias);
+                        continue;
                     }
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (sq + r < n) dst[(size_t)(sq + r) * f.out_stride] = acc[tw][t][r] + bias;
+                }
             }
         }
     }
@@ -3094,11 +3100,33 @@ static int launch_bounds_kernel(const StepArgs& a, float* U, float* hn, int rese
     return CSV_OK;
 }
 
-// out[s][perm[r]] = tmp[s][r]: coalesced reads, scattered 4-byte writes, kept out of the streaming product kernel
-__global__ __launch_bounds__(256) void unpermute_kernel(const float* __restrict__ tmp, const int32_t* __restrict__ perm, int V,
+// out[s][t] = tmp[inv[t]][s]: the product leaves the n logits of a row side by side, so a token's are read as one run (of up
+// to 256 bytes a block) and turned in LDS, and everything is written in 256-byte runs.  Grid (tiles of 64 tokens, slabs of
+// 64 sequences).  A scatter of single logits to out[s][perm[r]], one 4-byte request each, was bound by the number of
+// requests: 53 us for 32 sequences at V = 256000, also with every sequence kept behind one XCD's L2.
+#define UNPERM_TILE 64
+__global__ __launch_bounds__(256) void unpermute_kernel(const float* __restrict__ tmp, const int32_t* __restrict__ inv, int V, int n,
                                                         float* __restrict__ out) {
-    const int r = blockIdx.x * 256 + threadIdx.x, s = blockIdx.y;
-    if (r < V) out[(size_t)s * V + perm[r]] = tmp[(size_t)s * V + r];
+    __shared__ float tile[UNPERM_TILE][UNPERM_TILE + 1];       // [token][sequence]
+    __shared__ int32_t row[UNPERM_TILE];
+    const int tid = threadIdx.x, t0 = blockIdx.x * UNPERM_TILE, s0 = blockIdx.y * UNPERM_TILE;
+    const int nt = min(UNPERM_TILE, V - t0), ns = min(UNPERM_TILE, n - s0);
+    if (tid < nt) row[tid] = inv[t0 + tid];
+    __syncthreads();
+    // the lanes of a wave read 64 / w runs of w values, w = ns rounded up to a power of two
+    int lw = 0;
+    while ((1 << lw) < ns) ++lw;
+    const int s = tid & ((1 << lw) - 1), per = 256 >> lw;
+    if (s < ns) {
+        const float* src = tmp + s0 + s;
+#pragma unroll 4
+        for (int t = tid >> lw; t < nt; t += per) tile[t][s] = src[(size_t)row[t] * n];
+    }
+    __syncthreads();
+    const int t = tid & 63;
+    if (t < nt)
+#pragma unroll 4
+        for (int q = tid >> 6; q < ns; q += 4) out[(size_t)(s0 + q) * V + t0 + t] = tile[t][q];
 }
 
 // tmp: [n_fixed x V] scratch for the MFMA path when the result is wanted in token-id order (may be NULL otherwise)
@@ -3106,7 +3134,7 @@ static int launch_full(const csv_index* idx, const uint16_t* d_h, const int32_t*
                        float* out, long long stride, int scatter, float* tmp, hipStream_t st) {
     FullArgs f;
     f.V = idx->V; f.d = idx->d; f.Wp = idx->Wp; f.bp = idx->bp; f.perm = idx->perm; f.h = d_h;
-    f.list = list; f.n_ptr = n_ptr; f.n_fixed = n_fixed; f.out = out; f.out_stride = stride; f.scatter = scatter;
+    f.list = list; f.n_ptr = n_ptr; f.n_fixed = n_fixed; f.out = out; f.out_stride = stride; f.row_stride = 1; f.scatter = scatter;
     if (!n_ptr && n_fixed > FULL_G) {
         int dev = 0, cus = 0;
         CSV_HIP(hipGetDevice(&dev));
@@ -3115,11 +3143,13 @@ static int launch_full(const csv_index* idx, const uint16_t* d_h, const int32_t*
         if (two_step) {
             f.out = tmp;
             f.scatter = 0;
+            f.out_stride = 1;
+            f.row_stride = n_fixed;
         }
         full_mfma_kernel<<<cus, MFMA_THREADS, MFMA_LDS, st>>>(f);
         CSV_LAUNCH_CHECK("full_mfma_kernel");
         if (two_step) {
-            unpermute_kernel<<<dim3((idx->V + 255) / 256, n_fixed), 256, 0, st>>>(tmp, idx->perm, idx->V, out);
+            unpermute_kernel<<<dim3((idx->V + UNPERM_TILE - 1) / UNPERM_TILE, (n_fixed + UNPERM_TILE - 1) / UNPERM_TILE), 256, 0, st>>>(tmp, idx->inv, idx->V, n_fixed, out);
             CSV_LAUNCH_CHECK("unpermute_kernel");
         }
         return CSV_OK;
@@ -3352,7 +3382,7 @@ extern "C" int csv_decode_step(csv_workspace* ws, const csv_index* idx, const ui
     CSV_MARK(1);
     FullArgs f;
     f.V = idx->V; f.d = idx->d; f.Wp = idx->Wp; f.bp = idx->bp; f.perm = idx->perm; f.h = d_h;
-    f.list = ws->fb_list; f.n_ptr = nullptr; f.n_fixed = 0; f.out = ws->fb_logits; f.out_stride = idx->V; f.scatter = 0;
+    f.list = ws->fb_list; f.n_ptr = nullptr; f.n_fixed = 0; f.out = ws->fb_logits; f.out_stride = idx->V; f.row_stride = 1; f.scatter = 0;
     if (p->schedule == CSV_SCHEDULE_ALG1) {
         // Algorithm 1's own order: one block per sequence opens one cluster per iteration; then the fallback launches
         const size_t general = (size_t)ws->Npad * 8 + (size_t)ws->C * 8 + 8;
