@@ -2317,67 +2317,69 @@ struct FullArgs {
     int scatter;            // 1: write at the original token id instead of the permuted row
 };
 
-// Vector path: FULL_G sequences per pass over W', h of the pass in LDS, two rows per wave at a time.
-__device__ __forceinline__ void full_gemv_device(const FullArgs& f, int n, uint4* hs4, int block, int nblocks) {
+// Vector path: NG <= FULL_G sequences (g0 ...) in one pass over W', their h in LDS, two rows per wave at a time and
+// FULL_PF pieces of each requested together.
+#define FULL_PF 4
+#define FULL_BLOCKS_MAX 8192
+template <int NG>
+__device__ __forceinline__ void full_gemv_pass(const FullArgs& f, int g0, uint4* hs4, int block, int nblocks) {
     const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6;
     const int nch = f.d >> 3;
     const int rpt = (nt >> 6) * 2;                 // rows per tile: two per wave
     const int ntiles = (f.V + rpt - 1) / rpt;
-    for (int g0 = 0; g0 < n; g0 += FULL_G) {
-        const int ng = min(FULL_G, n - g0);
-        __syncthreads();
-        for (int i = tid; i < FULL_G * nch; i += nt) {
-            const int s = i / nch, j = i - s * nch;
-            hs4[i] = s < ng ? (reinterpret_cast<const uint4*>(f.h) + (size_t)f.list[g0 + s] * nch)[j] : make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    for (int i = tid; i < NG * nch; i += nt) {
+        const int s = NG == 1 ? 0 : i / nch, j = i - s * nch;
+        hs4[i] = (reinterpret_cast<const uint4*>(f.h) + (size_t)f.list[g0 + s] * nch)[j];
+    }
+    __syncthreads();
+    for (int tile = block; tile < ntiles; tile += nblocks) {
+        const int r0 = tile * rpt + wave * 2;
+        if (r0 >= f.V) continue;
+        const bool two = r0 + 1 < f.V;
+        const int r1 = two ? r0 + 1 : r0;
+        const uint4* w0 = reinterpret_cast<const uint4*>(f.Wp + (size_t)r0 * f.d);
+        const uint4* w1 = reinterpret_cast<const uint4*>(f.Wp + (size_t)r1 * f.d);
+        float acc0[NG], acc1[NG];
+#pragma unroll
+        for (int s = 0; s < NG; ++s) acc0[s] = acc1[s] = 0.f;
+        auto add = [&](const uint4& a, const uint4& c, int i) {
+#pragma unroll
+            for (int s = 0; s < NG; ++s) {
+                const uint4 h = hs4[s * nch + i];
+                acc0[s] = dot8_bf16(a, h, acc0[s]);
+                acc1[s] = dot8_bf16(c, h, acc1[s]);
+            }
+        };
+        int i = lane;
+        for (; i + 64 * (FULL_PF - 1) < nch; i += 64 * FULL_PF) {
+            uint4 a[FULL_PF], c[FULL_PF];
+#pragma unroll
+            for (int q = 0; q < FULL_PF; ++q) a[q] = w0[i + 64 * q];
+#pragma unroll
+            for (int q = 0; q < FULL_PF; ++q) c[q] = w1[i + 64 * q];
+#pragma unroll
+            for (int q = 0; q < FULL_PF; ++q) add(a[q], c[q], i + 64 * q);
         }
-        __syncthreads();
-        for (int tile = block; tile < ntiles; tile += nblocks) {
-            const int r0 = tile * rpt + wave * 2;
-            if (r0 >= f.V) continue;
-            const bool two = r0 + 1 < f.V;
-            const int r1 = two ? r0 + 1 : r0;
-            const uint4* w0 = reinterpret_cast<const uint4*>(f.Wp + (size_t)r0 * f.d);
-            const uint4* w1 = reinterpret_cast<const uint4*>(f.Wp + (size_t)r1 * f.d);
-            float acc0[FULL_G], acc1[FULL_G];
+        for (; i < nch; i += 64) add(w0[i], w1[i], i);
 #pragma unroll
-            for (int s = 0; s < FULL_G; ++s) acc0[s] = acc1[s] = 0.f;
-            int i = lane;
-            for (; i + 64 < nch; i += 128) {
-                const uint4 a0 = w0[i], a1 = w0[i + 64];
-                const uint4 c0 = w1[i], c1 = w1[i + 64];
-#pragma unroll
-                for (int s = 0; s < FULL_G; ++s) {
-                    if (s < ng) {
-                        const uint4 h0 = hs4[s * nch + i], h1 = hs4[s * nch + i + 64];
-                        acc0[s] = dot8_bf16(a0, h0, acc0[s]);
-                        acc1[s] = dot8_bf16(c0, h0, acc1[s]);
-                        acc0[s] = dot8_bf16(a1, h1, acc0[s]);
-                        acc1[s] = dot8_bf16(c1, h1, acc1[s]);
-                    }
-                }
+        for (int s = 0; s < NG; ++s) {
+            const float v0 = wave_sum(acc0[s]), v1 = wave_sum(acc1[s]);
+            if (lane == 0) {
+                float* dst = f.out + (size_t)(g0 + s) * f.out_stride;
+                dst[f.scatter ? f.perm[r0] : r0] = v0 + f.bp[r0];
+                if (two) dst[f.scatter ? f.perm[r1] : r1] = v1 + f.bp[r1];
             }
-            for (; i < nch; i += 64) {
-                const uint4 a0 = w0[i], c0 = w1[i];
-#pragma unroll
-                for (int s = 0; s < FULL_G; ++s) {
-                    if (s < ng) {
-                        const uint4 h0 = hs4[s * nch + i];
-                        acc0[s] = dot8_bf16(a0, h0, acc0[s]);
-                        acc1[s] = dot8_bf16(c0, h0, acc1[s]);
-                    }
-                }
-            }
-#pragma unroll
-            for (int s = 0; s < FULL_G; ++s) {
-                if (s < ng) {
-                    const float v0 = wave_sum(acc0[s]), v1 = wave_sum(acc1[s]);
-                    if (lane == 0) {
-                        float* dst = f.out + (size_t)(g0 + s) * f.out_stride;
-                        dst[f.scatter ? f.perm[r0] : r0] = v0 + f.bp[r0];
-                        if (two) dst[f.scatter ? f.perm[r1] : r1] = v1 + f.bp[r1];
-                    }
-                }
-            }
+        }
+    }
+}
+__device__ __forceinline__ void full_gemv_device(const FullArgs& f, int n, uint4* hs4, int block, int nblocks) {
+    for (int g0 = 0; g0 < n; g0 += FULL_G) {
+        switch (min(FULL_G, n - g0)) {
+            case 1: full_gemv_pass<1>(f, g0, hs4, block, nblocks); break;
+            case 2: full_gemv_pass<2>(f, g0, hs4, block, nblocks); break;
+            case 3: full_gemv_pass<3>(f, g0, hs4, block, nblocks); break;
+            default: full_gemv_pass<4>(f, g0, hs4, block, nblocks); break;
         }
     }
 }
@@ -3154,9 +3156,11 @@ static int launch_full(const csv_index* idx, const uint16_t* d_h, const int32_t*
         }
         return CSV_OK;
     }
+    // Many short blocks rather than few that stay: the hardware hands them out in order, so the rows in flight lie close
+    // together (d = 4096, V = 128256: 186 us with 2048 blocks, 179 with 8192, 239 with 16032 of one tile each, where staging h shows)
     const int ntiles = (idx->V + 7) / 8;
-    const int grid = ntiles < 2048 ? ntiles : 2048;
-    full_gemv_kernel<<<grid, 256, (size_t)FULL_G * idx->d * 2, st>>>(f);
+    const int grid = ntiles < FULL_BLOCKS_MAX ? ntiles : FULL_BLOCKS_MAX;
+    full_gemv_kernel<<<grid, 256, (size_t)(n_fixed < FULL_G ? n_fixed : FULL_G) * idx->d * 2, st>>>(f);
     CSV_LAUNCH_CHECK("full_gemv_kernel");
     return CSV_OK;
 }
