@@ -401,21 +401,22 @@ __device__ __forceinline__ void lds_barrier() {      // all LDS accesses of the 
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// Grid (groups of 8 cluster tiles, K slices).  The block's slice of h goes to LDS once, in fragment order (1 KB per
+// Grid (groups of 8 cluster tiles, K slices, 64 sequences each: 256 sequences at C = 1024, d = 4096 take 4 x 8 us as launches of
+// their own).  The block's slice of h goes to LDS once, in fragment order (1 KB per
 // k-block and sequence tile, read without bank conflicts), zero where the sequence, the k-block or k itself lies
 // outside: centroid values can then be read from clamped addresses without a select, which would be waited for right
 // behind the load.  Every wave has BOUND_PIPE k-blocks of its 16 centroid rows requested ahead; a register buffer is
 // requested again as soon as its values are split.  The last chunk is a copy of the loop body without requests, so
 // that the waits the compiler places are counted at compile time.
 template <int NT, bool MU16>
-__global__ __launch_bounds__(512) void bound_mfma_kernel(StepArgs a, float* __restrict__ P, int seq0, int KS, int kb_per_slice,
+__global__ __launch_bounds__(512) void bound_mfma_kernel(StepArgs a, float* __restrict__ P, int kb_per_slice,
                                                          int reset_counters) {
     extern __shared__ uint4 bound_lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int li = lane & 15, g = lane >> 4;
-    if (reset_counters && blockIdx.x == 0 && blockIdx.y == 0)
+    if (reset_counters && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
         reset_step_counters(a.counters, a.B, 512, a.host_history, a.slots, a.B_max);
-    const int ks = blockIdx.y;
+    const int ks = blockIdx.y, seq0 = blockIdx.z * 64;
     const int nkb = (a.d + 31) >> 5;
     const int kb0 = ks * kb_per_slice, kb1 = min(nkb, kb0 + kb_per_slice);      // the host gives every slice at least one k-block
     const int nchunk = (kb1 - kb0 + BOUND_PIPE - 1) / BOUND_PIPE;
@@ -3030,23 +3031,19 @@ static int launch_bounds_kernel(const StepArgs& a, float* U, float* hn, int rese
         const int tiles = (a.C + 15) / 16;
         int KS, kbs;
         bound_mfma_plan(a.C, a.d, a.B, KS, kbs);
-        dim3 grid((tiles + BOUND_TILES_PER_BLOCK - 1) / BOUND_TILES_PER_BLOCK, KS);
-        for (int s0 = 0; s0 < a.B; s0 += 64) {
-            const int nseq = a.B - s0 < 64 ? a.B - s0 : 64;
-            const int r = reset && s0 == 0;
-            const int nt = nseq <= 16 ? 1 : (nseq <= 32 ? 2 : 4);
-            const size_t lds = (size_t)kbs * nt * 1024;
-            if (a.mu16) {
-                if (nt == 1) bound_mfma_kernel<1, true><<<grid, 512, lds, st>>>(a, a.bound_partial, s0, KS, kbs, r);
-                else if (nt == 2) bound_mfma_kernel<2, true><<<grid, 512, lds, st>>>(a, a.bound_partial, s0, KS, kbs, r);
-                else bound_mfma_kernel<4, true><<<grid, 512, lds, st>>>(a, a.bound_partial, s0, KS, kbs, r);
-            } else {
-                if (nt == 1) bound_mfma_kernel<1, false><<<grid, 512, lds, st>>>(a, a.bound_partial, s0, KS, kbs, r);
-                else if (nt == 2) bound_mfma_kernel<2, false><<<grid, 512, lds, st>>>(a, a.bound_partial, s0, KS, kbs, r);
-                else bound_mfma_kernel<4, false><<<grid, 512, lds, st>>>(a, a.bound_partial, s0, KS, kbs, r);
-            }
-            CSV_LAUNCH_CHECK("bound_mfma_kernel");
+        dim3 grid((tiles + BOUND_TILES_PER_BLOCK - 1) / BOUND_TILES_PER_BLOCK, KS, (a.B + 63) / 64);
+        const int nt = bound_mfma_nt(a.B);
+        const size_t lds = (size_t)kbs * nt * 1024;
+        if (a.mu16) {
+            if (nt == 1) bound_mfma_kernel<1, true><<<grid, 512, lds, st>>>(a, a.bound_partial, kbs, reset);
+            else if (nt == 2) bound_mfma_kernel<2, true><<<grid, 512, lds, st>>>(a, a.bound_partial, kbs, reset);
+            else bound_mfma_kernel<4, true><<<grid, 512, lds, st>>>(a, a.bound_partial, kbs, reset);
+        } else {
+            if (nt == 1) bound_mfma_kernel<1, false><<<grid, 512, lds, st>>>(a, a.bound_partial, kbs, reset);
+            else if (nt == 2) bound_mfma_kernel<2, false><<<grid, 512, lds, st>>>(a, a.bound_partial, kbs, reset);
+            else bound_mfma_kernel<4, false><<<grid, 512, lds, st>>>(a, a.bound_partial, kbs, reset);
         }
+        CSV_LAUNCH_CHECK("bound_mfma_kernel");
         bound_finish_kernel<<<dim3((a.C + 255) / 256, a.B), 256, 0, st>>>(a, a.bound_partial, KS, U, hn);
         CSV_LAUNCH_CHECK("bound_finish_kernel");
         return CSV_OK;
