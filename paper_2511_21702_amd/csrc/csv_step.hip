@@ -660,6 +660,30 @@ __device__ __forceinline__ void load_clusters(const StepArgs& a, int b, const Cl
     }
 }
 
+// fn(c, key, rows, term) for the thread's clusters, four at a time: all LDS reads of a trip are issued, from clamped indexes, before the
+// first is looked at (a read behind a test of another would add its latency to every cluster).  Past the end: key 0.
+template <bool ROWS, bool TERMS, class Fn>
+__device__ __forceinline__ void for_clusters(int C, const ClusterLds& L, Fn fn) {
+    const int nt = blockDim.x;
+    for (int c0 = threadIdx.x; c0 < C; c0 += 4 * nt) {
+        u64 k[4];
+        int o0[4], o1[4];
+        float v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int cc = min(c0 + q * nt, C - 1);
+            k[q] = L.keys[cc];
+            if (ROWS) {
+                o0[q] = L.offl[cc];
+                o1[q] = L.offl[cc + 1];
+            }
+            if (TERMS) v[q] = L.vl[cc];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) fn(c0 + q * nt, c0 + q * nt < C ? k[q] : 0ull, ROWS ? o1[q] - o0[q] : 0, TERMS ? v[q] : 0.f);
+    }
+}
+
 // Exclusive prefix sums of three ints per thread in one pass.  wtot: 48 ints of LDS.
 __device__ __forceinline__ void block_excl_scan3(int& v0, int& v1, int& v2, int* wtot, int& t0, int& t1, int& t2) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
@@ -759,7 +783,104 @@ __device__ __forceinline__ void emit_clusters(const StepArgs& a, int b, int roun
     __syncthreads();
 }
 
+// The same for at most SEQ_THREADS opened clusters of an index of at most EMIT_LIST_C, cnt of them (the block has SEQ_THREADS
+// threads): the opened ids go into a list in id order, a thread takes one of them for the prefix sums, and the
+// tiles are then written one per thread, neighbouring threads side by side.  emit_clusters gives each thread a run of neighbouring
+// clusters, whose LDS reads fall on few banks, and mostly one thread writes all the tiles of a cluster: 3.7-5.6 us
+// at C = 4096 with 8 to 52 clusters of 62 rows, 4.0 this way; 4.2-5.0 and 3.2 at C = 2048 with clusters of very unequal sizes.  opens: a test of a cluster's key (false for 0).  Uses s.hist, s.rank, s.wval and s.wid (the
+// caller's top-k list is dead by then); the caller passes a barrier before it uses them again.
+#define EMIT_LIST_C 16384      // s.hist counts 256 groups of 64 clusters; a thread keeps its up to 32 answers in one word
+static_assert(EMIT_LIST_C <= 256 * 64 && EMIT_LIST_C <= 32 * SEQ_THREADS, "emit_list: groups and answers");
+template <class OpensFn>
+__device__ __forceinline__ void emit_list(const StepArgs& a, int b, int round, int pos_base, int sel_base, int cnt, OpensFn opens,
+                                          const ClusterLds& L, SeqShared& s) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, C = a.C;
+    constexpr int NW = SEQ_THREADS / 64;
+    __syncthreads();
+    if (tid < 256) s.hist[tid] = 0u;
+    __syncthreads();
+    // trip i of a thread is cluster tid + SEQ_THREADS i, and the 64 clusters of a wave's trip are group wave + NW i
+    unsigned mine = 0;
+    int trip = 0;
+    for_clusters<false, false>(C, L, [&](int, u64 kx, int, float) {
+        mine |= (opens(kx) ? 1u : 0u) << trip;
+        ++trip;
+    });
+    const int trips = (C + SEQ_THREADS - 1) / SEQ_THREADS;
+    for (int i = 0; i < trips; ++i) {
+        const unsigned long long bal = __ballot((mine >> i) & 1u);
+        if (lane == 0) s.hist[wave + NW * i] = (unsigned)__popcll(bal);
+    }
+    __syncthreads();
+    if (tid < 64) {                                                  // groups before each one, lane l: groups 4l..4l+3
+        unsigned h[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) h[q] = s.hist[4 * lane + q];
+        const unsigned sum = h[0] + h[1] + h[2] + h[3];
+        unsigned x = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned y = __shfl_up(x, o, CSV_WAVE);
+            if (lane >= o) x += y;
+        }
+        x -= sum;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            s.hist[4 * lane + q] = x;
+            x += h[q];
+        }
+    }
+    __syncthreads();
+    for (int i = 0; i < trips; ++i) {
+        const bool on = (mine >> i) & 1u;
+        const unsigned long long bal = __ballot(on);
+        if (on) s.rank[s.hist[wave + NW * i] + __popcll(bal & ((1ull << lane) - 1ull))] = tid + SEQ_THREADS * i;
+    }
+    __syncthreads();
+    int one = 0, rows = 0, tiles = 0, c = 0, n = 0;
+    if (tid < cnt) {
+        c = s.rank[tid];
+        n = L.offl[c + 1] - L.offl[c];
+        rows = n;
+        tiles = (n + TILE_ROWS - 1) / TILE_ROWS;
+    }
+    int tot_one, tot_rows, tot_tiles;
+    block_excl_scan3(one, rows, tiles, s.scan3, tot_one, tot_rows, tot_tiles);
+    int* pos = reinterpret_cast<int*>(s.wval);
+    if (tid < cnt) {
+        s.wid[tid] = tiles;
+        pos[tid] = pos_base + rows;
+    }
+    __syncthreads();                       // no store to global memory before this: a barrier waits for those too
+    if (tid < cnt) a.sel[(size_t)b * C + sel_base + tid] = c;
+    if (tid == 0) {
+        a.counters[CNT_TILES + round * CSV_MAX_BATCH + b] = tot_tiles;
+        __hip_atomic_store(&a.counters[CNT_TAIL_NEEDED], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    Tile* tl = a.tiles[round & 1] + (size_t)b * a.tile_stride;
+    for (int g = tid; g < tot_tiles; g += SEQ_THREADS) {
+        int lo = 0, hi = cnt;               // the last cluster whose tiles start at or before g (every one has at least one)
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (s.wid[mid] <= g) lo = mid; else hi = mid;
+        }
+        const int t = g - s.wid[lo], cc = s.rank[lo], r0 = L.offl[cc], m = L.offl[cc + 1] - r0;
+        Tile x;
+        x.b = b; x.row0 = r0 + t * TILE_ROWS; x.nrows = min(TILE_ROWS, m - t * TILE_ROWS); x.pos = pos[lo] + t * TILE_ROWS;
+        tl[g] = x;
+    }
+}
+
 // Largest bound and log tail mass over the unopened clusters {c : 0 < key_c < kappa}: a max pass, then a sum pass.
+// (best, vmax: the largest key and term among them)
+__device__ __forceinline__ void tail_mass(const StepArgs& a, const ClusterLds& L, u64 kappa, u64 best, float vmax, SeqShared& s, float& nxtU, float& T) {
+    float sum = 0.f;
+    if (vmax > -INFINITY)
+        for_clusters<false, true>(a.C, L, [&](int, u64 kx, int, float v) { sum += kx != 0 && kx < kappa ? expf(v - vmax) : 0.f; });
+    sum = block_sum(sum, s.redf);
+    nxtU = best ? ckey_bound(best) : -INFINITY;
+    T = vmax > -INFINITY ? vmax + logf(sum) : -INFINITY;
+}
 __device__ __forceinline__ void tail_stats(const StepArgs& a, const ClusterLds& L, u64 kappa, SeqShared& s, float& nxtU, float& T) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
     u64 best = 0;
@@ -785,15 +906,48 @@ __device__ __forceinline__ void tail_stats(const StepArgs& a, const ClusterLds& 
         best = s.redu[i] > best ? s.redu[i] : best;
         vmax = fmaxf(vmax, s.redf[i]);
     }
-    float sum = 0.f;
-    if (vmax > -INFINITY)
-        for (int c = threadIdx.x; c < a.C; c += blockDim.x) {
-            const u64 kx = L.keys[c];
-            if (kx != 0 && kx < kappa) sum += expf(L.vl[c] - vmax);
-        }
-    sum = block_sum(sum, s.redf);
-    nxtU = best ? ckey_bound(best) : -INFINITY;
-    T = vmax > -INFINITY ? vmax + logf(sum) : -INFINITY;
+    tail_mass(a, L, kappa, best, vmax, s, nxtU, T);
+}
+
+// What a plan needs to know of the clusters, in one pass and one reduction instead of two passes and three (C = 4096: with the
+// log tail mass 7.0 us, 7.7 before): the clusters with kappa1 <= key < kappa0 (those
+// it opens) and their rows, and of those below kappa1 the largest key and the largest term of the log tail mass (kappa1 <= kappa0).
+struct PlanSums {
+    int cnt, rows;
+    u64 best;
+    float vmax;
+};
+__device__ __forceinline__ PlanSums plan_sweep(const StepArgs& a, const ClusterLds& L, u64 kappa0, u64 kappa1, SeqShared& s) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+    PlanSums p;
+    p.cnt = p.rows = 0; p.best = 0; p.vmax = -INFINITY;
+    for_clusters<true, true>(a.C, L, [&](int, u64 kx, int n, float v) {
+        const bool on = kx != 0 && kx >= kappa1 && kx < kappa0, rest = kx != 0 && kx < kappa1;
+        p.cnt += on ? 1 : 0;
+        p.rows += on ? n : 0;
+        p.best = rest && kx > p.best ? kx : p.best;
+        p.vmax = fmaxf(p.vmax, rest ? v : -INFINITY);
+    });
+    p.cnt = wave_sum_i(p.cnt);
+    p.rows = wave_sum_i(p.rows);
+    p.best = wave_max_u64(p.best);
+    p.vmax = wave_max(p.vmax);
+    __syncthreads();
+    if (lane == 0) {
+        s.scan3[w] = p.cnt;
+        s.scan3[16 + w] = p.rows;
+        s.redu[w] = p.best;
+        s.redf[w] = p.vmax;
+    }
+    __syncthreads();
+    p.cnt = s.scan3[0]; p.rows = s.scan3[16]; p.best = s.redu[0]; p.vmax = s.redf[0];
+    for (int i = 1; i < nw; ++i) {
+        p.cnt += s.scan3[i];
+        p.rows += s.scan3[16 + i];
+        p.best = s.redu[i] > p.best ? s.redu[i] : p.best;
+        p.vmax = fmaxf(p.vmax, s.redf[i]);
+    }
+    return p;
 }
 
 // ================================================================================================ gathered GEMV
@@ -1210,6 +1364,44 @@ __device__ __forceinline__ LseAcc block_lse(int n, ValFn val, SeqShared& s) {
 }
 
 // ================================================================================================ prefix search
+// The first wave: of 256 classes of ascending keys (H: weights, cnt: members) the largest that is not empty and has at most the
+// limit (2^40) below it, base included.  Leaves it in s.sel and the weight below it in s.redu[0].
+__device__ __forceinline__ void prefix_pick(const u64* H, const unsigned* cnt, u64 base, SeqShared& s) {
+    const int lane = threadIdx.x & 63;
+    // lane l owns digits 4l..4l+3; weights below a digit by an ascending scan inside the first wave
+    u64 h[4];
+    unsigned n4[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        h[q] = H[4 * lane + q];
+        n4[q] = cnt[4 * lane + q];
+    }
+    const u64 mine = h[0] + h[1] + h[2] + h[3];
+    u64 x = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const u64 y = __shfl_up(x, o, CSV_WAVE);
+        if (lane >= o) x += y;
+    }
+    u64 below[4];
+    below[0] = base + (x - mine);
+    below[1] = below[0] + h[0];
+    below[2] = below[1] + h[1];
+    below[3] = below[2] + h[2];
+    int pick = -1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (n4[q] != 0 && below[q] <= (1ull << 40)) pick = 4 * lane + q;
+    const int best = (int)wave_max_u((unsigned)(pick + 1)) - 1;
+    if (best >= 0 && (best >> 2) == lane) {
+        s.sel = (unsigned)best;
+        s.redu[0] = below[best & 3];
+    }
+    if (best < 0 && lane == 0) {                  // cannot happen (the smallest key has nothing below it); stay defined
+        s.sel = 0u;
+        s.redu[0] = base;
+    }
+}
 // The shortest prefix of the bound order, no shorter than the open one, whose log tail mass is within lam of Z0
 // (Theorem 2): returns the key of its last cluster.  In terms of keys: the largest key kappa <= kappa0 such that the
 // clusters below it weigh  sum_{key_c < kappa} n_c exp(U_c)  <=  exp(Z0 + lam).  No sort: the key is found digit by
@@ -1219,13 +1411,15 @@ __device__ __forceinline__ LseAcc block_lse(int n, ValFn val, SeqShared& s) {
 // the largest such digit is taken.  Weights are summed as 64-bit fixed point relative to the limit (2^-40 steps, each
 // term capped at 2^9, which already exceeds the limit of 1): integer sums do not depend on the order of the atomic
 // additions, so the result is the same in every run.  Leaves the cluster data in LDS as it is.  Uses s.rank and s.hist.
-__device__ __forceinline__ u64 softmax_prefix_key(const StepArgs& a, const ClusterLds& L, u64 kappa0, float Z0, SeqShared& s) {
-    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63;
+// among: the clusters to search, base: the weight of everything below them (all clusters and 0 unless softmax_prefix_fast has
+// narrowed them down).
+template <class AmongFn>
+__device__ __forceinline__ u64 softmax_prefix_key(const StepArgs& a, const ClusterLds& L, u64 kappa0, float Z0, SeqShared& s, AmongFn among, u64 base) {
+    const int tid = threadIdx.x, nt = blockDim.x;
     u64* H = reinterpret_cast<u64*>(s.rank);               // 256 weights
     unsigned* cnt = s.hist;                                // 256 counts
     const float shift = Z0 + a.lam;
-    const u64 LIMIT = 1ull << 40;
-    u64 prefix = 0, base = 0;
+    u64 prefix = 0;
     for (int sb = 56; sb >= 0; sb -= 8) {
         if (sb == 24 || sb == 16) {                        // bits 16..31 of ~c: ones for every cluster id below 65536
             prefix |= 0xffull << sb;
@@ -1239,7 +1433,7 @@ __device__ __forceinline__ u64 softmax_prefix_key(const StepArgs& a, const Clust
         for (int c = tid; c < a.C; c += nt) {
             const u64 kx = L.keys[c];
             const bool match = sb == 56 || ((kx ^ prefix) >> (sb + 8)) == 0;
-            if (kx != 0 && kx <= kappa0 && match) {
+            if (kx != 0 && kx <= kappa0 && match && among(kx)) {
                 const float e = expf(fminf(L.vl[c] - shift, 6.f));         // e^6 < 2^9
                 const unsigned dg = (unsigned)(kx >> sb) & 255u;
                 atomicAdd(reinterpret_cast<unsigned long long*>(&H[dg]), (unsigned long long)(e * 1099511627776.f));
@@ -1247,47 +1441,85 @@ __device__ __forceinline__ u64 softmax_prefix_key(const StepArgs& a, const Clust
             }
         }
         __syncthreads();
-        if (tid < 64) {
-            // lane l owns digits 4l..4l+3; weights below a digit by an ascending scan inside the first wave
-            u64 h[4];
-            unsigned n4[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                h[q] = H[4 * lane + q];
-                n4[q] = cnt[4 * lane + q];
-            }
-            const u64 mine = h[0] + h[1] + h[2] + h[3];
-            u64 x = mine;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const u64 y = __shfl_up(x, o, CSV_WAVE);
-                if (lane >= o) x += y;
-            }
-            u64 below[4];
-            below[0] = base + (x - mine);
-            below[1] = below[0] + h[0];
-            below[2] = below[1] + h[1];
-            below[3] = below[2] + h[2];
-            int pick = -1;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (n4[q] != 0 && below[q] <= LIMIT) pick = 4 * lane + q;
-            const int best = (int)wave_max_u((unsigned)(pick + 1)) - 1;
-            if (best >= 0 && (best >> 2) == lane) {
-                s.sel = (unsigned)best;
-                s.redu[0] = below[best & 3];
-            }
-            if (best < 0 && lane == 0) {                  // cannot happen (the smallest key has nothing below it); stay defined
-                s.sel = 0u;
-                s.redu[0] = base;
-            }
-        }
+        if (tid < 64) prefix_pick(H, cnt, base, s);
         __syncthreads();
         prefix |= (u64)s.sel << sb;
         base = s.redu[0];
     }
     __syncthreads();
     return prefix;
+}
+
+// The same key, found sooner: 256 classes of equal width between the smallest and the largest bound instead of leading digits.
+// Nearly all bounds share their first digits, and 64-bit LDS additions to one address go one after the other (the
+// digits took 7.4 us at C = 1024, mostly that; this way 4.2 us).  The class of a bound is a monotone function of it, so the class that holds the
+// answer is picked as a digit is; up to 64 members of it then settle it in every wave alone: each lane adds up what lies
+// below its own key.  The sums are the same integers, so the answer is the same key.  More members: the digits, among
+// them only.  Bounds that are not finite, or too close together for a finite class width: the digits, from the start.
+__device__ __forceinline__ u64 softmax_prefix_fast(const StepArgs& a, const ClusterLds& L, u64 kappa0, float Z0, SeqShared& s) {
+    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63;
+    const float shift = Z0 + a.lam;
+    float up = -INFINITY, down = -INFINITY;                // the largest bound, the largest negated bound
+    for_clusters<false, false>(a.C, L, [&](int, u64 kx, int, float) {
+        const bool on = kx != 0 && kx <= kappa0;
+        const float u = ckey_bound(kx);
+        up = fmaxf(up, on ? (isfinite(u) ? u : INFINITY) : -INFINITY);
+        down = fmaxf(down, on ? -u : -INFINITY);
+    });
+    up = wave_max(up);
+    down = wave_max(down);
+    __syncthreads();
+    if (lane == 0) {
+        s.redf[tid >> 6] = up;
+        s.redi[tid >> 6] = __float_as_int(down);
+    }
+    __syncthreads();
+    for (int i = 0; i < (nt >> 6); ++i) {
+        up = fmaxf(up, s.redf[i]);
+        down = fmaxf(down, __int_as_float(s.redi[i]));
+    }
+    const float lo = -down, scale = 256.f / (up - lo);
+    if (!(isfinite(up) && isfinite(lo) && isfinite(scale) && scale > 0.f))
+        return softmax_prefix_key(a, L, kappa0, Z0, s, [](u64) { return true; }, 0ull);
+    auto cls = [&](u64 kx) { return (unsigned)fminf((ckey_bound(kx) - lo) * scale, 255.f); };
+    auto weight = [&](float v) { return (u64)(expf(fminf(v - shift, 6.f)) * 1099511627776.f); };       // as in the digit search
+    u64* H = reinterpret_cast<u64*>(s.rank);
+    unsigned* cnt = s.hist;
+    if (tid < 256) {
+        H[tid] = 0ull;
+        cnt[tid] = 0u;
+    }
+    __syncthreads();
+    for_clusters<false, true>(a.C, L, [&](int, u64 kx, int, float v) {
+        if (kx == 0 || kx > kappa0) return;
+        const unsigned q = cls(kx);
+        atomicAdd(reinterpret_cast<unsigned long long*>(&H[q]), (unsigned long long)weight(v));
+        atomicAdd(&cnt[q], 1u);
+    });
+    __syncthreads();
+    if (tid < 64) prefix_pick(H, cnt, 0ull, s);
+    if (tid == 0) s.cnt = 0;
+    __syncthreads();
+    const unsigned q0 = s.sel;
+    const int m = (int)cnt[q0];
+    const u64 base = s.redu[0];
+    __syncthreads();                                       // everyone has read the class: its members take its place
+    if (m > 64) return softmax_prefix_key(a, L, kappa0, Z0, s, [&](u64 kx) { return cls(kx) == q0; }, base);
+    u64* mk = H;
+    u64* mw = H + 64;
+    for_clusters<false, true>(a.C, L, [&](int, u64 kx, int, float v) {
+        if (kx == 0 || kx > kappa0 || cls(kx) != q0) return;
+        const unsigned i = atomicAdd(&s.cnt, 1u);
+        mk[i] = kx;
+        mw[i] = weight(v);
+    });
+    __syncthreads();
+    const u64 mine = lane < m ? mk[lane] : 0ull;
+    u64 below = base;
+    for (int i = 0; i < m; ++i) below += mk[i] < mine ? mw[i] : 0ull;
+    const u64 best = wave_max_u64(mine != 0 && below <= (1ull << 40) ? mine : 0ull);
+    __syncthreads();
+    return best;
 }
 
 // Ordered top-kk (value descending, id ascending) of len <= blockDim.x values V in LDS with ids I; V is followed by
@@ -1695,13 +1927,13 @@ __device__ __forceinline__ bool cert_body(const StepArgs& a, int b, int chunk, i
                 // when the top-k threshold alone opens more rows than allowed, the joint plan (a superset) does too:
                 // the sorted prefix search for the softmax threshold would change nothing
                 int r2 = 0;
-                for (int c = tid; c < C; c += nt) {
-                    const u64 kx = L.keys[c];
-                    if (kx >= kappa_a && kx < kappa0 && kx != 0) r2 += L.offl[c + 1] - L.offl[c];
-                }
+                for_clusters<true, false>(C, L, [&](int, u64 kx, int m, float) { r2 += kx >= kappa_a && kx < kappa0 && kx != 0 ? m : 0; });
                 hopeless = n + block_sum_i(r2, s.redi) > a.K_max;
             }
-            if (!hopeless) kappa_s = softmax_prefix_key(a, L, kappa0, Z, s);
+            if (!hopeless) {
+                if constexpr (THRESH) kappa_s = softmax_prefix_fast(a, L, kappa0, Z, s);
+                else kappa_s = softmax_prefix_key(a, L, kappa0, Z, s, [](u64) { return true; }, 0ull);
+            }
             intact = true;
         }
         u64 kappa1;
@@ -1714,15 +1946,23 @@ __device__ __forceinline__ bool cert_body(const StepArgs& a, int b, int chunk, i
             __syncthreads();
         }
         int cnt = 0, rows = 0;
-        for (int c = tid; c < C; c += nt) {
-            const u64 kx = L.keys[c];
-            if (kx >= kappa1 && kx < kappa0 && kx != 0) {
-                cnt += 1;
-                rows += L.offl[c + 1] - L.offl[c];
+        PlanSums ps;
+        if constexpr (THRESH) {
+            ps = plan_sweep(a, L, kappa0, kappa1, s);
+            cnt = ps.cnt;
+            rows = ps.rows;
+        } else {
+            for (int c = tid; c < C; c += nt) {
+                const u64 kx = L.keys[c];
+                if (kx >= kappa1 && kx < kappa0 && kx != 0) {
+                    cnt += 1;
+                    rows += L.offl[c + 1] - L.offl[c];
+                }
             }
+            cnt = block_sum_i(cnt, s.redi);
+            rows = block_sum_i(rows, s.redi);
         }
-        cnt = block_sum_i(cnt, s.redi);
-        rows = block_sum_i(rows, s.redi);
+        bool whole = true;                                 // the plan as swept, not a part of it
         bool expand = n + rows <= a.K_max;
         if (!expand) {
             if (tid == 0) {          // sizes of the plan that did not fit (reported if the sequence falls back)
@@ -1750,16 +1990,20 @@ __device__ __forceinline__ bool cert_body(const StepArgs& a, int b, int chunk, i
             }
             if (add > 0) {
                 kappa1 = kp;
+                whole = false;
                 cnt = add;
                 rows = radd;
                 expand = true;
             }
         }
         if (expand) {
-            auto isnew = [&](int c) { const u64 kx = L.keys[c]; return kx >= kappa1 && kx < kappa0 && kx != 0; };
+            auto opens = [&](u64 kx) { return kx >= kappa1 && kx < kappa0 && kx != 0; };
+            auto isnew = [&](int c) { return opens(L.keys[c]); };
             float nxtU, T1;
-            tail_stats(a, L, kappa1, s, nxtU, T1);
-            emit_clusters(a, b, round + 1, n, st.n_open, isnew, L, s);
+            if (THRESH && whole) tail_mass(a, L, kappa1, ps.best, ps.vmax, s, nxtU, T1);
+            else tail_stats(a, L, kappa1, s, nxtU, T1);
+            if (THRESH && cnt <= SEQ_THREADS && C <= EMIT_LIST_C) emit_list(a, b, round + 1, n, st.n_open, cnt, opens, L, s);
+            else emit_clusters(a, b, round + 1, n, st.n_open, isnew, L, s);
             if (tid == 0) {
                 SeqState o = st;
                 o.n_open = st.n_open + cnt; o.n_rows = n + rows; o.rounds = round + 1; o.kappa = kappa1; o.nxtU = nxtU; o.T = T1;
@@ -1899,6 +2143,7 @@ __device__ __forceinline__ void wave_seed_tail(const StepArgs& a, const WaveSeed
 // sequence: 1 when the sequence is finished (certified, or flagged invalid), 2 when it left work for later phases
 // (a planned round, a hand-over, a fallback) or gave up.
 // settled_count: where a sequence that finishes here is counted as soon as that is decided (the return value is then 3).
+template <bool SPLIT>
 __device__ __forceinline__ int round0_device(const StepArgs& a, int b, int j, int NB, SeqShared& s, int* settled_count = nullptr) {
     extern __shared__ __align__(16) u64 arena[];
     const int tid = threadIdx.x, nt = SEQ_THREADS, lane = tid & 63, wave = tid >> 6, C = a.C;
@@ -2150,7 +2395,7 @@ __device__ __forceinline__ int round0_device(const StepArgs& a, int b, int j, in
         }
         return 2;
     }
-    return cert_body<false>(a, b, 0, 0, st, s, true, settled_count) ? (settled_count ? 3 : 1) : 2;     // every path of it that leaves work behind writes the state it needs
+    return cert_body<SPLIT>(a, b, 0, 0, st, s, true, settled_count) ? (settled_count ? 3 : 1) : 2;     // every path of it that leaves work behind writes the state it needs
 }
 
 // ================================================================================================ Algorithm 1's own order
@@ -2850,7 +3095,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void tail_kernel(StepArgs a, FullArgs
 // Plain form, grid NB x B: round 0 only; what follows is launched separately.
 __global__ __launch_bounds__(SEQ_THREADS) void round0_kernel(StepArgs a, int NB) {
     __shared__ SeqShared s;
-    round0_device(a, blockIdx.x / NB, blockIdx.x % NB, NB, s);
+    round0_device<true>(a, blockIdx.x / NB, blockIdx.x % NB, NB, s);
 }
 
 // Fused form, used while recent steps rarely needed anything after round 0: the first NB x B blocks run round 0,
@@ -2865,7 +3110,7 @@ __global__ __launch_bounds__(SEQ_THREADS) void step_kernel(StepArgs a, FullArgs 
     __shared__ int s_flag;
     const int n0 = NB * a.B;
     if ((int)blockIdx.x < n0) {
-        const int settled = round0_device(a, blockIdx.x / NB, blockIdx.x % NB, NB, s, &a.counters[CNT_R0_DONE]);
+        const int settled = round0_device<false>(a, blockIdx.x / NB, blockIdx.x % NB, NB, s, &a.counters[CNT_R0_DONE]);
         if (!settled || settled == 3) return;          // 3: finished and already counted
         __syncthreads();                      // all of the block's writes are issued
         if (threadIdx.x == 0) {
