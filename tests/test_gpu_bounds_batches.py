@@ -1,7 +1,6 @@
 """Cluster bounds of batches around the 64 sequences that one block of the batched product carries."""
 import numpy as np
 import pytest
-import torch
 
 import synth
 
