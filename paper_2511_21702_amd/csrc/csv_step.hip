@@ -2652,6 +2652,7 @@ __global__ __launch_bounds__(256) void full_gemv_kernel(FullArgs f) {
 // h is fed as the first operand and W' as the second, so accumulator register r of lane (li, g) is
 // out[sequence 4g + r][row li]: stores are 64-byte runs per sequence instead of 4-byte pieces 4V bytes apart.
 #define MFMA_THREADS 512
+#define FULL_K_LEVELS 2             // four parts of K where it is cut
 #define MFMA_LDS (64 * 1024)        // two buffers of K blocks x 4 fragments x 1 KB x groups of 16 sequences: at most 2x4
 template <int NT, int TW, int MFMA_PIPE>
 __device__ __forceinline__ void full_mfma_device(const FullArgs& f, int n, int seq0, uint4* lds, int block, int nblocks) {
@@ -2692,34 +2693,61 @@ __device__ __forceinline__ void full_mfma_device(const FullArgs& f, int n, int s
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) A[kb][tw][jj] = ap[tw][min(sb * 16 + jj * 4 + g, nq - 1)];
         };
-        // Groups start at different chunks and wrap around: in step, all the blocks' rows would ask for the same columns at
-        // the same time, and with rows of a power of two in length those sit behind few of the memory channels (16 sequences at
-        // d = 8192, V = 128256: 404 -> 371 us; 5 to 8 at d = 4096: 228 -> 186 us; d = 4608 and 5120: no difference).
-        const int rot = grp % nchunk;
-        auto at = [&](int c) { return c + rot < nchunk ? c + rot : c + rot - nchunk; };
+        // Order of K.  In step, all the blocks' rows ask for the same columns at the same time, and with rows of a multiple of
+        // 4 KB those sit behind few of the memory channels.  There K is cut into four parts, which a group takes in the order
+        // p ^ rot, rot its own; the parts' sums are added as ((0 + 1) + (2 + 3)), each pair in either order, so a row's logit
+        // has the same bits whatever its group, the grid and the launch form: equal rows get equal logits, and none depends on
+        // how the step was launched.  (rot by both the group and its octet: groups are dealt round-robin to the eight XCDs,
+        // and each of those then has all four parts in flight.)  V = 128256, 8 sequences, us for one order / with parts:
+        // d = 2048 120 / 102, 4096 243 / 188, 6144 325 / 283, 8192 371 / 345; 64 sequences at d = 8192 412 / 388.  Other lengths
+        // spread by themselves: d = 4608 (V = 256000) 410 / 420, 5120 (V = 151552) 299 / 304, 3072 and 7168 no difference.
+        const int levels = f.d % 2048 == 0 ? FULL_K_LEVELS : 0, rot = (grp + (grp >> 3)) & ((1 << levels) - 1);
+        auto part_at = [&](int q) { return (q * nchunk) >> levels; };        // first chunk of part q (d >= 2048: no part is empty)
+        int part = 0, cur_c = part_at(rot), next_c = 0;                      // parts done, the chunk in use, the one after it
+        floatx4_t held[FULL_K_LEVELS][TW][NT];
+        // behind part i: acc joins the sum held on every level that is full, and is held on the first that is not
+        auto fold = [&](int i) {
+            bool carry = true;
+#pragma unroll
+            for (int l = 0; l < FULL_K_LEVELS; ++l) {
+                if (l >= levels || !carry) continue;
+                carry = (i >> l) & 1;
+#pragma unroll
+                for (int tw = 0; tw < TW; ++tw)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        if (carry) {
+                            acc[tw][t] = acc[tw][t] + held[l][tw][t];
+                        } else {
+                            held[l][tw][t] = acc[tw][t];
+                            acc[tw][t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+                        }
+                    }
+            }
+        };
         auto stage_q = [&](int c, int s) {
             const int kbjj = wave / NT + (NW / NT) * s;
             return (c * MFMA_PIPE + (kbjj >> 2)) * 16 + (kbjj & 3) * 4 + g;
         };
         auto stage_load = [&](int c) {
 #pragma unroll
-            for (int s = 0; s < SPT; ++s) sreg[s] = st_h[min(stage_q(at(c), s), nq - 1)];
+            for (int s = 0; s < SPT; ++s) sreg[s] = st_h[min(stage_q(c, s), nq - 1)];
         };
         auto stage_store = [&](uint4* buf, int c) {
 #pragma unroll
-            for (int s = 0; s < SPT; ++s) buf[tid + MFMA_THREADS * s] = keep_if(st_on && stage_q(at(c), s) < nq, sreg[s]);
+            for (int s = 0; s < SPT; ++s) buf[tid + MFMA_THREADS * s] = keep_if(st_on && stage_q(c, s) < nq, sreg[s]);
         };
-        stage_load(0);
+        stage_load(cur_c);
 #pragma unroll
-        for (int kb = 0; kb < MFMA_PIPE; ++kb) load_A(kb, at(0) * MFMA_PIPE + kb);
-        stage_store(lds, 0);
+        for (int kb = 0; kb < MFMA_PIPE; ++kb) load_A(kb, cur_c * MFMA_PIPE + kb);
+        stage_store(lds, cur_c);
         lds_barrier();
         // The last chunk is a copy of the loop body without the requests for a next one: with the requests under a
         // condition the compiler could not count, at compile time, how many younger loads a wait may leave open.
         auto chunk = [&](auto more_t, int c) {
             constexpr bool more = decltype(more_t)::value;
             const uint4* cur = lds + (c & 1) * CH;
-            if (more) stage_load(c + 1);
+            if (more) stage_load(next_c);
             __builtin_amdgcn_sched_barrier(0);      // requests are issued where they are written: the scheduler would sink them
 #pragma unroll
             for (int kb = 0; kb < MFMA_PIPE; ++kb) {
@@ -2734,14 +2762,22 @@ __device__ __forceinline__ void full_mfma_device(const FullArgs& f, int n, int s
                                                                                  __builtin_bit_cast(bf16x8_t, A[kb][tw][jj]), acc[tw][t], 0, 0, 0);
                     }
                 __builtin_amdgcn_sched_barrier(0);
-                if (more) load_A(kb, at(c + 1) * MFMA_PIPE + kb);
+                if (more) load_A(kb, next_c * MFMA_PIPE + kb);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (more) stage_store(lds + ((c + 1) & 1) * CH, c + 1);
+            if (more) stage_store(lds + ((c + 1) & 1) * CH, next_c);
             lds_barrier();          // the chunk just consumed may be overwritten, the next one is complete
         };
-        for (int c = 0; c + 1 < nchunk; ++c) chunk(std::true_type{}, c);
+        for (int c = 0; c + 1 < nchunk; ++c) {
+            next_c = cur_c + 1;
+            const bool ends = next_c == part_at((part ^ rot) + 1);
+            if (ends) next_c = part_at((part + 1) ^ rot);
+            chunk(std::true_type{}, c);
+            if (ends) fold(part++);
+            cur_c = next_c;
+        }
         chunk(std::false_type{}, nchunk - 1);
+        fold(part);
 #pragma unroll
         for (int tw = 0; tw < TW; ++tw) {
             const int row = (tile0 + tw) * 16 + li;
