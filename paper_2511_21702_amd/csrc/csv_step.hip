@@ -783,14 +783,15 @@ __device__ __forceinline__ void emit_clusters(const StepArgs& a, int b, int roun
     __syncthreads();
 }
 
-// The same for at most SEQ_THREADS opened clusters of an index of at most EMIT_LIST_C, cnt of them (the block has SEQ_THREADS
+// The same for at most SEQ_THREADS opened clusters, cnt of them (the block has SEQ_THREADS
 // threads): the opened ids go into a list in id order, a thread takes one of them for the prefix sums, and the
 // tiles are then written one per thread, neighbouring threads side by side.  emit_clusters gives each thread a run of neighbouring
-// clusters, whose LDS reads fall on few banks, and mostly one thread writes all the tiles of a cluster: 3.7-5.6 us
-// at C = 4096 with 8 to 52 clusters of 62 rows, 4.0 this way; 4.2-5.0 and 3.2 at C = 2048 with clusters of very unequal sizes.  opens: a test of a cluster's key (false for 0).  Uses s.hist, s.rank, s.wval and s.wid (the
+// clusters, whose LDS reads fall on few banks, and mostly one thread writes all the tiles of a cluster: 4.2-5.0 us
+// against 3.2 at C = 2048 with clusters of very unequal sizes; at C = 4096 with 8 to 52 clusters of 62 rows 3.7-5.6 against 4.0.
+// opens: a test of a cluster's key (false for 0).  Uses s.hist, s.rank, s.wval and s.wid (the
 // caller's top-k list is dead by then); the caller passes a barrier before it uses them again.
-#define EMIT_LIST_C 16384      // s.hist counts 256 groups of 64 clusters; a thread keeps its up to 32 answers in one word
-static_assert(EMIT_LIST_C <= 256 * 64 && EMIT_LIST_C <= 32 * SEQ_THREADS, "emit_list: groups and answers");
+// s.hist counts 256 groups of 64 clusters; a thread keeps its up to 32 answers in one word
+static_assert(CSV_MAX_CLUSTERS <= 256 * 64 && CSV_MAX_CLUSTERS <= 32 * SEQ_THREADS, "emit_list: groups and answers");
 template <class OpensFn>
 __device__ __forceinline__ void emit_list(const StepArgs& a, int b, int round, int pos_base, int sel_base, int cnt, OpensFn opens,
                                           const ClusterLds& L, SeqShared& s) {
@@ -1769,7 +1770,10 @@ __device__ __forceinline__ void write_distribution(const StepArgs& a, int b, int
 // THRESH: compile the threshold selection for more than RANK_DIRECT values.  The fused step kernel leaves it out (its
 // rare larger selections take the general path): with that code in the kernel a single-sequence step took 0.3 us
 // longer, although the step never runs it.
-template <bool THRESH>
+// PLANS: compile the quicker forms of a plan (softmax_prefix_fast, plan_sweep, emit_list).  They pay where plans are made
+// (us a step without / with them: 8 sequences, C = 1500 121 / 113; 34, C = 2445 545 / 525; 25, C = 1108 64 / 61) and cost, as code
+// that is never run, where none is (11 sequences certified at once, C = 1550: 36.3 / 37.7; 3, C = 825: 20.2 / 21.0).
+template <bool THRESH, bool PLANS>
 __device__ __forceinline__ bool cert_body(const StepArgs& a, int b, int chunk, int round, const SeqState& st, SeqShared& s,
                                           bool staged = false, int* settled_count = nullptr) {
     extern __shared__ __align__(16) u64 arena[];
@@ -1931,7 +1935,7 @@ __device__ __forceinline__ bool cert_body(const StepArgs& a, int b, int chunk, i
                 hopeless = n + block_sum_i(r2, s.redi) > a.K_max;
             }
             if (!hopeless) {
-                if constexpr (THRESH) kappa_s = softmax_prefix_fast(a, L, kappa0, Z, s);
+                if constexpr (PLANS) kappa_s = softmax_prefix_fast(a, L, kappa0, Z, s);
                 else kappa_s = softmax_prefix_key(a, L, kappa0, Z, s, [](u64) { return true; }, 0ull);
             }
             intact = true;
@@ -1947,7 +1951,7 @@ __device__ __forceinline__ bool cert_body(const StepArgs& a, int b, int chunk, i
         }
         int cnt = 0, rows = 0;
         PlanSums ps;
-        if constexpr (THRESH) {
+        if constexpr (PLANS) {
             ps = plan_sweep(a, L, kappa0, kappa1, s);
             cnt = ps.cnt;
             rows = ps.rows;
@@ -2000,9 +2004,9 @@ __device__ __forceinline__ bool cert_body(const StepArgs& a, int b, int chunk, i
             auto opens = [&](u64 kx) { return kx >= kappa1 && kx < kappa0 && kx != 0; };
             auto isnew = [&](int c) { return opens(L.keys[c]); };
             float nxtU, T1;
-            if (THRESH && whole) tail_mass(a, L, kappa1, ps.best, ps.vmax, s, nxtU, T1);
+            if (PLANS && whole) tail_mass(a, L, kappa1, ps.best, ps.vmax, s, nxtU, T1);
             else tail_stats(a, L, kappa1, s, nxtU, T1);
-            if (THRESH && cnt <= SEQ_THREADS && C <= EMIT_LIST_C) emit_list(a, b, round + 1, n, st.n_open, cnt, opens, L, s);
+            if (PLANS && cnt <= SEQ_THREADS) emit_list(a, b, round + 1, n, st.n_open, cnt, opens, L, s);
             else emit_clusters(a, b, round + 1, n, st.n_open, isnew, L, s);
             if (tid == 0) {
                 SeqState o = st;
@@ -2029,7 +2033,7 @@ __device__ __forceinline__ bool cert_body(const StepArgs& a, int b, int chunk, i
 template <bool THRESH>
 __device__ __forceinline__ void cert_device(const StepArgs& a, int b, int chunk, int round, SeqShared& s) {
     const SeqState st = a.st[b];
-    cert_body<THRESH>(a, b, chunk, round, st, s);
+    cert_body<THRESH, THRESH>(a, b, chunk, round, st, s);
 }
 
 // ================================================================================================ round 0
@@ -2143,7 +2147,7 @@ __device__ __forceinline__ void wave_seed_tail(const StepArgs& a, const WaveSeed
 // sequence: 1 when the sequence is finished (certified, or flagged invalid), 2 when it left work for later phases
 // (a planned round, a hand-over, a fallback) or gave up.
 // settled_count: where a sequence that finishes here is counted as soon as that is decided (the return value is then 3).
-template <bool SPLIT>
+template <bool THRESH, bool PLANS>
 __device__ __forceinline__ int round0_device(const StepArgs& a, int b, int j, int NB, SeqShared& s, int* settled_count = nullptr) {
     extern __shared__ __align__(16) u64 arena[];
     const int tid = threadIdx.x, nt = SEQ_THREADS, lane = tid & 63, wave = tid >> 6, C = a.C;
@@ -2395,7 +2399,7 @@ __device__ __forceinline__ int round0_device(const StepArgs& a, int b, int j, in
         }
         return 2;
     }
-    return cert_body<SPLIT>(a, b, 0, 0, st, s, true, settled_count) ? (settled_count ? 3 : 1) : 2;     // every path of it that leaves work behind writes the state it needs
+    return cert_body<THRESH, PLANS>(a, b, 0, 0, st, s, true, settled_count) ? (settled_count ? 3 : 1) : 2;     // every path of it that leaves work behind writes the state it needs
 }
 
 // ================================================================================================ Algorithm 1's own order
@@ -3128,10 +3132,11 @@ __global__ __launch_bounds__(TAIL_THREADS) void tail_kernel(StepArgs a, FullArgs
 }
 
 // ------------------------------------------------------------------------------------------------ round 0 as a launch
-// Plain form, grid NB x B: round 0 only; what follows is launched separately.
+// Plain form, grid NB x B: round 0 only; what follows is launched separately.  THRESH, PLANS: see cert_body.
+template <bool THRESH, bool PLANS>
 __global__ __launch_bounds__(SEQ_THREADS) void round0_kernel(StepArgs a, int NB) {
     __shared__ SeqShared s;
-    round0_device<true>(a, blockIdx.x / NB, blockIdx.x % NB, NB, s);
+    round0_device<THRESH, PLANS>(a, blockIdx.x / NB, blockIdx.x % NB, NB, s);
 }
 
 // Fused form, used while recent steps rarely needed anything after round 0: the first NB x B blocks run round 0,
@@ -3146,7 +3151,7 @@ __global__ __launch_bounds__(SEQ_THREADS) void step_kernel(StepArgs a, FullArgs 
     __shared__ int s_flag;
     const int n0 = NB * a.B;
     if ((int)blockIdx.x < n0) {
-        const int settled = round0_device<false>(a, blockIdx.x / NB, blockIdx.x % NB, NB, s, &a.counters[CNT_R0_DONE]);
+        const int settled = round0_device<false, false>(a, blockIdx.x / NB, blockIdx.x % NB, NB, s, &a.counters[CNT_R0_DONE]);
         if (!settled || settled == 3) return;          // 3: finished and already counted
         __syncthreads();                      // all of the block's writes are issued
         if (threadIdx.x == 0) {
@@ -3275,7 +3280,7 @@ static int check_pair(const csv_workspace* ws, const csv_index* idx, const void*
 
 // The dynamic-LDS limit of a kernel is one attribute per process and device, shared by every workspace: it is only
 // ever raised, so a workspace created later with smaller needs cannot take away what an earlier one's launches rely on.
-enum { K_ROUND0, K_STEP, K_TAIL, K_RCERT, K_FBPROD, K_FBPRODM, K_FULLMFMA, K_ALG1, K_BOUND0, K_NKERN = K_BOUND0 + 8 };
+enum { K_ROUND0, K_ROUND0_THRESH, K_ROUND0_PLANS, K_STEP, K_TAIL, K_RCERT, K_FBPROD, K_FBPRODM, K_FULLMFMA, K_ALG1, K_BOUND0, K_NKERN = K_BOUND0 + 8 };
 static size_t g_lds_limit[CSV_STATIC_MAX_DEVICES][K_NKERN];
 static pthread_mutex_t g_attr_lock = PTHREAD_MUTEX_INITIALIZER;
 #define CSV_STATIC_LDS_MAX 16384     // at least the static shared memory of any kernel here
@@ -3487,7 +3492,9 @@ extern "C" int csv_workspace_create(const csv_index* idx, int B_max, int K_cap_r
     }
     // the per-sequence kernels may need more dynamic LDS than the default limit when C is large
     if (e == hipSuccess) e = raise_lds(ws->device, K_FULLMFMA, (const void*)full_mfma_kernel, MFMA_LDS);
-    if (e == hipSuccess) e = raise_lds(ws->device, K_ROUND0, (const void*)round0_kernel, round0_lds(ws));
+    if (e == hipSuccess) e = raise_lds(ws->device, K_ROUND0, (const void*)round0_kernel<false, false>, round0_lds(ws));
+    if (e == hipSuccess) e = raise_lds(ws->device, K_ROUND0_THRESH, (const void*)round0_kernel<true, false>, round0_lds(ws));
+    if (e == hipSuccess) e = raise_lds(ws->device, K_ROUND0_PLANS, (const void*)round0_kernel<true, true>, round0_lds(ws));
     if (e == hipSuccess) {
         size_t l = cert_lds(ws);
         const size_t cand[] = {(size_t)FULL_G * idx->d * 2 /* also covers the two h slots of the tile loop */, (size_t)FB_CHUNK * 4, (size_t)STAGE_CAP * 8,
@@ -3513,8 +3520,15 @@ extern "C" int csv_workspace_create(const csv_index* idx, int B_max, int K_cap_r
         if (e == hipSuccess) e = raise_lds(ws->device, K_RCERT, (const void*)round_cert_kernel, cert_lds(ws));
         if (e == hipSuccess) e = raise_lds(ws->device, K_FBPROD, (const void*)fb_product_kernel, (size_t)FULL_G * idx->d * 2);
         if (e == hipSuccess) e = raise_lds(ws->device, K_FBPRODM, (const void*)fb_product_mfma_kernel, MFMA_LDS);
-        int r0_per_cu = 0;
-        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&r0_per_cu, round0_kernel, SEQ_THREADS, round0_lds(ws));
+        int r0_per_cu = 0x7fffffff;          // of every form of the kernel: the blocks of a sequence wait for each other
+        auto fits = [&](auto kernel) {
+            int n = 0;
+            if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, SEQ_THREADS, round0_lds(ws));
+            r0_per_cu = n < r0_per_cu ? n : r0_per_cu;
+        };
+        fits(round0_kernel<false, false>);
+        fits(round0_kernel<true, false>);
+        fits(round0_kernel<true, true>);
         if (e == hipSuccess && r0_per_cu < 1) {
             csv_set_error("round-0 kernel does not fit a compute unit (dynamic LDS %zu bytes)", round0_lds(ws));
             csv_workspace_free(ws);
@@ -3727,7 +3741,11 @@ extern "C" int csv_decode_step(csv_workspace* ws, const csv_index* idx, const ui
         step_kernel<<<ws->tail_grid, SEQ_THREADS, ws->fused_lds, st>>>(a, f, nb);
         CSV_LAUNCH_CHECK("step_kernel");
     } else {
-        round0_kernel<<<nb * B, SEQ_THREADS, round0_lds(ws), st>>>(a, nb);
+        // Plans are made where recent steps needed later rounds; lists of more than RANK_DIRECT rows only where a seed prefix can
+        // be that long (5 sequences certified on 478 rows each: 53 us without the threshold selection, 30 with it).
+        if (split) round0_kernel<true, true><<<nb * B, SEQ_THREADS, round0_lds(ws), st>>>(a, nb);
+        else if (prefix_max > RANK_DIRECT) round0_kernel<true, false><<<nb * B, SEQ_THREADS, round0_lds(ws), st>>>(a, nb);
+        else round0_kernel<false, false><<<nb * B, SEQ_THREADS, round0_lds(ws), st>>>(a, nb);
         CSV_LAUNCH_CHECK("round0_kernel");
     }
     CSV_MARK(2);
