@@ -2559,8 +2559,7 @@ struct FullArgs {
     const int32_t* perm;
     const uint16_t* h;
     const int32_t* list;    // sequences to score
-    const int32_t* n_ptr;   // device count of entries in list, or NULL
-    int n_fixed;            // count when n_ptr is NULL
+    int n_fixed;            // their number (the fallback products pass their own, counted on the device)
     float* out;             // [slot*out_stride + row*row_stride]
     long long out_stride;
     int row_stride;         // 1, or (MFMA product) the number of sequences with out_stride = 1: a row's logits side by side
@@ -2636,9 +2635,7 @@ __device__ __forceinline__ void full_gemv_device(const FullArgs& f, int n, uint4
 
 __global__ __launch_bounds__(256) void full_gemv_kernel(FullArgs f) {
     extern __shared__ uint4 hs4[];
-    const int n = f.n_ptr ? *f.n_ptr : f.n_fixed;
-    if (n <= 0) return;
-    full_gemv_device(f, n, hs4, blockIdx.x, gridDim.x);
+    full_gemv_device(f, f.n_fixed, hs4, blockIdx.x, gridDim.x);
 }
 
 // MFMA path of the full-vocabulary product, used when more than FULL_G sequences share the pass over W' (then it
@@ -2830,9 +2827,7 @@ __device__ __forceinline__ void full_mfma_all(const FullArgs& f, int n, uint4* l
 
 __global__ __launch_bounds__(MFMA_THREADS) void full_mfma_kernel(FullArgs f) {
     extern __shared__ uint4 mfma_lds[];
-    const int n = f.n_ptr ? *f.n_ptr : f.n_fixed;
-    if (n <= 0) return;
-    full_mfma_all(f, n, mfma_lds, blockIdx.x, gridDim.x);
+    full_mfma_all(f, f.n_fixed, mfma_lds, blockIdx.x, gridDim.x);
 }
 
 // The first stage for k <= RANK_DIRECT < n with the chunk's logits in registers (blockDim.x = SEQ_THREADS, sixteen values
@@ -3415,12 +3410,12 @@ __global__ __launch_bounds__(256) void unpermute_kernel(const float* __restrict_
 }
 
 // tmp: [n_fixed x V] scratch for the MFMA path when the result is wanted in token-id order (may be NULL otherwise)
-static int launch_full(const csv_index* idx, const uint16_t* d_h, const int32_t* list, const int32_t* n_ptr, int n_fixed,
+static int launch_full(const csv_index* idx, const uint16_t* d_h, const int32_t* list, int n_fixed,
                        float* out, long long stride, int scatter, float* tmp, hipStream_t st) {
     FullArgs f;
     f.V = idx->V; f.d = idx->d; f.Wp = idx->Wp; f.bp = idx->bp; f.perm = idx->perm; f.h = d_h;
-    f.list = list; f.n_ptr = n_ptr; f.n_fixed = n_fixed; f.out = out; f.out_stride = stride; f.row_stride = 1; f.scatter = scatter;
-    if (!n_ptr && n_fixed > FULL_G) {
+    f.list = list; f.n_fixed = n_fixed; f.out = out; f.out_stride = stride; f.row_stride = 1; f.scatter = scatter;
+    if (n_fixed > FULL_G) {
         int dev = 0, cus = 0;
         CSV_HIP(hipGetDevice(&dev));
         CSV_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -3634,7 +3629,7 @@ extern "C" int csv_full_logits(csv_workspace* ws, const csv_index* idx, const ui
     int rc = check_pair(ws, idx, d_h, B);
     if (rc) return rc;
     if (!d_logits) { csv_set_error("null d_logits"); return CSV_EINVAL; }
-    return launch_full(idx, d_h, ws->all_list, nullptr, B, d_logits, idx->V, 1, ws->fb_logits, (hipStream_t)stream);
+    return launch_full(idx, d_h, ws->all_list, B, d_logits, idx->V, 1, ws->fb_logits, (hipStream_t)stream);
 }
 
 extern "C" int csv_decode_step(csv_workspace* ws, const csv_index* idx, const uint16_t* d_h, int B,
@@ -3678,7 +3673,7 @@ extern "C" int csv_decode_step(csv_workspace* ws, const csv_index* idx, const ui
     CSV_MARK(1);
     FullArgs f;
     f.V = idx->V; f.d = idx->d; f.Wp = idx->Wp; f.bp = idx->bp; f.perm = idx->perm; f.h = d_h;
-    f.list = ws->fb_list; f.n_ptr = nullptr; f.n_fixed = 0; f.out = ws->fb_logits; f.out_stride = idx->V; f.row_stride = 1; f.scatter = 0;
+    f.list = ws->fb_list; f.n_fixed = 0; f.out = ws->fb_logits; f.out_stride = idx->V; f.row_stride = 1; f.scatter = 0;
     if (p->schedule == CSV_SCHEDULE_ALG1) {
         // Algorithm 1's own order: one block per sequence opens one cluster per iteration; then the fallback launches
         const size_t general = (size_t)ws->Npad * 8 + (size_t)ws->C * 8 + 8;
