@@ -2566,11 +2566,9 @@ struct FullArgs {
     int scatter;            // 1: write at the original token id instead of the permuted row
 };
 
-// Vector path: NG <= FULL_G sequences (g0 ...) in one pass over W', their h in LDS, two rows per wave at a time and
-// FULL_PF pieces of each requested together.
-#define FULL_PF 4
-#define FULL_BLOCKS_MAX 8192
-template <int NG>
+// Vector path: NG <= FULL_G sequences (g0 ...) in one pass over W', their h in LDS, two rows per wave at a time and PF pieces of
+// each requested together, of what is left two, then one.
+template <int NG, int PF>
 __device__ __forceinline__ void full_gemv_pass(const FullArgs& f, int g0, uint4* hs4, int block, int nblocks) {
     const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6;
     const int nch = f.d >> 3;
@@ -2601,16 +2599,20 @@ __device__ __forceinline__ void full_gemv_pass(const FullArgs& f, int g0, uint4*
             }
         };
         int i = lane;
-        for (; i + 64 * (FULL_PF - 1) < nch; i += 64 * FULL_PF) {
-            uint4 a[FULL_PF], c[FULL_PF];
+        auto trip = [&](auto pieces_t) {
+            constexpr int N = decltype(pieces_t)::value;
+            uint4 a[N], c[N];
 #pragma unroll
-            for (int q = 0; q < FULL_PF; ++q) a[q] = w0[i + 64 * q];
+            for (int q = 0; q < N; ++q) a[q] = w0[i + 64 * q];
 #pragma unroll
-            for (int q = 0; q < FULL_PF; ++q) c[q] = w1[i + 64 * q];
+            for (int q = 0; q < N; ++q) c[q] = w1[i + 64 * q];
 #pragma unroll
-            for (int q = 0; q < FULL_PF; ++q) add(a[q], c[q], i + 64 * q);
-        }
-        for (; i < nch; i += 64) add(w0[i], w1[i], i);
+            for (int q = 0; q < N; ++q) add(a[q], c[q], i + 64 * q);
+            i += 64 * N;
+        };
+        while (i + 64 * (PF - 1) < nch) trip(std::integral_constant<int, PF>{});
+        if (PF > 2 && i + 64 < nch) trip(std::integral_constant<int, 2>{});
+        while (i < nch) trip(std::integral_constant<int, 1>{});
 #pragma unroll
         for (int s = 0; s < NG; ++s) {
             const float v0 = wave_sum(acc0[s]), v1 = wave_sum(acc1[s]);
@@ -2622,20 +2624,26 @@ __device__ __forceinline__ void full_gemv_pass(const FullArgs& f, int g0, uint4*
         }
     }
 }
+template <int PF = 4>
 __device__ __forceinline__ void full_gemv_device(const FullArgs& f, int n, uint4* hs4, int block, int nblocks) {
     for (int g0 = 0; g0 < n; g0 += FULL_G) {
         switch (min(FULL_G, n - g0)) {
-            case 1: full_gemv_pass<1>(f, g0, hs4, block, nblocks); break;
-            case 2: full_gemv_pass<2>(f, g0, hs4, block, nblocks); break;
-            case 3: full_gemv_pass<3>(f, g0, hs4, block, nblocks); break;
-            default: full_gemv_pass<4>(f, g0, hs4, block, nblocks); break;
+            case 1: full_gemv_pass<1, PF>(f, g0, hs4, block, nblocks); break;
+            case 2: full_gemv_pass<2, PF>(f, g0, hs4, block, nblocks); break;
+            case 3: full_gemv_pass<3, PF>(f, g0, hs4, block, nblocks); break;
+            default: full_gemv_pass<4, PF>(f, g0, hs4, block, nblocks); break;
         }
     }
 }
 
-__global__ __launch_bounds__(256) void full_gemv_kernel(FullArgs f) {
+// Dense logits of up to FULL_G sequences.  PF: 4 where a row has that many pieces per lane (d >= 2048), 2 for shorter rows, which never
+// fill a trip of four: the registers then allow eight waves per SIMD, which hide what fewer requests per wave leave open
+// (us with four pieces and four waves / two and five / two and eight: V = 24000, d = 768, one sequence 9.5 / 8.9 / 7.4, four 16.2 /
+// 15.0 / 12.0; V = 128256, d = 1536, four 103 / 102 / 81.  V = 32000, d = 4096, one 39.4 / 43.7 with two pieces).
+template <int PF>
+__global__ __launch_bounds__(256, PF == 2 ? 8 : 4) void full_gemv_kernel(FullArgs f) {
     extern __shared__ uint4 hs4[];
-    full_gemv_device(f, f.n_fixed, hs4, blockIdx.x, gridDim.x);
+    full_gemv_device<PF>(f, f.n_fixed, hs4, blockIdx.x, gridDim.x);
 }
 
 // MFMA path of the full-vocabulary product, used when more than FULL_G sequences share the pass over W' (then it
@@ -3434,11 +3442,19 @@ static int launch_full(const csv_index* idx, const uint16_t* d_h, const int32_t*
         }
         return CSV_OK;
     }
-    // Many short blocks rather than few that stay: the hardware hands them out in order, so the rows in flight lie close
-    // together (d = 4096, V = 128256: 186 us with 2048 blocks, 179 with 8192, 239 with 16032 of one tile each, where staging h shows)
-    const int ntiles = (idx->V + 7) / 8;
-    const int grid = ntiles < FULL_BLOCKS_MAX ? ntiles : FULL_BLOCKS_MAX;
-    full_gemv_kernel<<<grid, 256, (size_t)(n_fixed < FULL_G ? n_fixed : FULL_G) * idx->d * 2, st>>>(f);
+    // Blocks.  Many short ones rather than few that stay keep the rows in flight close together (the hardware hands them out in
+    // order), but each stages h: a share of n / 8 of a tile's bytes per tile it computes.
+    // Long rows: 8192 for one and two sequences (V = 128256, d = 4096: 177 and 182 us, with 2048 blocks 188 and 191), for three
+    // where that leaves a block more than one tile (190 / 194); 2048 for four (V = 64000, d = 4096 103 us, with 8192 115).
+    // Short rows: four tiles a block, 2048 to 8192 blocks (d = 1024, four sequences, us with 2048 / 4096 / 8192, at five waves per SIMD:
+    // V = 32000 18.5 / 19.5 / 19.5, V = 128256 60 / 58 / 59, V = 256000 154 / 146 / 139).
+    const int ntiles = (idx->V + 7) / 8, n = n_fixed;
+    const bool rows_long = idx->d >= 2048;
+    int grid = rows_long ? (n <= 2 || (n == 3 && ntiles >= 12288) ? 8192 : 2048) : (ntiles / 4 < 2048 ? 2048 : (ntiles / 4 < 8192 ? ntiles / 4 : 8192));
+    grid = grid < ntiles ? grid : ntiles;
+    const size_t lds = (size_t)n * idx->d * 2;
+    if (rows_long) full_gemv_kernel<4><<<grid, 256, lds, st>>>(f);
+    else full_gemv_kernel<2><<<grid, 256, lds, st>>>(f);
     CSV_LAUNCH_CHECK("full_gemv_kernel");
     return CSV_OK;
 }
