@@ -89,41 +89,52 @@ __global__ __launch_bounds__(512) void layout_scan_kernel(int32_t* __restrict__ 
 }
 
 // off, and the list of row chunks of the centroid and distance passes: chunks[i] = {cluster, first permuted row}, coff[c] =
-// first chunk of cluster c, coff[C] = their number.  One block.
+// first chunk of cluster c, coff[C] = their number; poff[c] = the partial sums of cluster c's chunks, which only clusters of several
+// have (PART_SLOTS of them at most).  One block.
 #define CHUNK_ROWS 128
+// a cluster of n > CHUNK_ROWS rows has at most n / CHUNK_ROWS + 1 chunks, and there are at most V / (CHUNK_ROWS + 1) such clusters
+#define PART_SLOTS(V) ((V) / CHUNK_ROWS + (V) / (CHUNK_ROWS + 1) + 1)
 __global__ __launch_bounds__(1024) void layout_offsets_kernel(const int32_t* __restrict__ n, int C, int32_t* __restrict__ off,
-                                                              int32_t* __restrict__ coff, int2* __restrict__ chunks) {
-    __shared__ int32_t ws[2][16];
+                                                              int32_t* __restrict__ coff, int32_t* __restrict__ poff, int2* __restrict__ chunks) {
+    __shared__ int32_t ws[3][16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int per = (C + 1023) / 1024, c0 = min(C, tid * per), c1 = min(C, c0 + per);
-    int rows = 0, nch = 0;
+    int rows = 0, nch = 0, nparts = 0;
     for (int c = c0; c < c1; ++c) {
+        const int m = (n[c] + CHUNK_ROWS - 1) / CHUNK_ROWS;
         rows += n[c];
-        nch += (n[c] + CHUNK_ROWS - 1) / CHUNK_ROWS;
+        nch += m;
+        nparts += m > 1 ? m : 0;
     }
-    int x = rows, y = nch;
+    int x = rows, y = nch, z = nparts;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        const int xx = __shfl_up(x, o, CSV_WAVE), yy = __shfl_up(y, o, CSV_WAVE);
+        const int xx = __shfl_up(x, o, CSV_WAVE), yy = __shfl_up(y, o, CSV_WAVE), zz = __shfl_up(z, o, CSV_WAVE);
         if (lane >= o) {
             x += xx;
             y += yy;
+            z += zz;
         }
     }
     if (lane == 63) {
         ws[0][wave] = x;
         ws[1][wave] = y;
+        ws[2][wave] = z;
     }
     __syncthreads();
     x -= rows;
     y -= nch;
+    z -= nparts;
     for (int q = 0; q < wave; ++q) {
         x += ws[0][q];
         y += ws[1][q];
+        z += ws[2][q];
     }
     for (int c = c0; c < c1; ++c) {
         off[c] = x;
         coff[c] = y;
+        poff[c] = z;
+        if (n[c] > CHUNK_ROWS) z += (n[c] + CHUNK_ROWS - 1) / CHUNK_ROWS;
         for (int r = 0; r < n[c]; r += CHUNK_ROWS) chunks[y++] = make_int2(c, x + r);
         x += n[c];
     }
@@ -171,7 +182,7 @@ __global__ __launch_bounds__(64) void layout_scatter_kernel(const int32_t* __res
 // UNIT (spherical clustering): rows are divided by their norm nrm[token], the sums themselves go to out_sum.
 template <bool UNIT>
 __global__ __launch_bounds__(256) void centroid_chunk_kernel(const uint16_t* __restrict__ W, const int32_t* __restrict__ perm, const int32_t* __restrict__ off,
-                                                             const int32_t* __restrict__ coff, const int2* __restrict__ chunks, int d, int C,
+                                                             const int32_t* __restrict__ coff, const int32_t* __restrict__ poff, const int2* __restrict__ chunks, int d, int C,
                                                              const double* __restrict__ nrm, float* __restrict__ mu, double* __restrict__ out_sum,
                                                              double* __restrict__ part) {
     __shared__ double red[4][8][64];
@@ -219,7 +230,7 @@ __global__ __launch_bounds__(256) void centroid_chunk_kernel(const uint16_t* __r
     for (int q = 0; q < 2; ++q) {
         const int e = 2 * wave + q, col = piece * 8 + e;
         const double sum = ((red[0][e][lane] + red[1][e][lane]) + red[2][e][lane]) + red[3][e][lane];
-        if (last - first > CHUNK_ROWS) part[(size_t)chunk * d + col] = sum;
+        if (last - first > CHUNK_ROWS) part[(size_t)(poff[c] + chunk - coff[c]) * d + col] = sum;
         else if (UNIT) out_sum[(size_t)c * d + col] = sum;
         else mu[(size_t)c * d + col] = (float)(sum / (double)rows);
     }
@@ -228,7 +239,7 @@ __global__ __launch_bounds__(256) void centroid_chunk_kernel(const uint16_t* __r
 // Clusters of several chunks: the partial sums, in chunk order.  An empty cluster keeps its centroid (Lloyd) or is zeroed
 // (final metadata; direction_finish_kernel does that for directions).
 template <bool UNIT>
-__global__ __launch_bounds__(256) void centroid_finish_kernel(const int32_t* __restrict__ off, const int32_t* __restrict__ coff, int d, int zero_empty,
+__global__ __launch_bounds__(256) void centroid_finish_kernel(const int32_t* __restrict__ off, const int32_t* __restrict__ poff, int d, int zero_empty,
                                                               const double* __restrict__ part, float* __restrict__ mu, double* __restrict__ out_sum) {
     const int c = blockIdx.x, n = off[c + 1] - off[c];
     const int col = blockIdx.y * 256 + threadIdx.x;
@@ -237,7 +248,7 @@ __global__ __launch_bounds__(256) void centroid_finish_kernel(const int32_t* __r
     if (n <= CHUNK_ROWS) return;
     double sum = 0.0;
 #pragma unroll 4
-    for (int q = coff[c]; q < coff[c + 1]; ++q) sum += part[(size_t)q * d + col];
+    for (int q = 0; q < (n + CHUNK_ROWS - 1) / CHUNK_ROWS; ++q) sum += part[(size_t)(poff[c] + q) * d + col];
     if (UNIT) out_sum[(size_t)c * d + col] = sum;
     else mu[(size_t)c * d + col] = (float)(sum / (double)n);
 }
@@ -943,8 +954,11 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
         used += (bytes + 255) / 256 * 256;
         return at;
     };
-    const size_t o_labels = take((size_t)V * 4), o_hist = take((size_t)nw * C * 4), o_coff = take((size_t)(C + 1) * 4), o_chunks = take((size_t)max_chunks * sizeof(int2)),
-                 o_part = take((size_t)max_chunks * d * 8), o_pieces = take(assigns ? (size_t)nkb * ap.CT * 192 * sizeof(uint4) : 0),
+    // partial centroid sums and the assignment's pieces are never live together: they share their bytes
+    const size_t part_slots = PART_SLOTS(V) < max_chunks ? PART_SLOTS(V) : max_chunks;
+    const size_t part_bytes = part_slots * d * 8, piece_bytes = assigns ? (size_t)nkb * ap.CT * 192 * sizeof(uint4) : 0;
+    const size_t o_labels = take((size_t)V * 4), o_hist = take((size_t)nw * C * 4), o_coff = take((size_t)(C + 1) * 4), o_poff = take((size_t)C * 4), o_chunks = take((size_t)max_chunks * sizeof(int2)),
+                 o_both = take(part_bytes > piece_bytes ? part_bytes : piece_bytes),
                  o_cand = take(assigns ? (size_t)V * ap.ncol * 8 : 0), o_cn = take((size_t)C * 4), o_d2max = take((size_t)C * 8),
                  o_d2row = take(bt_m ? (size_t)V * 8 : 0), o_nrm = take(sph ? (size_t)V * 8 : 0), o_sums = take(sph ? (size_t)C * d * 8 : 0),
                  o_ext = take(sph ? (size_t)3 * C * 8 : 0);
@@ -958,10 +972,10 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
     };
     if (sph && (o->centroid_bf16 || bt_m)) { csv_set_error("spherical clustering takes neither bf16 centroids nor a bias table"); return fail(CSV_EINVAL); }
     if (hipMalloc((void**)&arena, used) != hipSuccess) { csv_set_error("out of device memory (index build scratch, %zu bytes)", used); return fail(CSV_ENOMEM); }
-    int32_t *d_labels = (int32_t*)(arena + o_labels), *d_hist = (int32_t*)(arena + o_hist), *d_coff = (int32_t*)(arena + o_coff);
+    int32_t *d_labels = (int32_t*)(arena + o_labels), *d_hist = (int32_t*)(arena + o_hist), *d_coff = (int32_t*)(arena + o_coff), *d_poff = (int32_t*)(arena + o_poff);
     int2* d_chunks = (int2*)(arena + o_chunks);
-    double *d_part = (double*)(arena + o_part), *d_nrm = (double*)(arena + o_nrm), *d_sums = (double*)(arena + o_sums), *d_d2row = bt_m ? (double*)(arena + o_d2row) : nullptr;
-    uint4* d_pieces = (uint4*)(arena + o_pieces);
+    double *d_part = (double*)(arena + o_both), *d_nrm = (double*)(arena + o_nrm), *d_sums = (double*)(arena + o_sums), *d_d2row = bt_m ? (double*)(arena + o_d2row) : nullptr;
+    uint4* d_pieces = (uint4*)(arena + o_both);
     float* d_cn = (float*)(arena + o_cn);
     unsigned long long *d_cand = (unsigned long long*)(arena + o_cand), *d_d2max = (unsigned long long*)(arena + o_d2max), *d_ext = (unsigned long long*)(arena + o_ext);
     if (sph) {
@@ -1002,16 +1016,16 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
         const bool last = it == o->iters;
         label_hist_kernel<<<nw, 64, (size_t)C * 4, st>>>(assigned ? d_cand : nullptr, ap.ncol, d_labels, V, C, d_hist);
         layout_scan_kernel<<<(C + 63) / 64, 512, 0, st>>>(d_hist, nw, C, x->n);
-        layout_offsets_kernel<<<1, 1024, 0, st>>>(x->n, C, x->off, d_coff, d_chunks);
+        layout_offsets_kernel<<<1, 1024, 0, st>>>(x->n, C, x->off, d_coff, d_poff, d_chunks);
         layout_scatter_kernel<<<nw, 64, (size_t)C * 4, st>>>(d_labels, d_hist, x->off, V, C, label_bits, x->perm);
         const dim3 kgrid(max_chunks, (d + 511) / 512), fgrid(C, (d + 255) / 256);
         if (sph) {
-            centroid_chunk_kernel<true><<<kgrid, 256, 0, st>>>(d_W, x->perm, x->off, d_coff, d_chunks, d, C, d_nrm, x->mu, d_sums, d_part);
-            centroid_finish_kernel<true><<<fgrid, 256, 0, st>>>(x->off, d_coff, d, 0, d_part, x->mu, d_sums);
+            centroid_chunk_kernel<true><<<kgrid, 256, 0, st>>>(d_W, x->perm, x->off, d_coff, d_poff, d_chunks, d, C, d_nrm, x->mu, d_sums, d_part);
+            centroid_finish_kernel<true><<<fgrid, 256, 0, st>>>(x->off, d_poff, d, 0, d_part, x->mu, d_sums);
             direction_finish_kernel<<<C, 256, 0, st>>>(d_sums, x->off, d, last ? 1 : 0, x->mu);
         } else {
-            centroid_chunk_kernel<false><<<kgrid, 256, 0, st>>>(d_W, x->perm, x->off, d_coff, d_chunks, d, C, nullptr, x->mu, nullptr, d_part);
-            centroid_finish_kernel<false><<<fgrid, 256, 0, st>>>(x->off, d_coff, d, last ? 1 : 0, d_part, x->mu, nullptr);
+            centroid_chunk_kernel<false><<<kgrid, 256, 0, st>>>(d_W, x->perm, x->off, d_coff, d_poff, d_chunks, d, C, nullptr, x->mu, nullptr, d_part);
+            centroid_finish_kernel<false><<<fgrid, 256, 0, st>>>(x->off, d_poff, d, last ? 1 : 0, d_part, x->mu, nullptr);
         }
         if (hipGetLastError() != hipSuccess) { csv_set_error("launch of the centroid kernels failed"); return fail(CSV_EHIP); }
         if (last) break;

@@ -81,3 +81,22 @@ def test_a_row_that_is_not_finite_leaves_no_finite_radius():
     R = g.export()["R"]
     assert np.isnan(R[1]) and np.isfinite(R[[0, 2]]).all()
     g.free()
+
+
+# The most partial sums for the rows: clusters one row past a chunk, among clusters without partial sums; then one cluster with all the rows.
+@pytest.mark.parametrize("sizes", [[129] * 70, [128, 129] * 40 + [1, 0, 130], [16385], [0, 1] * 30 + [9000]])
+@pytest.mark.parametrize("iters", [0, 1])
+def test_partial_centroid_sums_fit_their_slots(sizes, iters):
+    import paper_2511_21702_amd as csv
+    C, V, d = len(sizes), sum(sizes), 40
+    # CHUNK_ROWS and PART_SLOTS of the library
+    assert sum(-(-n // 128) for n in sizes if n > 128) <= V // 128 + V // 129 + 1
+    labels = np.random.default_rng(V).permutation(np.repeat(np.arange(C, dtype=np.int32), sizes))
+    centers = np.random.default_rng(d).normal(0, 1, (C, d)).astype(np.float32)
+    W = synth.f32_to_bf16_bits(centers[labels] + np.random.default_rng(C).normal(0, 0.01, (V, d)).astype(np.float32))
+    b = np.zeros(V, np.float32)
+    log(f"partial sums V={V} C={C} iters={iters}")
+    g = csv.csv_build_index(csv.bits_to_device(W), torch.from_numpy(b).cuda(), C, init_labels=labels, iters=iters)
+    if min(sizes) or not iters:                  # (an empty cluster has no planted centre to be found again)
+        _same_metadata(g.export(), O.build_index(W, b, labels, C))
+    g.free()
