@@ -954,8 +954,23 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
         used += (bytes + 255) / 256 * 256;
         return at;
     };
-    // partial centroid sums and the assignment's pieces are never live together: they share their bytes
-    const size_t part_slots = PART_SLOTS(V) < max_chunks ? PART_SLOTS(V) : max_chunks;
+    // Partial centroid sums and the assignment's pieces are never live together: they share their bytes.  Given labels that stay say
+    // how many partial sums there are, mostly none (V = 32000, d = 1024, 256 clusters: 4 MB less to allocate and to give back;
+    // build and csv_index_free 0.24 + 0.30 ms, now 0.18 + 0.04; before the build moved to the device 0.23 + 0.03).
+    size_t part_slots = PART_SLOTS(V) < max_chunks ? PART_SLOTS(V) : max_chunks;
+    if (o->h_init_labels) {
+        std::vector<int32_t> rows(C, 0);
+        for (int i = 0; i < V; ++i) {
+            const int l = o->h_init_labels[i];
+            if (l < 0 || l >= C) { csv_set_error("label %d of token %d outside 0..C-1", l, i); csv_index_free(x); return CSV_EINVAL; }
+            ++rows[l];
+        }
+        if (o->iters == 0) {
+            part_slots = 0;
+            for (int c = 0; c < C; ++c)
+                if (rows[c] > CHUNK_ROWS) part_slots += (rows[c] + CHUNK_ROWS - 1) / CHUNK_ROWS;
+        }
+    }
     const size_t part_bytes = part_slots * d * 8, piece_bytes = assigns ? (size_t)nkb * ap.CT * 192 * sizeof(uint4) : 0;
     const size_t o_labels = take((size_t)V * 4), o_hist = take((size_t)nw * C * 4), o_coff = take((size_t)(C + 1) * 4), o_poff = take((size_t)C * 4), o_chunks = take((size_t)max_chunks * sizeof(int2)),
                  o_both = take(part_bytes > piece_bytes ? part_bytes : piece_bytes),
@@ -994,8 +1009,6 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
     bool assigned = false;               // the labels are the assignment's candidates (else: the caller's)
     std::vector<int32_t> seed;
     if (o->h_init_labels) {
-        for (int i = 0; i < V; ++i)
-            if (o->h_init_labels[i] < 0 || o->h_init_labels[i] >= C) { csv_set_error("label %d of token %d outside 0..C-1", o->h_init_labels[i], i); return fail(CSV_EINVAL); }
         if (hipMemcpyAsync(d_labels, o->h_init_labels, (size_t)V * 4, hipMemcpyHostToDevice, st) != hipSuccess) { csv_set_error("copy of the labels failed"); return fail(CSV_EHIP); }
     } else {
         // seeding rule when the caller names no rows: C tokens evenly spread over the vocabulary, token floor(c V / C)
