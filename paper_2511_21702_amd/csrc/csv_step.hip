@@ -2661,14 +2661,27 @@ __global__ __launch_bounds__(256, PF == 2 ? 8 : 4) void full_gemv_kernel(FullArg
 // h is fed as the first operand and W' as the second, so accumulator register r of lane (li, g) is
 // out[sequence 4g + r][row li]: stores are 64-byte runs per sequence instead of 4-byte pieces 4V bytes apart.
 #define MFMA_THREADS 512
-#define FULL_K_LEVELS 2             // four parts of K where it is cut
-#define MFMA_LDS (64 * 1024)        // two buffers of K blocks x 4 fragments x 1 KB x groups of 16 sequences: at most 2x4
-template <int NT, int TW, int MFMA_PIPE>
+// Order of K.  In step, all the blocks' rows ask for the same columns at the same time, and with rows of a multiple of
+// 4 KB those sit behind few of the memory channels.  There K is cut into 2^levels parts, which a group of rows takes in the order
+// p ^ rot, rot its own; the parts' sums are added as a binary tree, ((0 + 1) + (2 + 3)) + ..., each pair in either order, so a row's logit
+// has the same bits whatever its group, the grid and the launch form: equal rows get equal logits, and none depends on
+// how the step was launched.  (rot by both the group and its octet: groups are dealt round-robin to the eight XCDs,
+// and each of those then has all parts in flight.)  V = 128256, us for one order / with parts: 8 sequences, d = 2048 120 / 99,
+// 4096 243 / 188, 6144 325 / 283, 8192 371 / 365; 64 sequences at d = 8192 412 / 390.  Eight parts rather than four at
+// d = 8192: the same there, but not up to 10 % more where W' comes to lie less well (8 sequences 365 in each of five places, with
+// four parts 353-390); at d = 4096 four are 1-3 % faster.  Other lengths spread by themselves: d = 4608 (V = 256000) 410 without /
+// 420 with, 5120 (V = 151552) 299 / 304, 3072 and 7168 no difference.
+__host__ __device__ __forceinline__ int full_k_levels(int d) { return d % 8192 == 0 ? 3 : (d % 2048 == 0 ? 2 : 0); }
+// Dynamic LDS: two buffers of K blocks x 4 fragments x 1 KB x groups of 16 sequences, at most 2 x 4; where K is cut also the
+// sums of the last level, 128 bytes a thread
+__host__ __device__ constexpr int mfma_lds(int levels) { return levels > 0 ? 128 * 1024 : 64 * 1024; }
+// LEVELS: at least the full_k_levels of d
+template <int NT, int TW, int MFMA_PIPE, int LEVELS>
 __device__ __forceinline__ void full_mfma_device(const FullArgs& f, int n, int seq0, uint4* lds, int block, int nblocks) {
     constexpr int NW = MFMA_THREADS / 64;
     constexpr int CH = MFMA_PIPE * 4 * NT * 64;       // 16-byte pieces per LDS buffer
     constexpr int SPT = CH / MFMA_THREADS;            // pieces a thread stages per chunk
-    static_assert(CH % MFMA_THREADS == 0 && NW % NT == 0 && 2 * CH * 16 <= MFMA_LDS, "staging layout");
+    static_assert(CH % MFMA_THREADS == 0 && NW % NT == 0 && 2 * CH * 16 + (LEVELS > 0 ? TW * NT * MFMA_THREADS * 16 : 0) <= mfma_lds(LEVELS), "staging layout");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int li = lane & 15, g = lane >> 4;
     const int ntiles = (f.V + 15) >> 4;
@@ -2702,33 +2715,27 @@ __device__ __forceinline__ void full_mfma_device(const FullArgs& f, int n, int s
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) A[kb][tw][jj] = ap[tw][min(sb * 16 + jj * 4 + g, nq - 1)];
         };
-        // Order of K.  In step, all the blocks' rows ask for the same columns at the same time, and with rows of a multiple of
-        // 4 KB those sit behind few of the memory channels.  There K is cut into four parts, which a group takes in the order
-        // p ^ rot, rot its own; the parts' sums are added as ((0 + 1) + (2 + 3)), each pair in either order, so a row's logit
-        // has the same bits whatever its group, the grid and the launch form: equal rows get equal logits, and none depends on
-        // how the step was launched.  (rot by both the group and its octet: groups are dealt round-robin to the eight XCDs,
-        // and each of those then has all four parts in flight.)  V = 128256, 8 sequences, us for one order / with parts:
-        // d = 2048 120 / 102, 4096 243 / 188, 6144 325 / 283, 8192 371 / 345; 64 sequences at d = 8192 412 / 388.  Other lengths
-        // spread by themselves: d = 4608 (V = 256000) 410 / 420, 5120 (V = 151552) 299 / 304, 3072 and 7168 no difference.
-        const int levels = f.d % 2048 == 0 ? FULL_K_LEVELS : 0, rot = (grp + (grp >> 3)) & ((1 << levels) - 1);
+        const int levels = LEVELS == 0 ? 0 : full_k_levels(f.d), rot = (grp + (grp >> 3)) & ((1 << levels) - 1);
         auto part_at = [&](int q) { return (q * nchunk) >> levels; };        // first chunk of part q (d >= 2048: no part is empty)
         int part = 0, cur_c = part_at(rot), next_c = 0;                      // parts done, the chunk in use, the one after it
-        floatx4_t held[FULL_K_LEVELS][TW][NT];
+        floatx4_t held[LEVELS > 1 ? LEVELS - 1 : 1][TW][NT];                 // the levels but the last, which lies in LDS
+        floatx4_t* park = reinterpret_cast<floatx4_t*>(lds + 2 * CH) + tid;
         // behind part i: acc joins the sum held on every level that is full, and is held on the first that is not
         auto fold = [&](int i) {
             bool carry = true;
 #pragma unroll
-            for (int l = 0; l < FULL_K_LEVELS; ++l) {
+            for (int l = 0; l < LEVELS; ++l) {
                 if (l >= levels || !carry) continue;
                 carry = (i >> l) & 1;
 #pragma unroll
                 for (int tw = 0; tw < TW; ++tw)
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
+                        floatx4_t& h = l < LEVELS - 1 ? held[l < LEVELS - 1 ? l : 0][tw][t] : park[(tw * NT + t) * MFMA_THREADS];
                         if (carry) {
-                            acc[tw][t] = acc[tw][t] + held[l][tw][t];
+                            acc[tw][t] = acc[tw][t] + h;
                         } else {
-                            held[l][tw][t] = acc[tw][t];
+                            h = acc[tw][t];
                             acc[tw][t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
                         }
                     }
@@ -2814,28 +2821,32 @@ __device__ __forceinline__ void full_mfma_device(const FullArgs& f, int n, int s
 // measured 2-8 % slower at d = 8192 for up to 32 sequences (and spill with 64), one no faster, eight far slower.  The groups of 128 TW rows are dealt to the blocks in rounds:
 // two row tiles per wave (a fragment of h read from LDS then serves two MFMAs) unless one tile per wave saves a
 // round's worth of idle blocks.  Four tiles per wave with half the K blocks ahead measured 4-7 % slower at d = 8192.
-template <int TW>
+template <int TW, int LEVELS>
 __device__ __forceinline__ void full_mfma_pass(const FullArgs& f, int n, uint4* lds, int block, int nblocks) {
     for (int s0 = 0; s0 < n; s0 += 64) {
         const int m = n - s0;
-        if (m <= 16) full_mfma_device<1, TW, 2>(f, n, s0, lds, block, nblocks);
-        else if (m <= 32) full_mfma_device<2, TW, 2>(f, n, s0, lds, block, nblocks);
-        else full_mfma_device<4, TW, 2>(f, n, s0, lds, block, nblocks);
+        if (m <= 16) full_mfma_device<1, TW, 2, LEVELS>(f, n, s0, lds, block, nblocks);
+        else if (m <= 32) full_mfma_device<2, TW, 2, LEVELS>(f, n, s0, lds, block, nblocks);
+        else full_mfma_device<4, TW, 2, LEVELS>(f, n, s0, lds, block, nblocks);
     }
 }
+template <int LEVELS>
 __device__ __forceinline__ void full_mfma_all(const FullArgs& f, int n, uint4* lds, int block, int nblocks) {
     const int ntiles = (f.V + 15) >> 4, NW = MFMA_THREADS / 64;
     auto cost = [&](int tw) {           // rounds of groups x time of a group
         const int groups = (ntiles + NW * tw - 1) / (NW * tw);
         return (groups + nblocks - 1) / nblocks * tw;
     };
-    if (cost(2) <= cost(1)) full_mfma_pass<2>(f, n, lds, block, nblocks);
-    else full_mfma_pass<1>(f, n, lds, block, nblocks);
+    if (cost(2) <= cost(1)) full_mfma_pass<2, LEVELS>(f, n, lds, block, nblocks);
+    else full_mfma_pass<1, LEVELS>(f, n, lds, block, nblocks);
 }
 
+// Of this kernel and the fallback product there is a form per full_k_levels: sums held for levels that a length does not
+// use cost registers (d = 4096, 8 sequences in a step 217 us, with three levels compiled in 223).
+template <int LEVELS>
 __global__ __launch_bounds__(MFMA_THREADS) void full_mfma_kernel(FullArgs f) {
-    extern __shared__ uint4 mfma_lds[];
-    full_mfma_all(f, f.n_fixed, mfma_lds, blockIdx.x, gridDim.x);
+    extern __shared__ uint4 stage_lds[];
+    full_mfma_all<LEVELS>(f, f.n_fixed, stage_lds, blockIdx.x, gridDim.x);
 }
 
 // The first stage for k <= RANK_DIRECT < n with the chunk's logits in registers (blockDim.x = SEQ_THREADS, sixteen values
@@ -3069,7 +3080,7 @@ __device__ __forceinline__ bool grid_barrier(int* counters, int which, int nbloc
 }
 
 // block / nblocks: this block's position among the blocks that run the tail together (all resident).
-template <bool THRESH>
+template <bool THRESH, bool MANY>
 __device__ __forceinline__ void tail_device(const StepArgs& a, const FullArgs& f, int fallback_only, int block, int nblocks,
                                             SeqShared& s, GemvShared& gs, int* s_flag) {
     extern __shared__ __align__(16) u64 arena[];
@@ -3111,8 +3122,8 @@ __device__ __forceinline__ void tail_device(const StepArgs& a, const FullArgs& f
     const int n_fb = __hip_atomic_load(&a.counters[CNT_FALLBACK], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
     if (n_fb == 0) return;
     // the same rule as the separate launches, so that a sequence's logits do not depend on how the step was launched
-    if (n_fb > FULL_G)
-        full_mfma_all(f, n_fb, reinterpret_cast<uint4*>(arena), block, nblocks);
+    if (MANY && n_fb > FULL_G)
+        full_mfma_all<3>(f, n_fb, reinterpret_cast<uint4*>(arena), block, nblocks);
     else
         full_gemv_device(f, n_fb, reinterpret_cast<uint4*>(arena), block, nblocks);
     if (!grid_barrier(a.counters, 2 * CSV_MAX_ROUNDS, nblocks, s_flag, a.spin_limit)) return;
@@ -3131,7 +3142,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void tail_kernel(StepArgs a, FullArgs
     __shared__ SeqShared s;
     __shared__ GemvShared gs;
     __shared__ int s_flag;
-    tail_device<true>(a, f, fallback_only, blockIdx.x, gridDim.x, s, gs, &s_flag);
+    tail_device<true, true>(a, f, fallback_only, blockIdx.x, gridDim.x, s, gs, &s_flag);
 }
 
 // ------------------------------------------------------------------------------------------------ round 0 as a launch
@@ -3148,6 +3159,9 @@ __global__ __launch_bounds__(SEQ_THREADS) void round0_kernel(StepArgs a, int NB)
 // tail exactly as tail_kernel does (the round-0 blocks have left by then; the tail's blocks are all resident: the
 // host sizes the grid for one block per compute unit).  Blocks start in index order, so the blocks waited for are
 // already running when a parked block starts; the wait is bounded all the same (the poll limit of the grid barriers).
+// MANY: the product for more than FULL_G fallback sequences is compiled in, for batches that can have them (in the kernel of smaller
+// ones it costs a step that never runs it up to 0.7 us of 14).
+template <bool MANY>
 __global__ __launch_bounds__(SEQ_THREADS) void step_kernel(StepArgs a, FullArgs f, int NB) {
     __shared__ SeqShared s;
     __shared__ GemvShared gs;
@@ -3182,7 +3196,7 @@ __global__ __launch_bounds__(SEQ_THREADS) void step_kernel(StepArgs a, FullArgs 
     }
     __syncthreads();
     if (!s_flag) return;
-    tail_device<false>(a, f, 0, (int)blockIdx.x - n0, (int)gridDim.x - n0, s, gs, &s_flag);   // the lean form: see cert_body
+    tail_device<false, MANY>(a, f, 0, (int)blockIdx.x - n0, (int)gridDim.x - n0, s, gs, &s_flag);   // the lean form: see cert_body
 }
 
 // ------------------------------------------------------------------------------------------------ the tail, one launch per phase
@@ -3213,12 +3227,13 @@ __global__ __launch_bounds__(TAIL_THREADS, 2) void fb_product_kernel(StepArgs a,
     full_gemv_device(f, n_fb, reinterpret_cast<uint4*>(arena), blockIdx.x, gridDim.x);
 }
 
+template <int LEVELS>
 __global__ __launch_bounds__(MFMA_THREADS) void fb_product_mfma_kernel(StepArgs a, FullArgs f) {
-    extern __shared__ uint4 mfma_lds[];
+    extern __shared__ uint4 stage_lds[];
     const int n_fb = a.counters[CNT_FALLBACK];
     if (n_fb == 0) return;
-    if (n_fb > FULL_G) full_mfma_all(f, n_fb, mfma_lds, blockIdx.x, gridDim.x);
-    else full_gemv_device(f, n_fb, mfma_lds, blockIdx.x, gridDim.x);
+    if (n_fb > FULL_G) full_mfma_all<LEVELS>(f, n_fb, stage_lds, blockIdx.x, gridDim.x);
+    else full_gemv_device(f, n_fb, stage_lds, blockIdx.x, gridDim.x);
 }
 
 __global__ __launch_bounds__(SEQ_THREADS) void fb_topk_kernel(StepArgs a) {             // grid (chunks of V, B)
@@ -3283,7 +3298,7 @@ static int check_pair(const csv_workspace* ws, const csv_index* idx, const void*
 
 // The dynamic-LDS limit of a kernel is one attribute per process and device, shared by every workspace: it is only
 // ever raised, so a workspace created later with smaller needs cannot take away what an earlier one's launches rely on.
-enum { K_ROUND0, K_ROUND0_THRESH, K_ROUND0_PLANS, K_STEP, K_TAIL, K_RCERT, K_FBPROD, K_FBPRODM, K_FULLMFMA, K_ALG1, K_BOUND0, K_NKERN = K_BOUND0 + 8 };
+enum { K_ROUND0, K_ROUND0_THRESH, K_ROUND0_PLANS, K_STEP, K_STEP_MANY, K_TAIL, K_RCERT, K_FBPROD, K_FBPRODM /* + levels */, K_FULLMFMA = K_FBPRODM + 4 /* + levels */, K_ALG1 = K_FULLMFMA + 4, K_BOUND0, K_NKERN = K_BOUND0 + 8 };
 static size_t g_lds_limit[CSV_STATIC_MAX_DEVICES][K_NKERN];
 static pthread_mutex_t g_attr_lock = PTHREAD_MUTEX_INITIALIZER;
 #define CSV_STATIC_LDS_MAX 16384     // at least the static shared memory of any kernel here
@@ -3417,6 +3432,15 @@ __global__ __launch_bounds__(256) void unpermute_kernel(const float* __restrict_
         for (int q = tid >> 6; q < ns; q += 4) out[(size_t)(s0 + q) * V + t0 + t] = tile[t][q];
 }
 
+// (a full_k_levels of zero, two or three)
+static void launch_fb_product_mfma(int grid, const StepArgs& a, const FullArgs& f, hipStream_t st) {
+    switch (full_k_levels(f.d)) {
+        case 3: fb_product_mfma_kernel<3><<<grid, MFMA_THREADS, mfma_lds(3), st>>>(a, f); break;
+        case 2: fb_product_mfma_kernel<2><<<grid, MFMA_THREADS, mfma_lds(2), st>>>(a, f); break;
+        default: fb_product_mfma_kernel<0><<<grid, MFMA_THREADS, mfma_lds(0), st>>>(a, f); break;
+    }
+}
+
 // tmp: [n_fixed x V] scratch for the MFMA path when the result is wanted in token-id order (may be NULL otherwise)
 static int launch_full(const csv_index* idx, const uint16_t* d_h, const int32_t* list, int n_fixed,
                        float* out, long long stride, int scatter, float* tmp, hipStream_t st) {
@@ -3434,7 +3458,11 @@ static int launch_full(const csv_index* idx, const uint16_t* d_h, const int32_t*
             f.out_stride = 1;
             f.row_stride = n_fixed;
         }
-        full_mfma_kernel<<<cus, MFMA_THREADS, MFMA_LDS, st>>>(f);
+        switch (full_k_levels(idx->d)) {
+            case 3: full_mfma_kernel<3><<<cus, MFMA_THREADS, mfma_lds(3), st>>>(f); break;
+            case 2: full_mfma_kernel<2><<<cus, MFMA_THREADS, mfma_lds(2), st>>>(f); break;
+            default: full_mfma_kernel<0><<<cus, MFMA_THREADS, mfma_lds(0), st>>>(f); break;
+        }
         CSV_LAUNCH_CHECK("full_mfma_kernel");
         if (two_step) {
             unpermute_kernel<<<dim3((idx->V + UNPERM_TILE - 1) / UNPERM_TILE, (n_fixed + UNPERM_TILE - 1) / UNPERM_TILE), 256, 0, st>>>(tmp, idx->inv, idx->V, n_fixed, out);
@@ -3502,14 +3530,15 @@ extern "C" int csv_workspace_create(const csv_index* idx, int B_max, int K_cap_r
         free(tmp);
     }
     // the per-sequence kernels may need more dynamic LDS than the default limit when C is large
-    if (e == hipSuccess) e = raise_lds(ws->device, K_FULLMFMA, (const void*)full_mfma_kernel, MFMA_LDS);
+    const int levels = full_k_levels(idx->d);
+    if (e == hipSuccess) e = raise_lds(ws->device, K_FULLMFMA + levels, levels == 3 ? (const void*)full_mfma_kernel<3> : levels == 2 ? (const void*)full_mfma_kernel<2> : (const void*)full_mfma_kernel<0>, mfma_lds(levels));
     if (e == hipSuccess) e = raise_lds(ws->device, K_ROUND0, (const void*)round0_kernel<false, false>, round0_lds(ws));
     if (e == hipSuccess) e = raise_lds(ws->device, K_ROUND0_THRESH, (const void*)round0_kernel<true, false>, round0_lds(ws));
     if (e == hipSuccess) e = raise_lds(ws->device, K_ROUND0_PLANS, (const void*)round0_kernel<true, true>, round0_lds(ws));
     if (e == hipSuccess) {
         size_t l = cert_lds(ws);
         const size_t cand[] = {(size_t)FULL_G * idx->d * 2 /* also covers the two h slots of the tile loop */, (size_t)FB_CHUNK * 4, (size_t)STAGE_CAP * 8,
-                               B_max > FULL_G ? (size_t)MFMA_LDS : 0 /* more than FULL_G fallback sequences: the MFMA product's h fragments */};
+                               B_max > FULL_G ? (size_t)mfma_lds(levels) : 0 /* more than FULL_G fallback sequences: the MFMA product's h fragments */};
         for (size_t c : cand) l = c > l ? c : l;
         ws->tail_lds = l;
         e = raise_lds(ws->device, K_TAIL, (const void*)tail_kernel, l);
@@ -3530,7 +3559,7 @@ extern "C" int csv_workspace_create(const csv_index* idx, int B_max, int K_cap_r
         ws->split_min_B = 0;      // decided per step from the history
         if (e == hipSuccess) e = raise_lds(ws->device, K_RCERT, (const void*)round_cert_kernel, cert_lds(ws));
         if (e == hipSuccess) e = raise_lds(ws->device, K_FBPROD, (const void*)fb_product_kernel, (size_t)FULL_G * idx->d * 2);
-        if (e == hipSuccess) e = raise_lds(ws->device, K_FBPRODM, (const void*)fb_product_mfma_kernel, MFMA_LDS);
+        if (e == hipSuccess) e = raise_lds(ws->device, K_FBPRODM + levels, levels == 3 ? (const void*)fb_product_mfma_kernel<3> : levels == 2 ? (const void*)fb_product_mfma_kernel<2> : (const void*)fb_product_mfma_kernel<0>, mfma_lds(levels));
         int r0_per_cu = 0x7fffffff;          // of every form of the kernel: the blocks of a sequence wait for each other
         auto fits = [&](auto kernel) {
             int n = 0;
@@ -3548,10 +3577,12 @@ extern "C" int csv_workspace_create(const csv_index* idx, int B_max, int K_cap_r
         ws->round0_capacity = r0_per_cu * cus;
         // round 0 and the tail in one launch: every block of that grid (one per compute unit) must be resident
         ws->fused_lds = round0_lds(ws) > l ? round0_lds(ws) : l;
-        int fused_per_cu = 0;
-        if (e == hipSuccess) e = raise_lds(ws->device, K_STEP, (const void*)step_kernel, ws->fused_lds);
-        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&fused_per_cu, step_kernel, SEQ_THREADS, ws->fused_lds);
-        ws->fused_ok = fused_per_cu >= 1;
+        int few_per_cu = 0, many_per_cu = 0;
+        if (e == hipSuccess) e = raise_lds(ws->device, K_STEP, (const void*)step_kernel<false>, ws->fused_lds);
+        if (e == hipSuccess) e = raise_lds(ws->device, K_STEP_MANY, (const void*)step_kernel<true>, ws->fused_lds);
+        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&few_per_cu, step_kernel<false>, SEQ_THREADS, ws->fused_lds);
+        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&many_per_cu, step_kernel<true>, SEQ_THREADS, ws->fused_lds);
+        ws->fused_ok = few_per_cu >= 1 && many_per_cu >= 1;
     }
     if (e != hipSuccess) {
         csv_set_error("workspace allocation failed: %s", hipGetErrorString(e));
@@ -3708,7 +3739,7 @@ extern "C" int csv_decode_step(csv_workspace* ws, const csv_index* idx, const ui
         CSV_LAUNCH_CHECK("alg1_kernel");
         CSV_MARK(2);
         if (B > FULL_G) {
-            fb_product_mfma_kernel<<<ws->tail_grid, MFMA_THREADS, MFMA_LDS, st>>>(a, f);
+            launch_fb_product_mfma(ws->tail_grid, a, f, st);
             CSV_LAUNCH_CHECK("fb_product_mfma_kernel");
         } else {
             fb_product_kernel<<<ws->tail_grid, TAIL_THREADS, (size_t)FULL_G * idx->d * 2, st>>>(a, f);
@@ -3749,7 +3780,8 @@ extern "C" int csv_decode_step(csv_workspace* ws, const csv_index* idx, const ui
     // the tail's blocks ride in the round-0 launch when they all fit next to the round-0 blocks (one block per unit)
     const bool fused = !split && ws->fused_ok && nb * B * 2 <= ws->tail_grid;
     if (fused) {
-        step_kernel<<<ws->tail_grid, SEQ_THREADS, ws->fused_lds, st>>>(a, f, nb);
+        if (B > FULL_G) step_kernel<true><<<ws->tail_grid, SEQ_THREADS, ws->fused_lds, st>>>(a, f, nb);
+        else step_kernel<false><<<ws->tail_grid, SEQ_THREADS, ws->fused_lds, st>>>(a, f, nb);
         CSV_LAUNCH_CHECK("step_kernel");
     } else {
         // Plans are made where recent steps needed later rounds; lists of more than RANK_DIRECT rows only where a seed prefix can
@@ -3779,7 +3811,7 @@ extern "C" int csv_decode_step(csv_workspace* ws, const csv_index* idx, const ui
             }
             if (fb_launches) {
                 if (B > FULL_G) {
-                    fb_product_mfma_kernel<<<ws->tail_grid, MFMA_THREADS, MFMA_LDS, st>>>(a, f);
+                    launch_fb_product_mfma(ws->tail_grid, a, f, st);
                     CSV_LAUNCH_CHECK("fb_product_mfma_kernel");
                 } else {
                     fb_product_kernel<<<ws->tail_grid, TAIL_THREADS, (size_t)FULL_G * idx->d * 2, st>>>(a, f);

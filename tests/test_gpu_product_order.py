@@ -13,7 +13,7 @@ torch = pytest.importorskip("torch")
 def _head(V, d, B, C, seed, k):
     """A random head in which 3 k tokens, spread over the vocabulary, have the same row and bias, and hidden states near that row."""
     rng = np.random.default_rng(seed)
-    W = rng.normal(0, 1 / np.sqrt(d), (V, d)).astype(np.float32)
+    W = rng.standard_normal((V, d), dtype=np.float32) / np.float32(np.sqrt(d))
     same = np.sort(rng.choice(V, 3 * k, replace=False))
     W[same] = W[same[0]]
     b = rng.normal(0, 0.1, V).astype(np.float32)
@@ -24,8 +24,8 @@ def _head(V, d, B, C, seed, k):
 
 
 # V and C such that seven sequences leave the fused launch 151 blocks for the product and the other forms 256, where groups of
-# 256 rows suit the one and groups of 128 the other; rows of 4 KB (their K is cut into parts), of 8 KB, and of 4.5 KB (they are not).
-@pytest.mark.parametrize("d", [2048, 2304, 4096])
+# 256 rows suit the one and groups of 128 the other; rows of 4 and 8 KB (their K is cut into four parts), of 16 KB (eight), and of 4.5 KB (none).
+@pytest.mark.parametrize("d", [2048, 2304, 4096, 8192])
 def test_fallback_logits_do_not_depend_on_the_launch_form(d):
     import paper_2511_21702_amd as csv
     V, C, B, k = 24000, 480, 7, 10
@@ -52,7 +52,7 @@ def test_fallback_logits_do_not_depend_on_the_launch_form(d):
 
 
 # one, two and four tiles of 16 sequences, two passes; K of a single chunk, a ragged last one, cut into parts
-@pytest.mark.parametrize("V,d,B", [(9000, 256, 8), (9001, 2056, 5), (9001, 2048, 17), (70003, 2048, 33), (33000, 4096, 64), (5003, 6144, 70)])
+@pytest.mark.parametrize("V,d,B", [(9000, 256, 8), (9001, 2056, 5), (9001, 2048, 17), (70003, 2048, 33), (33000, 4096, 64), (5003, 6144, 70), (6001, 8192, 40)])
 def test_equal_rows_have_equal_logits(V, d, B):
     import paper_2511_21702_amd as csv
     W, b, h, labels, same = _head(V, d, B, 7, V + B, 60)
