@@ -153,7 +153,7 @@ def main() -> int:
                           "lloyd_iterations": args.kmeans, "assignments": args.kmeans + 1, "seconds": sec,
                           "distance_product_TFLOPs_useful": flops / sec / 1e12,
                           "note": "whole build: every assignment (MFMA distance product, three bf16 pieces per float32 centroid value), "
-                                  "host-side layout, row gather, centroid means; then radii and metadata",
+                                  "layout, row gather, centroid means; then radii and metadata",
                           "empty_clusters": int((e["n"] == 0).sum()), "largest_cluster": int(e["n"].max()), "purity_vs_planted": float(purity)}))
         return 0
     idx = csv.csv_build_index(dW, db, r.C, init_labels=head["labels"].astype(np.int32), centroid_bf16=args.bf16_centroids,

@@ -1,6 +1,6 @@
 // Offline preprocessing: Lloyd's k-means over the rows of W, cluster metadata (centroid, radius, bias maximum)
 // and the row permutation that makes every cluster contiguous (Section III-A.1; Section IV "Offline Preprocessing").
-// Off the per-step hot path: clarity over speed, float64 accumulation for the metadata.
+// Off the per-step hot path.  Everything stays on the device until the metadata is done; float64 accumulation for the metadata.
 #include "csv_common.h"
 
 #include <math.h>

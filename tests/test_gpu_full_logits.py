@@ -13,7 +13,7 @@ torch = pytest.importorskip("torch")
 
 # Vector product: 1..4 sequences, odd V (a tile's second row missing), rows of fewer pieces than one trip and with a remainder.
 # MFMA product: 5.. sequences: sequence counts that are and are not a multiple of four, around 16, 32, 64 and two passes;
-# V around a tile of 64 tokens and a group of 256 rows; one K chunk of 256 (no rotation), a ragged last one, several.
+# V around a tile of 64 tokens and a group of 256 rows; one K chunk of 256, a ragged last one, several.
 @pytest.mark.parametrize("V,d,B", [(1, 8, 1), (65, 2056, 1), (4099, 4096, 2), (1003, 520, 3), (513, 2552, 4),
                                    (63, 8, 5), (64, 256, 8), (65, 264, 15), (257, 512, 16), (3001, 520, 17), (511, 1288, 31), (1025, 256, 32),
                                    (515, 776, 33), (2049, 1032, 64), (700, 264, 65), (129, 2048, 100), (321, 520, 256)])
