@@ -7,6 +7,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <type_traits>
 #include <vector>
 
@@ -32,8 +33,10 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const uint16_t* __rest
 // sort and three copies back took 0.4 ms).
 #define LAY_TOKENS 512
 // hist[wave][c] = its tokens of cluster c.  cand != NULL: the labels are made here, as the smallest word over the
-// assignment's column blocks (equal distances: the smaller cluster id is the smaller word).
-__global__ __launch_bounds__(64) void label_hist_kernel(const unsigned long long* __restrict__ cand, int ncol, int32_t* __restrict__ labels, int V,
+// assignment's column blocks (equal distances: the smaller cluster id is the smaller word).  A negative label ~i stands for
+// the cluster in the low half of win[i] (rows whose nearest centroid took a second look).
+__global__ __launch_bounds__(64) void label_hist_kernel(const unsigned long long* __restrict__ cand, int ncol, const unsigned long long* __restrict__ win,
+                                                        int32_t* __restrict__ labels, int V,
                                                         int C, int32_t* __restrict__ hist) {
     extern __shared__ int32_t lay_cnt[];
     const int lane = threadIdx.x, base = blockIdx.x * LAY_TOKENS;
@@ -54,6 +57,10 @@ __global__ __launch_bounds__(64) void label_hist_kernel(const unsigned long long
                 labels[t] = l;
             } else {
                 l = labels[t];
+                if (l < 0) {
+                    l = (int)(unsigned)win[~l];
+                    labels[t] = l;
+                }
             }
             atomicAdd(&lay_cnt[l], 1);
         }
@@ -453,40 +460,40 @@ __global__ __launch_bounds__(256) void radius_finish_kernel(const float* __restr
 
 // Lloyd assignment: labels[i] = argmin_c ||W_i - mu_c||^2, ties to the smaller cluster id.
 // ||W_i - mu_c||^2 = ||W_i||^2 - 2 <W_i,mu_c> + ||mu_c||^2 and the first term does not depend on c, so the work is the
-// dense contraction [V x d] . [d x C]: v_mfma_f32_16x16x32_bf16 with the rows of W (bf16) as one operand and the float32
-// centroids, split exactly into three bf16 pieces (three MFMAs per k-block give float32-exact products), as the other.
-// The pieces are split once per assignment (split_centroids_kernel), not by every block that reads them: they lie in
-// fragment order, [k-block of 32][cluster tile of 16][piece][lane], so that a block's share of a k-block is one run.
-// Block = 8 waves, 2 (rows) x 4 (clusters); a wave owns 16 MT rows x 16 NT clusters in accumulators over the whole of K.
-// Both operands go through LDS in fragment order (1 KB reads, no bank conflicts), one k-block per stage, two stages:
-// while a stage is consumed the next one, requested an iteration ahead into registers, is stored between the MFMAs, and
-// one barrier (for LDS traffic only: the requests cross it) ends the iteration.  A fragment of W serves 3 NT MFMAs, one
-// of the centroids MT: at MT = 8, NT = 4 a stage is 3072 matrix-core cycles per SIMD for 1792 cycles of LDS traffic.
-// Accumulator register r of lane (li, g) is [row 4g + r][cluster li]: the arg-min over a tile's 16 clusters is a
-// reduction inside a 16-lane DPP row, over a block's four column waves through LDS.  Each block writes, per row, the best
-// (distance key, cluster) of its columns as one 64-bit word; label_hist_kernel takes the smallest.
-// Bound by the matrix cores: V = 128256, d = 4096, C = 1024 takes 2.45 ms = 1.32 PFLOP/s (8 waves of 16 rows x 64 clusters, each
-// block splitting its own centroids: 7.45 ms); V = 32000, d = 1024, C = 256 (128 x 256 tiles) 49 us, was 124 us.
+// dense contraction [V x d] . [d x C].  W is bf16, the centroids are float32: split exactly into three bf16 pieces, three MFMAs
+// per k-block give a float32-exact product (assign_exact_kernel), at three times the matrix work of bf16 centroids.
+// One piece settles nearly every row: with mu_c rounded to bf16 a score is off by at most 2 ||W_i|| ||mu_c - bf16(mu_c)||, and only
+// centroids within twice that of the best can be the nearest.  So, where there is enough work to pay for the passes
+// (assign_near_pays): round_centroids_kernel rounds the centroids and measures what the rounding left out; assign_near_kernel scores
+// all pairs with the rounded ones and keeps, per row and group of clusters, the three best; assign_pick_kernel labels the rows with one
+// centroid in reach and lists the others' pairs, which assign_pairs_kernel scores exactly; rows with many in reach, or
+// whose reach is not finite, go to assign_exact_kernel.  An exact score is one sum in one order (k-blocks ascending, a value's
+// pieces one after the other) wherever it is taken, so the labels are the same whichever way they were found.
+// Rows with more than one in reach: 20 % where clusters were planted and some share their seeds or have none, 0.2-6 % of heads
+// without or with blurred clusters (V = 16384, d = 1024 and 4096, C = 256 and 512), 2.0-2.4 centroids each.
+// V = 128256, d = 4096, C = 1024: 1.01 ms an assignment (0.80 the rounded scores, 0.03 the look through them, 0.16 the pairs, 0.02 the rest), the
+// exact product over all rows 2.35.
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 as_bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float as_floatx4_t;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t as_uintx4_t;     // a 16-byte piece in registers (uint4 arrays held across the loop went to scratch)
 #define CSV_ANGLE_SLACK (1.0 / 4096.0)     // added to every angular radius (radians), next to the relative slack
 #define AS_THREADS 512
 
+__device__ __forceinline__ uint32_t as_tops(float lo, float hi) {         // the upper halves of two floats in one word
+    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+// v = hi + mid + lo, three bf16 values that add up to v exactly; what is cut off is never rounded, so the halves need no masks
 __device__ __forceinline__ void as_split3(const float4& x0, const float4& x1, uint4& hi, uint4& mid, uint4& lo) {
     const float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-    uint32_t h[8], m[8], l[8];
+    float r1[8], r2[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        h[i] = __float_as_uint(v[i]) & 0xffff0000u;
-        const float r1 = v[i] - __uint_as_float(h[i]);
-        m[i] = __float_as_uint(r1) & 0xffff0000u;
-        const float r2 = r1 - __uint_as_float(m[i]);
-        l[i] = __float_as_uint(r2) & 0xffff0000u;
+        r1[i] = v[i] - __uint_as_float(__float_as_uint(v[i]) & 0xffff0000u);
+        r2[i] = r1[i] - __uint_as_float(__float_as_uint(r1[i]) & 0xffff0000u);
     }
-    hi = make_uint4((h[0] >> 16) | h[1], (h[2] >> 16) | h[3], (h[4] >> 16) | h[5], (h[6] >> 16) | h[7]);
-    mid = make_uint4((m[0] >> 16) | m[1], (m[2] >> 16) | m[3], (m[4] >> 16) | m[5], (m[6] >> 16) | m[7]);
-    lo = make_uint4((l[0] >> 16) | l[1], (l[2] >> 16) | l[3], (l[4] >> 16) | l[5], (l[6] >> 16) | l[7]);
+    hi = make_uint4(as_tops(v[0], v[1]), as_tops(v[2], v[3]), as_tops(v[4], v[5]), as_tops(v[6], v[7]));
+    mid = make_uint4(as_tops(r1[0], r1[1]), as_tops(r1[2], r1[3]), as_tops(r1[4], r1[5]), as_tops(r1[6], r1[7]));
+    lo = make_uint4(as_tops(r2[0], r2[1]), as_tops(r2[2], r2[3]), as_tops(r2[4], r2[5]), as_tops(r2[6], r2[7]));
 }
 // minimum over the 16 lanes of a DPP row (lanes 16g .. 16g+15); every lane of the row gets it
 __device__ __forceinline__ unsigned row16_min_u(unsigned v) {
@@ -514,11 +521,11 @@ __global__ __launch_bounds__(256) void centroid_norm_kernel(const float* __restr
 }
 
 // The three bf16 pieces of every centroid value in fragment order: out[((kb * CT + ct) * 3 + piece) * 64 + lane], lane =
-// 16 g + li: cluster 16 ct + li, the eight k values 32 kb + 8 g ...; zero past C and past d.  One wave per (kb, ct).
-__global__ __launch_bounds__(256) void split_centroids_kernel(const float* __restrict__ mu, int d, int C, int CT, int nkb, uint4* __restrict__ out) {
+// 16 g + li: cluster 16 ct + li, the eight k values 32 kb + 8 g ...; zero past C and past d.  One wave per (kb, ct).  needed: nothing is done where it counts nothing.
+__global__ __launch_bounds__(256) void split_centroids_kernel(const float* __restrict__ mu, int d, int C, int CT, int nkb, const int* __restrict__ needed, uint4* __restrict__ out) {
     const int lane = threadIdx.x & 63;
     const int ct = blockIdx.x, kb = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (kb >= nkb) return;
+    if (kb >= nkb || (needed && *needed == 0)) return;
     const int c = ct * 16 + (lane & 15), k = kb * 32 + (lane >> 4) * 8;
     uint4 hi = make_uint4(0, 0, 0, 0), mid = hi, lo = hi;
     if (c < C && k < d) {                                    // d is a multiple of 8: the eight values are all in or all out
@@ -542,11 +549,26 @@ __device__ __forceinline__ void as_for(F f) {              // f(0), f(1), ... wi
     }
 }
 
-// Bs: CT cluster tiles (a multiple of 4 NT) of pieces.  cand[column block * V + row] = (monotone key of the best distance) << 32 | its cluster.
-template <int MT, int NT>
-__global__ __launch_bounds__(AS_THREADS) void assign_mfma_kernel(const uint16_t* __restrict__ W, const uint4* __restrict__ Bs,
-                                                                 const float* __restrict__ cn, int V, int d, int C, int CT,
-                                                                 int ncol, int ntot, unsigned long long* __restrict__ cand) {
+// The exact scores of rows against all centroids.  The centroids' pieces are split once per assignment (split_centroids_kernel): they lie in
+// fragment order, [k-block of 32][cluster tile of 16][piece][lane], so that a block's share of a k-block is one run.
+// Block = 8 waves, 2 (rows) x 4 (clusters); a wave owns 16 MT rows x 16 NT clusters in accumulators over the whole of K.
+// Both operands go through LDS in fragment order (1 KB reads, no bank conflicts), one k-block per stage, two stages:
+// while a stage is consumed the next one, requested an iteration ahead into registers, is stored between the MFMAs, and
+// one barrier (for LDS traffic only: the requests cross it) ends the iteration.  A fragment of W serves 3 NT MFMAs, one
+// of the centroids MT: at MT = 8, NT = 4 a stage is 3072 matrix-core cycles per SIMD for 1792 cycles of LDS traffic.
+// Accumulator register r of lane (li, g) is [row 4g + r][cluster li]: the arg-min over a tile's 16 clusters is a
+// reduction inside a 16-lane DPP row, over a block's four column waves through LDS.  Each block writes, per row, the best
+// (distance key, cluster) of its columns as one 64-bit word, to win[column block * V + row]; label_hist_kernel takes the smallest.
+// LISTED: the rows are rows[list[i]], i < *count (blocks beyond leave at once: few heads list any, then mostly few), and their best words meet in
+// win[list[i]].
+// Bound by the matrix cores: V = 128256, d = 4096, C = 1024 takes 2.45 ms = 1.32 PFLOP/s (8 waves of 16 rows x 64 clusters, each
+// block splitting its own centroids: 7.45 ms); V = 32000, d = 1024, C = 256 (128 x 256 tiles) 49 us, was 124 us.
+// Bs: CT cluster tiles (a multiple of 4 NT) of pieces.
+template <int MT, int NT, bool LISTED>
+__global__ __launch_bounds__(AS_THREADS) void assign_exact_kernel(const uint16_t* __restrict__ W, const uint4* __restrict__ Bs,
+                                                                  const float* __restrict__ cn, int V, int d, int C, int CT,
+                                                                  int ncol, int ntot, const int* __restrict__ count, const int* __restrict__ list,
+                                                                  const int* __restrict__ rows, unsigned long long* __restrict__ win) {
     extern __shared__ as_uintx4_t as_lds[];
     constexpr int AP = 2 * MT * 64 / AS_THREADS, BP = 4 * NT * 192 / AS_THREADS;      // 16-byte pieces a thread stages of W, of the centroids
     constexpr int ASZ = 2 * MT * 64, STAGE = ASZ + 4 * NT * 192;                      // pieces per stage
@@ -558,10 +580,17 @@ __global__ __launch_bounds__(AS_THREADS) void assign_mfma_kernel(const uint16_t*
     const int tile = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
     if (tile >= ntot) return;
     const int bn = tile % ncol, row0 = tile / ncol * (2 * MT * 16);
+    if (LISTED) {
+        V = *count;
+        if (row0 >= V) return;
+    }
     const int nq = d >> 3, nkb = (d + 31) >> 5;
     const as_uintx4_t* ap[AP];
 #pragma unroll
-    for (int i = 0; i < AP; ++i) ap[i] = reinterpret_cast<const as_uintx4_t*>(W + (size_t)min(row0 + (wave + 8 * i) * 16 + li, V - 1) * d);
+    for (int i = 0; i < AP; ++i) {
+        const int r = min(row0 + (wave + 8 * i) * 16 + li, V - 1);
+        ap[i] = reinterpret_cast<const as_uintx4_t*>(W + (size_t)(LISTED ? rows[list[r]] : r) * d);
+    }
     const as_uintx4_t* bp = reinterpret_cast<const as_uintx4_t*>(Bs) + (size_t)bn * (4 * NT) * 192 + tid;
     as_uintx4_t ra[AP], rb[BP];
     bool in_row = true;                                      // the requested pieces of W lie inside their rows
@@ -645,8 +674,441 @@ __global__ __launch_bounds__(AS_THREADS) void assign_mfma_kernel(const uint16_t*
             unsigned long long x = best[r * 4];
 #pragma unroll
             for (int q = 1; q < 4; ++q) x = best[r * 4 + q] < x ? best[r * 4 + q] : x;
-            cand[(size_t)bn * V + row0 + r] = x;
+            if (LISTED) atomicMin(&win[list[row0 + r]], x);
+            else win[(size_t)bn * V + row0 + r] = x;
         }
+}
+
+// Centroids rounded to bf16 (nearest even) in fragment order, out[(kb * CT + ct) * 64 + lane], lane = (cluster li of the tile, k
+// group g); zeros past C and past d.  With them cn[c] = ||mu_c||^2 and left[c], what a score against the rounded centroid can be off by per unit of ||W_i||: 2 (||mu_c -
+// bf16(mu_c)|| + 2^-17 ||mu_c||), the second term for the float32 sums; sums in float64.  (A centroid that is not finite is nobody's nearest by cn alone: left = 0.)
+// unit != 0 (spherical clustering): every direction counts as of length one, so the arg-min is the largest cosine.
+// One block per tile of 16 clusters, a k-block per wave at a time.  Also empties the lists.
+__global__ __launch_bounds__(1024) void round_centroids_kernel(const float* __restrict__ mu, int d, int C, int CT, int nkb, int unit, as_uintx4_t* __restrict__ out,
+                                                              float* __restrict__ cn, float* __restrict__ left, int* __restrict__ counts) {
+    __shared__ double red[2][16][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ct = blockIdx.x, c = ct * 16 + (lane & 15), g = lane >> 4;
+    if (ct == 0 && threadIdx.x < 3) counts[threadIdx.x] = 0;
+    double nn = 0.0, rr = 0.0;
+    for (int kb = wave; kb < nkb; kb += 16) {
+        const int k = kb * 32 + g * 8;
+        as_uintx4_t x = {0, 0, 0, 0};
+        if (c < C && k < d) {                                    // d is a multiple of 8: the eight values are all in or all out
+            const float4* src = reinterpret_cast<const float4*>(mu + (size_t)c * d + k);
+            const float4 x0 = src[0], x1 = src[1];
+            const float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t u = __float_as_uint(v[e]), r = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
+                const double whole = (double)v[e], rest = whole - (double)__uint_as_float(r);
+                nn = fma(whole, whole, nn);
+                rr = fma(rest, rest, rr);
+                x[e >> 1] |= e & 1 ? r : r >> 16;
+            }
+        }
+        out[((size_t)kb * CT + ct) * 64 + lane] = x;
+    }
+    red[0][wave][lane] = nn;
+    red[1][wave][lane] = rr;
+    __syncthreads();
+    if (threadIdx.x >= 16 || ct * 16 + threadIdx.x >= C) return;
+    nn = rr = 0.0;
+    for (int w = 0; w < 16; ++w)
+        for (int q = 0; q < 4; ++q) {
+            nn += red[0][w][threadIdx.x + 16 * q];
+            rr += red[1][w][threadIdx.x + 16 * q];
+        }
+    cn[ct * 16 + threadIdx.x] = unit ? 1.f : (float)nn;
+    const double off = 2.0 * (sqrt(rr) + 0x1p-17 * sqrt(nn)) * (1.0 + 1e-6);
+    left[ct * 16 + threadIdx.x] = nn + off < (double)INFINITY ? (float)off : 0.f;
+}
+
+// The three smallest of a set of words, ascending.
+struct Low3 {
+    unsigned a, b, c;
+};
+__device__ __forceinline__ Low3 low3_merge(const Low3& x, const Low3& y) {             // of two disjoint sets
+    return Low3{min(x.a, y.a), min(max(x.a, y.a), min(x.b, y.b)), min(min(x.c, y.c), min(max(x.b, y.a), max(x.a, y.b)))};
+}
+template <int CTRL>
+__device__ __forceinline__ Low3 low3_move(const Low3& x) {
+    return Low3{(unsigned)dpp_move<CTRL, 0xf>((int)x.a, (int)x.a), (unsigned)dpp_move<CTRL, 0xf>((int)x.b, (int)x.b), (unsigned)dpp_move<CTRL, 0xf>((int)x.c, (int)x.c)};
+}
+// The lane keeps its second set if odd, else its first, and merges it with the same set of the lane that CTRL pairs it with, which keeps the other.
+template <int CTRL>
+__device__ __forceinline__ Low3 low3_trade(bool odd, const Low3& first, const Low3& second) {
+    const Low3 keep = {odd ? second.a : first.a, odd ? second.b : first.b, odd ? second.c : first.c};
+    const Low3 give = {odd ? first.a : second.a, odd ? first.b : second.b, odd ? first.c : second.c};
+    return low3_merge(keep, low3_move<CTRL>(give));
+}
+
+// Score word of a (row, cluster) pair: the monotone key of the score with the cluster's place in its group in the low AS_ID_BITS bits.
+#define AS_ID_BITS 6
+#define AS_ID_MASK 63u
+
+// Scores ||mu_c||^2 - 2 <W_i, bf16(mu_c)> of all pairs, less what they can be off by; per row and group of 16 NT clusters the three smallest words, to
+// words[(group * 3 + place) * V + row].  Rows are taken in the given order (of the clusters so far: the rows of a block then mostly
+// have the same centroids in reach), row being the place in it.  Block = 8 waves, 2 (rows) x 4 (clusters); a wave owns 16 MT rows x 16 NT clusters (one
+// group) in accumulators over the whole of K.  Both operands go from memory to LDS without passing registers: W by whole 128-byte lines,
+// 64 values of K of every row a stage (three stages, its 16-byte pieces swapped within a line by the row's low bits, so that the
+// fragment reads are free of bank conflicts), the centroids 32 values of K a stage (four stages) in the fragment order in which
+// they lie in memory.  A wave requests its share of the pieces three to four k-blocks ahead; a k-block issues as many requests in every wave, so "all but
+// the last two k-blocks' requests" is a count of vmcnt.  The block's two halves (waves 0-3 and 4-7, one of each per SIMD) run half a k-block
+// apart: while one reads its fragments the other has the matrix cores, a barrier after each half.
+// A wave passes 2 nkb + 2 barriers, the second half one before the loop, the first half one after it.
+// V = 128256, d = 4096, C = 1024 (256 x 256 tiles): 0.80 ms = 1.35 PFLOP/s with the three best, 0.86 with the best and the norms; the product alone 0.77,
+// without the two halves 0.91, with W by 64-byte pieces 0.85, through registers 1.10 ms; without any requests in the loop it would take 0.61-0.64 ms.
+// FINAL: the centroids are bf16 values (rows of W, the first assignment's), so the scores are exact; the best (distance key, cluster) of a row over the
+// block's columns goes to win[column block * V + row] as assign_exact_kernel leaves it (a score that is not finite counts as none of a number, which is what
+// zero pieces make of a row with infinities).  norms: ||W_i||, a little more than that, for the assignments to come.
+template <int MT, int NT, bool FINAL>
+__global__ __launch_bounds__(AS_THREADS) void assign_near_kernel(const uint16_t* __restrict__ W, const int32_t* __restrict__ order, const as_uintx4_t* __restrict__ Bs,
+                                                                 const float* __restrict__ cn, int V, int d, int C, int CT,
+                                                                 int ncol, int ntot, const float* __restrict__ left, double* __restrict__ norms, unsigned* __restrict__ words, unsigned long long* __restrict__ win) {
+    extern __shared__ as_uintx4_t as_lds[];
+    constexpr int ASZ = 2 * MT * 128, BSZ = 4 * NT * 64;                                  // 16-byte pieces per stage of W, of the centroids
+    constexpr int AP = ASZ / AS_THREADS, BP = BSZ / AS_THREADS, AH = AP / 2, OPEN = 2 * (AH + BP);
+    static_assert(AP * AS_THREADS == ASZ && BP * AS_THREADS == BSZ && AP % 2 == 0 && (OPEN == 8 || OPEN == 6 || OPEN == 4), "staging layout");
+    as_uintx4_t* ldb = as_lds + 3 * ASZ;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, g = lane >> 4, wm = wave >> 2, wn = wave & 3;
+    // blocks are dealt round-robin to the eight XCDs: each gets a contiguous run of tiles, columns fastest, so that the
+    // blocks that share rows of W and the centroids of a k-block sit behind one L2
+    const int tile = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (tile >= ntot) return;
+    const int bn = tile % ncol, row0 = tile / ncol * (2 * MT * 16);
+    const int nq = d >> 3, nst = (d + 63) >> 6, nkb = 2 * nst;
+    const int piece = (lane & 7) ^ (lane >> 3);              // of the eight of a line; rows go to LDS by eights, so lane >> 3 is the row's low bits
+    const as_uintx4_t* ap[AP];
+#pragma unroll
+    for (int i = 0; i < AP; ++i) {
+        const int p = min(row0 + (wave + 8 * i) * 8 + (lane >> 3), V - 1);
+        ap[i] = reinterpret_cast<const as_uintx4_t*>(W + (size_t)(order ? order[p] : p) * d);
+    }
+    const as_uintx4_t* bp = Bs + (size_t)bn * (4 * NT) * 64 + tid;
+    auto load = [&](const as_uintx4_t* src, as_uintx4_t* dst) {          // lane l's piece to dst + l
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+    };
+    // past the last stage: requests from the last one to a stage nobody reads again; past d: some piece of the row, which meets zeros
+    auto request_w = [&](int s, int slot, int half) {
+        const int q = min(min(s, nst - 1) * 8 + piece, nq - 1);
+#pragma unroll
+        for (int i = 0; i < AH; ++i) load(ap[half * AH + i] + q, as_lds + slot * ASZ + wave * 64 + (half * AH + i) * AS_THREADS);
+    };
+    auto request_c = [&](int kb) {
+#pragma unroll
+        for (int i = 0; i < BP; ++i) load(bp + (size_t)min(kb, nkb - 1) * CT * 64 + i * AS_THREADS, ldb + (kb & 3) * BSZ + wave * 64 + i * AS_THREADS);
+    };
+    auto wait_open = [&]() {                                 // all requests but the last two k-blocks' have arrived
+        if constexpr (OPEN == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        else if constexpr (OPEN == 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+    };
+    auto barrier = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    as_floatx4_t acc[MT][NT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[m][t] = as_floatx4_t{0.f, 0.f, 0.f, 0.f};
+    // in the order of their k-blocks: the first stage's pieces and centroids are older than the last OPEN requests
+    request_w(0, 0, 0);
+    request_w(0, 0, 1);
+    request_c(0);
+    request_c(1);
+    request_w(1, 1, 0);
+    request_w(1, 1, 1);
+    request_c(2);
+    wait_open();
+    barrier();
+    if (wm == 1) barrier();
+    int slot = 0;
+    constexpr int NM = MT / 4;                               // FINAL: of the tile rows that four waves read, each sums the squares of a quarter
+    float ss[NM];
+#pragma unroll
+    for (int i = 0; i < NM; ++i) ss[i] = 0.f;
+    const int abase = (wm * MT * 2 + (li >> 3)) * 64 + (li & 7) * 8;
+    auto step = [&](auto odd_t, int kb) {
+        constexpr int odd = decltype(odd_t)::value;
+        const as_uintx4_t* cur = as_lds + slot * ASZ;
+        const as_uintx4_t* cub = ldb + (kb & 3) * BSZ;
+        as_bf16x8_t A[MT], B[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) B[t] = __builtin_bit_cast(as_bf16x8_t, cub[(wn * NT + t) * 64 + lane]);
+        const int q = (odd * 4 + g) ^ (li & 7);
+#pragma unroll
+        for (int m = 0; m < MT; ++m) A[m] = __builtin_bit_cast(as_bf16x8_t, cur[abase + m * 128 + q]);
+        uint4 sq[NM];
+        if constexpr (FINAL)
+#pragma unroll
+            for (int i = 0; i < NM; ++i) sq[i] = __builtin_bit_cast(uint4, cur[abase + (wn * NM + i) * 128 + q]);
+        // into the slots of the stage before this one, of the k-block before this one: both halves of the block have read them
+        request_w((kb >> 1) + 2, slot == 0 ? 2 : slot - 1, odd);
+        request_c(kb + 3);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (wm == 1) wait_open();
+        barrier();
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[m], B[t], acc[m][t], 0, 0, 0);
+        __builtin_amdgcn_s_setprio(0);
+        if constexpr (FINAL)
+#pragma unroll
+            for (int i = 0; i < NM; ++i) ss[i] = dot8_bf16(sq[i], sq[i], ss[i]);
+        if (wm == 0) wait_open();
+        barrier();
+    };
+    for (int kb = 0; kb < nkb; kb += 2) {
+        step(std::integral_constant<int, 0>{}, kb);
+        step(std::integral_constant<int, 1>{}, kb + 1);
+        slot = slot == 2 ? 0 : slot + 1;
+    }
+    if (wm == 0) barrier();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // no request may land in what the results go through
+    __syncthreads();
+    // accumulator register r of lane (li, g) is [row 4g + r][cluster li]: the three best of the wave's tiles, then of the 16 lanes
+    const int c0 = (bn * 4 + wn) * NT * 16 + li;
+    float norm[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) norm[t] = c0 + 16 * t < C ? cn[c0 + 16 * t] : INFINITY;        // past C: in nobody's reach
+    if constexpr (FINAL) {
+        if (norms && bn == 0) {
+#pragma unroll
+            for (int i = 0; i < NM; ++i) {                   // lane (li, g) holds a quarter of row li's squares
+                const float x = ss[i] + __shfl_xor(ss[i], 16, CSV_WAVE), y = x + __shfl_xor(x, 32, CSV_WAVE);
+                const int row = row0 + (wm * MT + wn * NM + i) * 16 + li;
+                if (g == 0 && row < V) norms[row] = sqrt((double)y) * (1.0 + 0x1p-10);
+            }
+        }
+        unsigned long long* best = reinterpret_cast<unsigned long long*>(as_lds);        // [2 MT 16 rows][4]
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                unsigned bk = 0xffffffffu;
+                int bc = 0x7fffffff;
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    const float v = norm[t] - 2.f * acc[m][t][r];
+                    const unsigned kx = c0 + 16 * t >= C ? 0xffffffffu : fabsf(v) < INFINITY ? fkey(v + 0.0f) : 0xffc00000u;
+                    if (kx < bk) {                           // tiles in ascending cluster order: a tie keeps the smaller id
+                        bk = kx;
+                        bc = c0 + 16 * t;
+                    }
+                }
+                const unsigned mk = row16_min_u(bk);
+                const unsigned cm = row16_min_u(bk == mk ? (unsigned)bc : 0x7fffffffu);
+                if (li == 0) best[((wm * MT + m) * 16 + 4 * g + r) * 4 + wn] = ((unsigned long long)mk << 32) | cm;
+            }
+        __syncthreads();
+        for (int r = tid; r < 2 * MT * 16; r += AS_THREADS)
+            if (row0 + r < V) win[(size_t)bn * V + row0 + r] = min(min(best[r * 4], best[r * 4 + 1]), min(best[r * 4 + 2], best[r * 4 + 3]));
+        return;
+    } else {
+        unsigned* best = reinterpret_cast<unsigned*>(as_lds);    // [column wave][3][2 MT 16 rows]
+        float* wnorm = reinterpret_cast<float*>(as_lds) + 12 * 2 * MT * 16;
+        if (tid < 2 * MT * 16) {
+            const int p = min(row0 + tid, V - 1);
+            wnorm[tid] = (float)norms[order ? order[p] : p];
+        }
+        float off[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) off[t] = c0 + 16 * t < C ? left[c0 + 16 * t] : 0.f;
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            Low3 w[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                unsigned x[NT];
+                const float wr = wnorm[(wm * MT + m) * 16 + 4 * g + r];
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    x[t] = (fkey(norm[t] - 2.f * acc[m][t][r] - wr * off[t]) & ~AS_ID_MASK) | (unsigned)(t * 16 + li);
+                const unsigned p = min(x[0], x[1]), P = max(x[0], x[1]), q = min(x[2], x[3]), Q = max(x[2], x[3]);
+                const unsigned m1 = max(p, q), m2 = min(P, Q);
+                w[r] = Low3{min(p, q), min(m1, m2), max(m1, m2)};
+            }
+            // a lane hands half of its rows to its neighbour, then half of the rest to the next but one: lane li goes on with one row
+            const Low3 x0 = low3_trade<0xB1>(li & 1, w[0], w[2]), x1 = low3_trade<0xB1>(li & 1, w[1], w[3]);
+            Low3 y = low3_trade<0x4E>(li & 2, x0, x1);
+            y = low3_merge(y, low3_move<0x128>(y));          // row_ror by 8, then by 4: the other lanes with this row
+            y = low3_merge(y, low3_move<0x124>(y));
+            const int row = (wm * MT + m) * 16 + 4 * g + (li & 1) * 2 + ((li >> 1) & 1);
+            if (li < 12) best[(wn * 3 + (li >> 2)) * (2 * MT * 16) + row] = li < 4 ? y.a : li < 8 ? y.b : y.c;
+        }
+        __syncthreads();
+        for (int i = tid; i < 12 * 2 * MT * 16; i += AS_THREADS) {
+            const int row = row0 + i % (2 * MT * 16);
+            if (row < V) words[(size_t)(bn * 12 + i / (2 * MT * 16)) * V + row] = best[i];
+        }
+    }
+}
+
+// Labels from the score words.  A word is a lower bound of a centroid's exact score, with twice what it can be off by an upper one; a row's reach is its
+// smallest upper bound.  One centroid in reach: the label.  Else the label is ~(a place in rows) until the place's win word holds the nearest: the row's
+// pairs with the centroids in reach are listed (all of a group whose third is in reach), or, where they are more than AS_PAIRS_ROW, or more than
+// the list holds, or the reach is not finite, the place itself is.  Whole groups and more than AS_PAIRS_CHEAP
+// pairs are listed only while less than an eighth of the list is in use: on heads with many such rows the exact product is the cheaper way.
+// counts: {rows, pairs, rows for all centroids}.  64 rows per block, four threads per row; a block takes its places and pairs in one piece, so
+// that pairs of neighbours in the row order, which share centroids, are neighbours in the list.
+// Bound by reading the words: V = 128256, C = 1024 in 30 us.
+#define AS_PAIRS_ROW 160
+#define AS_PAIRS_CHEAP 16
+#define AS_PAIRS_SHARE 2      // the list holds that many pairs per row of W, or C / 512 of them: a pair takes as long as 100 columns of the exact product
+__global__ __launch_bounds__(256) void assign_pick_kernel(const int32_t* __restrict__ order, const float* __restrict__ cn, const float* __restrict__ left,
+                                                          const double* __restrict__ nrm, const unsigned* __restrict__ words, int ngroups, int group, int V, int C,
+                                                          int cap, int32_t* __restrict__ labels, int* __restrict__ counts, int* __restrict__ rows,
+                                                          unsigned long long* __restrict__ win, int2* __restrict__ pairs, int* __restrict__ list) {
+    __shared__ float s_lim[4][64];
+    __shared__ int s_cnt[4][64], s_one[4][64], s_place[64], s_pair[64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, row = min((int)blockIdx.x * 64 + lane, V - 1);
+    const bool mine = blockIdx.x * 64 + lane < V;
+    const int token = order ? order[row] : row;
+    const float wr = (float)nrm[token];
+    float lim = INFINITY;
+#pragma unroll 4
+    for (int g = wave; g < ngroups; g += 4) {
+        const unsigned a = words[(size_t)(g * 3) * V + row];
+        const int c = min(g * group + (int)(a & AS_ID_MASK), C - 1);
+        const float lo = fkey_inv(a | AS_ID_MASK);
+        lim = fminf(lim, lo + (2.00001f * wr * left[c] + 0x1p-20f * (fabsf(lo) + cn[c])));
+    }
+    s_lim[wave][lane] = lim;
+    __syncthreads();
+    lim = fminf(fminf(s_lim[0][lane], s_lim[1][lane]), fminf(s_lim[2][lane], s_lim[3][lane]));
+    const bool finite = fabsf(lim) < INFINITY;
+    const unsigned reach = fkey(lim) | AS_ID_MASK;
+    auto reached = [&](auto fn) {                            // this thread's share of the row's centroids in reach, in runs
+#pragma unroll 4
+        for (int g = wave; g < ngroups; g += 4) {
+            const unsigned* w = words + (size_t)(g * 3) * V + row;
+            const unsigned a = w[0];
+            if (finite && a <= reach) {
+                const unsigned b = w[V];
+                if (b <= reach && w[2 * (size_t)V] <= reach) {
+                    fn(g * group, min(group, C - g * group));
+                } else {
+                    fn(g * group + (int)(a & AS_ID_MASK), 1);
+                    if (b <= reach) fn(g * group + (int)(b & AS_ID_MASK), 1);
+                }
+            }
+        }
+    };
+    int cnt = 0, one = 0;
+    reached([&](int c, int n) {
+        cnt += n;
+        one = n > 1 ? -1 : one < 0 ? one : c;                // -1: a whole group
+    });
+    s_cnt[wave][lane] = cnt;
+    s_one[wave][lane] = one;
+    __syncthreads();
+    if (wave == 0) {
+        int total = 0;
+        one = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int n = s_cnt[q][lane];
+            s_cnt[q][lane] = total;                          // becomes the row's pairs of the threads before
+            if (n) one = one < 0 ? one : s_one[q][lane];
+            total += n;
+        }
+        const bool settled = finite && total == 1 && one >= 0;
+        const int used = __builtin_amdgcn_readfirstlane(counts[1]);
+        bool few = mine && !settled && finite && total <= AS_PAIRS_ROW && ((one >= 0 && total <= AS_PAIRS_CHEAP) || used < cap >> 3);
+        int upto = few ? total : 0;                          // inclusive sum over the lanes
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(upto, o, CSV_WAVE);
+            if (lane >= o) upto += y;
+        }
+        const unsigned long long open = __ballot(mine && !settled), below = (1ull << lane) - 1ull;
+        const int npairs = __builtin_amdgcn_readlane(upto, 63);
+        int place0 = 0, pair0 = 0;
+        if (open && lane == 0) {
+            place0 = atomicAdd(&counts[0], __popcll(open));
+            if (npairs) pair0 = atomicAdd(&counts[1], npairs);
+        }
+        place0 = __builtin_amdgcn_readfirstlane(place0);
+        pair0 = __builtin_amdgcn_readfirstlane(pair0);
+        if (pair0 > cap - npairs) {                          // the list is full: what is left of it holds no pairs
+            for (int i = pair0 + lane; i < cap && i < pair0 + npairs; i += 64) pairs[i] = make_int2(0, -1);
+            few = false;
+        }
+        const unsigned long long all = __ballot(mine && !settled && !few);
+        int list0 = 0;
+        if (all && lane == 0) list0 = atomicAdd(&counts[2], __popcll(all));
+        list0 = __builtin_amdgcn_readfirstlane(list0);
+        const int place = place0 + __popcll(open & below);
+        s_place[lane] = few ? place : -1;
+        s_pair[lane] = pair0 + upto - total;
+        if (mine && settled) labels[token] = one;
+        if (mine && !settled) {
+            labels[token] = ~place;
+            rows[place] = token;
+            win[place] = ~0ull;
+            if (!few) list[list0 + __popcll(all & below)] = place;
+        }
+    }
+    __syncthreads();
+    if (s_place[lane] < 0) return;
+    int at = s_pair[lane] + s_cnt[wave][lane];
+    reached([&](int c, int n) {
+        for (int i = 0; i < n; ++i) pairs[at++] = make_int2(s_place[lane], c + i);
+    });
+}
+
+// Exact scores of the listed pairs {place, centroid}.  Sixteen pairs at a time are the diagonal of a 16 x 16 product whose first operand is
+// the pairs' rows and whose second is their centroids, split as they are read; a wave has AS_PIPE k-blocks requested ahead.
+// Bound by the splitting and, with few pairs a wave, by latency: 62000 pairs at d = 4096 in 0.16 ms (the rows in token order, so that
+// no two pairs of a wave share a centroid: 0.24; eight k-blocks ahead and half the waves: 1 % of a build slower).
+#define AS_PIPE 4
+__global__ __launch_bounds__(256) void assign_pairs_kernel(const uint16_t* __restrict__ W, const float* __restrict__ mu, const float* __restrict__ cn, int d,
+                                                           int cap, const int* __restrict__ counts, const int2* __restrict__ pairs,
+                                                           const int* __restrict__ rows, unsigned long long* __restrict__ win) {
+    const int lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4, nkb = (d + 31) >> 5, nq = d >> 3, npairs = min(counts[1], cap);
+    for (int i0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 16; i0 < npairs; i0 += gridDim.x * 64) {
+        const int2 pair = pairs[min(i0 + li, npairs - 1)];
+        const bool in = i0 + li < npairs && pair.y >= 0;
+        const as_uintx4_t* w = reinterpret_cast<const as_uintx4_t*>(W + (size_t)(pair.y >= 0 ? rows[pair.x] : 0) * d);
+        const float4* m = reinterpret_cast<const float4*>(mu + (size_t)max(pair.y, 0) * d);
+        as_uintx4_t x[AS_PIPE];
+        float4 m0[AS_PIPE], m1[AS_PIPE];
+        auto request = [&](int u, int kb) {                  // past d: the row's last values, which meet zeros
+            const int q = min(kb * 4 + g, nq - 1);
+            x[u] = w[q];
+            m0[u] = m[2 * q];
+            m1[u] = m[2 * q + 1];
+        };
+        as_floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < AS_PIPE; ++u) request(u, u);
+        for (int kb = 0; kb < nkb; kb += AS_PIPE) {
+#pragma unroll
+            for (int u = 0; u < AS_PIPE; ++u) {
+                uint4 hi, mid, lo;
+                as_uintx4_t xv = x[u];
+                as_split3(m0[u], m1[u], hi, mid, lo);
+                if ((kb + u) * 4 + 4 > nq && (kb + u) * 4 + g >= nq) xv = as_uintx4_t{0, 0, 0, 0};
+                __builtin_amdgcn_sched_barrier(0);
+                request(u, kb + u + AS_PIPE);
+                __builtin_amdgcn_sched_barrier(0);
+                const as_bf16x8_t A = __builtin_bit_cast(as_bf16x8_t, xv);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, __builtin_bit_cast(as_bf16x8_t, hi), acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, __builtin_bit_cast(as_bf16x8_t, mid), acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, __builtin_bit_cast(as_bf16x8_t, lo), acc, 0, 0, 0);
+            }
+        }
+        if ((li >> 2) == g && in) {                          // register li & 3 of this lane is [row li][centroid li]
+            const float dot = li & 2 ? (li & 1 ? acc[3] : acc[2]) : (li & 1 ? acc[1] : acc[0]), v = cn[pair.y] - 2.f * dot;
+            atomicMin(&win[pair.x], ((unsigned long long)fkey(v + 0.0f) << 32) | (unsigned)pair.y);
+        }
+    }
 }
 
 // mu[c] = row init_rows[c] of W widened to float32 (starting centroids).
@@ -897,35 +1359,115 @@ static int gather(csv_index* x, const uint16_t* d_W, const float* d_b, hipStream
     return CSV_OK;
 }
 
-// Which tile a block of the assignment computes: the one whose rounds over the compute units cost least.  Per k-block a
-// 256 x 256 tile takes 3072 cycles of a SIMD's matrix core, a 128 x 256 tile 1536 (with 1464 of LDS traffic), and two
-// 128 x 128 tiles, which share a compute unit, 1792 of LDS traffic between them.
+// Which tile a block of the assignment computes: the one whose rounds over the compute units cost least.  Per k-block of the exact
+// product a 256 x 256 tile takes 3072 cycles of a SIMD's matrix core, a 128 x 256 tile 1536 (with 1464 of LDS traffic), and two
+// 128 x 128 tiles, which share a compute unit, 1792 of LDS traffic between them; of the product with rounded centroids 1024 (matrix core
+// and LDS), 704 and 1024 (LDS).
 struct AssignPlan {
-    int mt, nt, ncol, CT, ntot;
+    int kind, nt, ncol, CT, ntot;
 };
-static AssignPlan assign_plan(int V, int C) {
-    static const struct { int mt, nt, per_cu, cycles; } kind[3] = {{8, 4, 1, 3072}, {4, 4, 1, 1536}, {4, 2, 2, 1792}};
+// kinds: how many of the tiles there are (assign_near_kernel with words has two: the third is never the cheapest where it is used)
+static AssignPlan assign_plan(int V, int C, bool near, int kinds = 3) {
+    static const struct { int mt, nt, per_cu, exact, near; } kind[3] = {{8, 4, 1, 3072, 1024}, {4, 4, 1, 1536, 704}, {4, 2, 2, 1792, 1024}};
     AssignPlan best = {0, 0, 0, 0, 0};
     long long cost = 0;
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < kinds; ++i) {
         const int bm = 2 * kind[i].mt * 16, bn = 4 * kind[i].nt * 16;
         const int ncol = (C + bn - 1) / bn, ntot = (V + bm - 1) / bm * ncol, at_once = 256 * kind[i].per_cu;
-        const long long c = (long long)((ntot + at_once - 1) / at_once) * kind[i].cycles;
+        const long long c = (long long)((ntot + at_once - 1) / at_once) * (near ? kind[i].near : kind[i].exact);
         if (i == 0 || c < cost) {
             cost = c;
-            best = {kind[i].mt, kind[i].nt, ncol, ncol * 4 * kind[i].nt, ntot};
+            best = {i, kind[i].nt, ncol, ncol * 4 * kind[i].nt, ntot};
         }
     }
     return best;
 }
-template <int MT, int NT>
-static int launch_assign(const AssignPlan& p, const uint16_t* W, const uint4* pieces, const float* cn, int V, int d, int C,
-                         unsigned long long* cand, hipStream_t st) {
+// Whether the rounded centroids come first.  They save two thirds of the exact product, V d C, and cost four launches and the pairs, which do not shrink with
+// C.  Builds of four iterations, exact against rounded first: V = 32000, d = 1024, C = 256 661 / 813 us, C = 512 799 / 786; V = 32000, d = 4096, C = 256
+// 1763 / 1914; V = 64000, d = 2048, C = 384 2137 / 1970; V = 128256, d = 4096, C = 256 4849 / 3939, C = 384 6764 / 6471.
+static bool assign_near_pays(int V, int d, int C) {
+    const double work = (double)V * d * C;
+    return C >= 384 ? work >= 20e9 : C >= 256 && work >= 100e9;
+}
+struct AssignRun {                       // what an assignment reads and writes, in the build's scratch
+    const uint16_t* W;
+    const float* mu;
+    float* cn;
+    int V, d, C;
+    uint4* pieces;                       // exact: the centroids' pieces; near: the same, for listed rows
+    unsigned long long* win;             // exact: [column block][V]; near: by place
+    as_uintx4_t* rounded;                // near only, as all below
+    float* left;
+    double* nrm;
+    unsigned* words;
+    int *counts, *rows, *list, cap;
+    int2* pairs;
+    int32_t* labels;
+    hipStream_t st;
+};
+template <int MT, int NT, bool LISTED>
+static int launch_exact(const AssignPlan& p, const AssignRun& r) {
     constexpr int lds = 2 * (2 * MT + 12 * NT) * 1024;
-    CSV_HIP(hipFuncSetAttribute((const void*)assign_mfma_kernel<MT, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-    assign_mfma_kernel<MT, NT><<<(p.ntot + 7) / 8 * 8, AS_THREADS, lds, st>>>(W, pieces, cn, V, d, C, p.CT, p.ncol, p.ntot, cand);
-    CSV_LAUNCH_CHECK("assign_mfma_kernel");
+    CSV_HIP(hipFuncSetAttribute((const void*)assign_exact_kernel<MT, NT, LISTED>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    assign_exact_kernel<MT, NT, LISTED><<<(p.ntot + 7) / 8 * 8, AS_THREADS, lds, r.st>>>(r.W, r.pieces, r.cn, r.V, r.d, r.C, p.CT, p.ncol, p.ntot,
+                                                                                        r.counts + 2, r.list, r.rows, r.win);
+    CSV_LAUNCH_CHECK("assign_exact_kernel");
     return CSV_OK;
+}
+template <int MT, int NT, bool FINAL>
+static int launch_near(const AssignPlan& p, const AssignRun& r, const int32_t* order) {
+    constexpr int lds = (3 * 2 * MT * 128 + 4 * 4 * NT * 64) * 16;
+    CSV_HIP(hipFuncSetAttribute((const void*)assign_near_kernel<MT, NT, FINAL>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    assign_near_kernel<MT, NT, FINAL><<<(p.ntot + 7) / 8 * 8, AS_THREADS, lds, r.st>>>(r.W, order, r.rounded, r.cn, r.V, r.d, r.C, p.CT, p.ncol, p.ntot, r.left, r.nrm, r.words, r.win);
+    CSV_LAUNCH_CHECK("assign_near_kernel");
+    return CSV_OK;
+}
+static int round_centroids(const AssignPlan& p, const AssignRun& r, int unit) {
+    round_centroids_kernel<<<p.CT, 1024, 0, r.st>>>(r.mu, r.d, r.C, p.CT, (r.d + 63) / 64 * 2, unit, r.rounded, r.cn, r.left, r.counts);
+    CSV_LAUNCH_CHECK("round_centroids_kernel");
+    return CSV_OK;
+}
+static int assign_exact(const AssignPlan& p, const AssignRun& r, int unit) {
+    centroid_norm_kernel<<<r.C, 256, 0, r.st>>>(r.mu, r.d, unit, r.cn);
+    CSV_LAUNCH_CHECK("centroid_norm_kernel");
+    const int nkb = (r.d + 31) / 32;
+    split_centroids_kernel<<<dim3(p.CT, (nkb + 3) / 4), 256, 0, r.st>>>(r.mu, r.d, r.C, p.CT, nkb, nullptr, r.pieces);
+    CSV_LAUNCH_CHECK("split_centroids_kernel");
+    return p.kind == 0 ? launch_exact<8, 4, false>(p, r) : p.kind == 1 ? launch_exact<4, 4, false>(p, r) : launch_exact<4, 2, false>(p, r);
+}
+// the first assignment: the centroids are rows of W
+static int assign_first(const AssignPlan& p, const AssignRun& r) {
+    const int rc = round_centroids(p, r, 0);
+    if (rc) return rc;
+    return p.kind == 0 ? launch_near<8, 4, true>(p, r, nullptr) : p.kind == 1 ? launch_near<4, 4, true>(p, r, nullptr) : launch_near<4, 2, true>(p, r, nullptr);
+}
+// order: the rows by the clusters so far.  give_up: looked at once the rounded scores are in, at the cost of a wait; set, and no labels made, where they
+// leave so many rows for the exact product that it is cheaper over all rows.
+static int assign_near(const AssignPlan& p, const AssignRun& r, int unit, const int32_t* order, bool* give_up) {
+    int rc = round_centroids(p, r, unit);
+    if (rc) return rc;
+    rc = p.kind == 0 ? launch_near<8, 4, false>(p, r, order) : launch_near<4, 4, false>(p, r, order);
+    if (rc) return rc;
+    assign_pick_kernel<<<(r.V + 63) / 64, 256, 0, r.st>>>(order, r.cn, r.left, r.nrm, r.words, p.ncol * 4, p.nt * 16, r.V, r.C, r.cap, r.labels, r.counts, r.rows,
+                                                          r.win, r.pairs, r.list);
+    CSV_LAUNCH_CHECK("assign_pick_kernel");
+    if (give_up) {
+        int n[3] = {0, 0, 0};
+        CSV_HIP(hipMemcpyAsync(n, r.counts, 12, hipMemcpyDeviceToHost, r.st));
+        CSV_HIP(hipStreamSynchronize(r.st));
+        // in passes of the exact product over all rows: the rounded scores and the look through them; 30 us of launches; a pair takes as long as 100
+        // columns of a row; listed rows go through smaller tiles
+        const double work = (double)r.V * r.d * r.C;
+        *give_up = 0.4 + 6.5e9 / work + 100.0 * std::min(n[1], r.cap) / ((double)r.V * r.C) + 1.15 * n[2] / r.V > 0.85;
+        if (*give_up) return CSV_OK;
+    }
+    assign_pairs_kernel<<<1024, 256, 0, r.st>>>(r.W, r.mu, r.cn, r.d, r.cap, r.counts, r.pairs, r.rows, r.win);
+    CSV_LAUNCH_CHECK("assign_pairs_kernel");
+    const int nkb = (r.d + 31) / 32, ncol = (r.C + 255) / 256;
+    const AssignPlan all = {1, 4, ncol, ncol * 16, (r.V + 127) / 128 * ncol};
+    split_centroids_kernel<<<dim3(all.CT, (nkb + 3) / 4), 256, 0, r.st>>>(r.mu, r.d, r.C, all.CT, nkb, r.counts + 2, r.pieces);
+    CSV_LAUNCH_CHECK("split_centroids_kernel");
+    return launch_exact<4, 4, true>(all, r);
 }
 
 extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int d, int C, const csv_build_opts* o,
@@ -942,11 +1484,14 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
     rc = csv_index_alloc(V, d, C, &x);
     if (rc) return rc;
     // One scratch allocation for the whole build: labels, the layout's counts and chunk list, partial centroid sums, the
-    // assignment's pieces, candidates and norms, squared distances; for spherical clustering row norms and sums of unit rows.
+    // assignment's pieces, words, lists and norms, squared distances; for spherical clustering row norms and sums of unit rows.
     const int sph = o->spherical != 0, bt_m = o->bias_table_m >= 2 ? o->bias_table_m : 0;
     const bool assigns = !o->h_init_labels || o->iters > 0;
     const int nkb = (d + 31) / 32, nw = (V + LAY_TOKENS - 1) / LAY_TOKENS, max_chunks = V / CHUNK_ROWS + C;
-    const AssignPlan ap = assign_plan(V, C);
+    // first: the centroids are rows of W and one bf16 piece is exact; may_near: the centroids rounded come first
+    const bool first = !o->h_init_labels && !o->spherical, may_near = o->iters > 0 && assign_near_pays(V, d, C);
+    const AssignPlan fp = assign_plan(V, C, true, may_near ? 2 : 3), ap = assign_plan(V, C, false);
+    bool near = may_near;                // until an assignment shows that most rows are out of its reach
     char* arena = nullptr;
     size_t used = 0;
     auto take = [&](size_t bytes) {
@@ -971,12 +1516,16 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
                 if (rows[c] > CHUNK_ROWS) part_slots += (rows[c] + CHUNK_ROWS - 1) / CHUNK_ROWS;
         }
     }
-    const size_t part_bytes = part_slots * d * 8, piece_bytes = assigns ? (size_t)nkb * ap.CT * 192 * sizeof(uint4) : 0;
+    const size_t part_bytes = part_slots * d * 8, piece_tiles = assigns ? std::max(ap.CT, (C + 255) / 256 * 16) : 0,
+                 piece_bytes = (size_t)nkb * piece_tiles * 192 * sizeof(uint4), near_rows = near ? V : 0;
+    const int pair_cap = near ? (int)std::min(std::min((long long)V * AS_PAIRS_SHARE, (long long)V * C / 512), (long long)INT32_MAX / 2) : 0;
     const size_t o_labels = take((size_t)V * 4), o_hist = take((size_t)nw * C * 4), o_coff = take((size_t)(C + 1) * 4), o_poff = take((size_t)C * 4), o_chunks = take((size_t)max_chunks * sizeof(int2)),
                  o_both = take(part_bytes > piece_bytes ? part_bytes : piece_bytes),
-                 o_cand = take(assigns ? (size_t)V * ap.ncol * 8 : 0), o_cn = take((size_t)C * 4), o_d2max = take((size_t)C * 8),
-                 o_d2row = take(bt_m ? (size_t)V * 8 : 0), o_nrm = take(sph ? (size_t)V * 8 : 0), o_sums = take(sph ? (size_t)C * d * 8 : 0),
-                 o_ext = take(sph ? (size_t)3 * C * 8 : 0);
+                 o_win = take(assigns ? (size_t)V * std::max(fp.ncol, ap.ncol) * 8 : 0), o_cn = take((size_t)C * 4), o_d2max = take((size_t)C * 8),
+                 o_d2row = take(bt_m ? (size_t)V * 8 : 0), o_nrm = take(sph ? (size_t)V * 8 : near_rows * 8), o_sums = take(sph ? (size_t)C * d * 8 : 0),
+                 o_ext = take(sph ? (size_t)3 * C * 8 : 0), o_rounded = take(first || near ? (size_t)(d + 63) / 64 * 2 * fp.CT * 64 * sizeof(as_uintx4_t) : 0),
+                 o_left = take((size_t)C * 4), o_words = take(near_rows * fp.ncol * 48), o_counts = take(256), o_rows = take(near_rows * 4),
+                 o_list = take(near_rows * 4), o_pairs = take((size_t)pair_cap * sizeof(int2));
     auto fail = [&](int code) {
         if (arena) {
             (void)hipStreamSynchronize(st);
@@ -990,23 +1539,15 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
     int32_t *d_labels = (int32_t*)(arena + o_labels), *d_hist = (int32_t*)(arena + o_hist), *d_coff = (int32_t*)(arena + o_coff), *d_poff = (int32_t*)(arena + o_poff);
     int2* d_chunks = (int2*)(arena + o_chunks);
     double *d_part = (double*)(arena + o_both), *d_nrm = (double*)(arena + o_nrm), *d_sums = (double*)(arena + o_sums), *d_d2row = bt_m ? (double*)(arena + o_d2row) : nullptr;
-    uint4* d_pieces = (uint4*)(arena + o_both);
-    float* d_cn = (float*)(arena + o_cn);
-    unsigned long long *d_cand = (unsigned long long*)(arena + o_cand), *d_d2max = (unsigned long long*)(arena + o_d2max), *d_ext = (unsigned long long*)(arena + o_ext);
-    if (sph) {
+    unsigned long long *d_win = (unsigned long long*)(arena + o_win), *d_d2max = (unsigned long long*)(arena + o_d2max), *d_ext = (unsigned long long*)(arena + o_ext);
+    if (sph || (near && !first)) {
         row_norm_kernel<<<(V + 3) / 4, 256, 0, st>>>(d_W, V, d, d_nrm);
         if (hipGetLastError() != hipSuccess) { csv_set_error("launch of row_norm_kernel failed"); return fail(CSV_EHIP); }
     }
-    auto assign = [&]() -> int {
-        centroid_norm_kernel<<<C, 256, 0, st>>>(x->mu, d, sph, d_cn);
-        CSV_LAUNCH_CHECK("centroid_norm_kernel");
-        split_centroids_kernel<<<dim3(ap.CT, (nkb + 3) / 4), 256, 0, st>>>(x->mu, d, C, ap.CT, nkb, d_pieces);
-        CSV_LAUNCH_CHECK("split_centroids_kernel");
-        return ap.mt == 8 ? launch_assign<8, 4>(ap, d_W, d_pieces, d_cn, V, d, C, d_cand, st)
-             : ap.nt == 4 ? launch_assign<4, 4>(ap, d_W, d_pieces, d_cn, V, d, C, d_cand, st)
-                          : launch_assign<4, 2>(ap, d_W, d_pieces, d_cn, V, d, C, d_cand, st);
-    };
-    bool assigned = false;               // the labels are the assignment's candidates (else: the caller's)
+    const AssignRun run = {d_W, x->mu, (float*)(arena + o_cn), V, d, C, (uint4*)(arena + o_both), d_win, (as_uintx4_t*)(arena + o_rounded), (float*)(arena + o_left),
+                           near || sph ? d_nrm : nullptr, (unsigned*)(arena + o_words), (int*)(arena + o_counts), (int*)(arena + o_rows), (int*)(arena + o_list), pair_cap,
+                           (int2*)(arena + o_pairs), d_labels, st};
+    int made = 0;                        // column blocks whose best words the labels come from (0: they are there already)
     std::vector<int32_t> seed;
     if (o->h_init_labels) {
         if (hipMemcpyAsync(d_labels, o->h_init_labels, (size_t)V * 4, hipMemcpyHostToDevice, st) != hipSuccess) { csv_set_error("copy of the labels failed"); return fail(CSV_EHIP); }
@@ -1020,14 +1561,14 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
         if (hipMemcpyAsync(x->n, seed.data(), (size_t)C * 4, hipMemcpyHostToDevice, st) != hipSuccess) { csv_set_error("copy of init rows failed"); return fail(CSV_EHIP); }
         if (sph) init_direction_kernel<<<C, 256, 0, st>>>(d_W, x->n, d_nrm, d, x->mu);
         else init_centroid_kernel<<<C, 256, 0, st>>>(d_W, x->n, d, x->mu);
-        if ((rc = assign())) return fail(rc);
-        assigned = true;
+        if ((rc = first ? assign_first(fp, run) : assign_exact(ap, run, sph))) return fail(rc);
+        made = first ? fp.ncol : ap.ncol;
     }
     int label_bits = 1;
     while ((1 << label_bits) < C) ++label_bits;
     for (int it = 0;; ++it) {
         const bool last = it == o->iters;
-        label_hist_kernel<<<nw, 64, (size_t)C * 4, st>>>(assigned ? d_cand : nullptr, ap.ncol, d_labels, V, C, d_hist);
+        label_hist_kernel<<<nw, 64, (size_t)C * 4, st>>>(made ? d_win : nullptr, made, d_win, d_labels, V, C, d_hist);
         layout_scan_kernel<<<(C + 63) / 64, 512, 0, st>>>(d_hist, nw, C, x->n);
         layout_offsets_kernel<<<1, 1024, 0, st>>>(x->n, C, x->off, d_coff, d_poff, d_chunks);
         layout_scatter_kernel<<<nw, 64, (size_t)C * 4, st>>>(d_labels, d_hist, x->off, V, C, label_bits, x->perm);
@@ -1042,8 +1583,11 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
         }
         if (hipGetLastError() != hipSuccess) { csv_set_error("launch of the centroid kernels failed"); return fail(CSV_EHIP); }
         if (last) break;
-        if ((rc = assign())) return fail(rc);
-        assigned = true;
+        bool give_up = false;
+        if (near && (rc = assign_near(fp, run, sph, x->perm, it == 0 ? &give_up : nullptr))) return fail(rc);
+        near = near && !give_up;
+        if (!near && (rc = assign_exact(ap, run, sph))) return fail(rc);
+        made = near ? 0 : ap.ncol;
     }
     if (o->centroid_bf16 && (rc = store_centroids_bf16(x, 0, st))) return fail(rc);
     if (bt_m && hipMalloc((void**)&x->bt, (size_t)C * bt_m * sizeof(float2)) != hipSuccess) { csv_set_error("out of device memory (bias table)"); return fail(CSV_ENOMEM); }

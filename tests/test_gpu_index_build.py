@@ -100,3 +100,104 @@ def test_partial_centroid_sums_fit_their_slots(sizes, iters):
     if min(sizes) or not iters:                  # (an empty cluster has no planted centre to be found again)
         _same_metadata(g.export(), O.build_index(W, b, labels, C))
     g.free()
+
+
+def _labels(e):
+    labels = np.empty(e["perm"].size, np.int64)
+    labels[e["perm"]] = np.repeat(np.arange(e["n"].size), e["n"])
+    return labels
+
+
+def _nearest(W, mu, labels, tol):
+    """Every row's label is a nearest centroid of mu in float64, up to tol * ||row|| * largest ||mu_c|| of score."""
+    W, mu, n = W.double(), torch.from_numpy(mu).cuda().double(), torch.from_numpy(labels).cuda()
+    d2 = (mu * mu).sum(1) - 2.0 * W @ mu.T
+    over = d2.gather(1, n[:, None])[:, 0] - d2.min(1).values
+    assert (over <= tol * W.norm(dim=1) * mu.norm(dim=1).max()).all(), over.max().item()
+
+
+# Heads large enough for the rounded centroids to come first (384 clusters, V d C of 20e9): 256 x 256 and 128 x 256 tiles, d a multiple of 64 and
+# not, V and C inside a tile.  "shared": a planted centre's rows are dealt to one to three clusters, whose centroids then differ in the noise, and some clusters
+# hold two centres (pairs); "crowd": one centre's rows are dealt to 90 clusters besides (whole groups and rows for all centroids); "alike": all rows
+# equal (given up: every score ties, the smallest id wins).  Two scores that float32 sums of exact products can tell apart are told apart right: a sum's error
+# is at most (d / 8 + 16) 2^-24 ||row|| ||mu||, 2^-15 at d = 4096; a third of that at the most has been seen.
+@pytest.mark.parametrize("V,d,C,spherical", [(70001, 264, 1200, False), (70001, 264, 1200, True), (16000, 3200, 400, False), (45003, 1096, 500, False)])
+@pytest.mark.parametrize("kind", ["shared", "crowd", "alike"])
+def test_rounded_centroids_find_the_nearest(V, d, C, kind, spherical):
+    import paper_2511_21702_amd as csv
+    assert C >= 384 and V * d * C >= 20e9                      # assign_near_pays of the library
+    gen = torch.Generator(device="cuda").manual_seed(V + d)
+    rng = np.random.default_rng(V)
+    centers = torch.randn(C, d, device="cuda", generator=gen) * (4.0 / d ** 0.5)
+    labels = rng.integers(0, C, V).astype(np.int32)
+    labels[:C] = np.arange(C)
+    centre = labels // 3 * 3 if kind != "alike" else labels * 0
+    centre = np.where((labels % 7 == 0) & (rng.random(V) < 0.5), (labels + C // 2) % C, centre)
+    if kind == "crowd":
+        centre = np.where(labels < 90, 5, centre)
+    W = centers[torch.from_numpy(centre).cuda().long()]
+    if kind != "alike":
+        W = W + torch.randn(V, d, device="cuda", generator=gen) * (0.05 / d ** 0.5)
+    else:
+        W = W[:1].expand(V, d)
+    W = W.to(torch.bfloat16).contiguous()
+    log(f"rounded centroids V={V} d={d} C={C} {kind} spherical={spherical}")
+    tol = 2.0 * (d / 8 + 16) * 2.0 ** -24
+    g0 = csv.csv_build_index(W, None, C, init_labels=labels, iters=0, spherical=spherical)
+    mu = g0.export()["mu"]
+    g0.free()
+    for iters in (1, 2):
+        g = csv.csv_build_index(W, None, C, init_labels=labels, iters=iters, spherical=spherical)
+        e = g.export()
+        g.free()
+        got = _labels(e)
+        if kind == "alike":
+            assert (got == 0).all()
+            break
+        if spherical:                                            # largest cosine: every direction counts as of length one
+            m = torch.from_numpy(mu).cuda().double()
+            dots = W.double() @ m.T
+            over = dots.max(1).values - dots.gather(1, torch.from_numpy(got).cuda()[:, None])[:, 0]
+            assert (over <= tol * W.double().norm(dim=1)).all(), over.max().item()
+        else:
+            _nearest(W, mu, got, tol)
+        if (e["n"] == 0).any():                                  # an empty cluster keeps a centroid that the export does not show
+            break
+        mu = e["mu"]
+
+
+# The same from seed rows: the first assignment's centroids are bf16 values and need no second look, the second's norms come from it.  A row with an infinity
+# and one with a NaN get some label and disturb no other row's.
+def test_first_assignment_from_rows_then_rounded_centroids():
+    import paper_2511_21702_amd as csv
+    V, d, C = 70001, 264, 1200
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    W = (torch.randn(C, d, device="cuda", generator=gen)[torch.arange(V, device="cuda") % C] * (4.0 / d ** 0.5)
+         + torch.randn(V, d, device="cuda", generator=gen) * (2.0 / d ** 0.5)).to(torch.bfloat16)
+    first = np.arange(C, dtype=np.int32)
+    log("first assignment from rows")
+    tol, mu, want = 2.0 * (d / 8 + 16) * 2.0 ** -24, W[:C].float().cpu().numpy(), None
+    for iters in (0, 1, 2):
+        g = csv.csv_build_index(W, None, C, init_rows=first, iters=iters)
+        e = g.export()
+        g.free()
+        want = _labels(e)
+        _nearest(W, mu, want, tol)
+        assert e["n"].min() > 0
+        mu = e["mu"]
+    W2 = W.clone()
+    W2[60000, 5] = float("inf")
+    W2[60001, 263] = float("nan")
+    g = csv.csv_build_index(W2, None, C, init_rows=first, iters=0)
+    once = _labels(g.export())
+    g.free()
+    g = csv.csv_build_index(W, None, C, init_rows=first, iters=0)
+    clean = _labels(g.export())
+    g.free()
+    keep = np.ones(V, bool)
+    keep[60000:60002] = False
+    assert np.array_equal(once[keep], clean[keep])
+    g = csv.csv_build_index(W2, None, C, init_rows=first, iters=2)
+    e = g.export()
+    g.free()
+    assert sorted(e["perm"].tolist()) == list(range(V)) and e["n"].sum() == V
