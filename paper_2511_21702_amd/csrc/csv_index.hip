@@ -1483,8 +1483,8 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
     csv_index* x = nullptr;
     rc = csv_index_alloc(V, d, C, &x);
     if (rc) return rc;
-    // One scratch allocation for the whole build: labels, the layout's counts and chunk list, partial centroid sums, the
-    // assignment's pieces, words, lists and norms, squared distances; for spherical clustering row norms and sums of unit rows.
+    // One scratch allocation for the whole build: labels, the layout's counts and chunk list, norms, squared distances; for spherical clustering
+    // sums of unit rows.
     const int sph = o->spherical != 0, bt_m = o->bias_table_m >= 2 ? o->bias_table_m : 0;
     const bool assigns = !o->h_init_labels || o->iters > 0;
     const int nkb = (d + 31) / 32, nw = (V + LAY_TOKENS - 1) / LAY_TOKENS, max_chunks = V / CHUNK_ROWS + C;
@@ -1499,9 +1499,9 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
         used += (bytes + 255) / 256 * 256;
         return at;
     };
-    // Partial centroid sums and the assignment's pieces are never live together: they share their bytes.  Given labels that stay say
-    // how many partial sums there are, mostly none (V = 32000, d = 1024, 256 clusters: 4 MB less to allocate and to give back;
-    // build and csv_index_free 0.24 + 0.30 ms, now 0.18 + 0.04; before the build moved to the device 0.23 + 0.03).
+    // Partial centroid sums and what an assignment needs (pieces, words, lists) are never live together: they share their bytes, and those are the
+    // index's own copy of W, which is written last, wherever they fit into it (an allocation of 64 MB or more takes 30 us to get and 225 us to give back).
+    // Given labels that stay say how many partial sums there are.
     size_t part_slots = PART_SLOTS(V) < max_chunks ? PART_SLOTS(V) : max_chunks;
     if (o->h_init_labels) {
         std::vector<int32_t> rows(C, 0);
@@ -1519,13 +1519,20 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
     const size_t part_bytes = part_slots * d * 8, piece_tiles = assigns ? std::max(ap.CT, (C + 255) / 256 * 16) : 0,
                  piece_bytes = (size_t)nkb * piece_tiles * 192 * sizeof(uint4), near_rows = near ? V : 0;
     const int pair_cap = near ? (int)std::min(std::min((long long)V * AS_PAIRS_SHARE, (long long)V * C / 512), (long long)INT32_MAX / 2) : 0;
+    size_t assign_bytes = 0;
+    auto share = [&](size_t bytes) {
+        const size_t at = assign_bytes;
+        assign_bytes += (bytes + 255) / 256 * 256;
+        return at;
+    };
+    const size_t a_pieces = share(piece_bytes), a_rounded = share(first || near ? (size_t)(d + 63) / 64 * 2 * fp.CT * 64 * sizeof(as_uintx4_t) : 0),
+                 a_win = share(assigns ? (size_t)V * std::max(fp.ncol, ap.ncol) * 8 : 0), a_words = share(near_rows * fp.ncol * 48), a_rows = share(near_rows * 4),
+                 a_list = share(near_rows * 4), a_pairs = share((size_t)pair_cap * sizeof(int2)), shared_bytes = std::max(part_bytes, assign_bytes);
+    const bool in_copy = shared_bytes <= (size_t)V * d * 2;
     const size_t o_labels = take((size_t)V * 4), o_hist = take((size_t)nw * C * 4), o_coff = take((size_t)(C + 1) * 4), o_poff = take((size_t)C * 4), o_chunks = take((size_t)max_chunks * sizeof(int2)),
-                 o_both = take(part_bytes > piece_bytes ? part_bytes : piece_bytes),
-                 o_win = take(assigns ? (size_t)V * std::max(fp.ncol, ap.ncol) * 8 : 0), o_cn = take((size_t)C * 4), o_d2max = take((size_t)C * 8),
+                 o_shared = take(in_copy ? 0 : shared_bytes), o_cn = take((size_t)C * 4), o_left = take((size_t)C * 4), o_counts = take(256), o_d2max = take((size_t)C * 8),
                  o_d2row = take(bt_m ? (size_t)V * 8 : 0), o_nrm = take(sph ? (size_t)V * 8 : near_rows * 8), o_sums = take(sph ? (size_t)C * d * 8 : 0),
-                 o_ext = take(sph ? (size_t)3 * C * 8 : 0), o_rounded = take(first || near ? (size_t)(d + 63) / 64 * 2 * fp.CT * 64 * sizeof(as_uintx4_t) : 0),
-                 o_left = take((size_t)C * 4), o_words = take(near_rows * fp.ncol * 48), o_counts = take(256), o_rows = take(near_rows * 4),
-                 o_list = take(near_rows * 4), o_pairs = take((size_t)pair_cap * sizeof(int2));
+                 o_ext = take(sph ? (size_t)3 * C * 8 : 0);
     auto fail = [&](int code) {
         if (arena) {
             (void)hipStreamSynchronize(st);
@@ -1538,15 +1545,16 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
     if (hipMalloc((void**)&arena, used) != hipSuccess) { csv_set_error("out of device memory (index build scratch, %zu bytes)", used); return fail(CSV_ENOMEM); }
     int32_t *d_labels = (int32_t*)(arena + o_labels), *d_hist = (int32_t*)(arena + o_hist), *d_coff = (int32_t*)(arena + o_coff), *d_poff = (int32_t*)(arena + o_poff);
     int2* d_chunks = (int2*)(arena + o_chunks);
-    double *d_part = (double*)(arena + o_both), *d_nrm = (double*)(arena + o_nrm), *d_sums = (double*)(arena + o_sums), *d_d2row = bt_m ? (double*)(arena + o_d2row) : nullptr;
-    unsigned long long *d_win = (unsigned long long*)(arena + o_win), *d_d2max = (unsigned long long*)(arena + o_d2max), *d_ext = (unsigned long long*)(arena + o_ext);
+    char* shared = in_copy ? (char*)x->Wp : arena + o_shared;
+    double *d_part = (double*)shared, *d_nrm = (double*)(arena + o_nrm), *d_sums = (double*)(arena + o_sums), *d_d2row = bt_m ? (double*)(arena + o_d2row) : nullptr;
+    unsigned long long *d_win = (unsigned long long*)(shared + a_win), *d_d2max = (unsigned long long*)(arena + o_d2max), *d_ext = (unsigned long long*)(arena + o_ext);
     if (sph || (near && !first)) {
         row_norm_kernel<<<(V + 3) / 4, 256, 0, st>>>(d_W, V, d, d_nrm);
         if (hipGetLastError() != hipSuccess) { csv_set_error("launch of row_norm_kernel failed"); return fail(CSV_EHIP); }
     }
-    const AssignRun run = {d_W, x->mu, (float*)(arena + o_cn), V, d, C, (uint4*)(arena + o_both), d_win, (as_uintx4_t*)(arena + o_rounded), (float*)(arena + o_left),
-                           near || sph ? d_nrm : nullptr, (unsigned*)(arena + o_words), (int*)(arena + o_counts), (int*)(arena + o_rows), (int*)(arena + o_list), pair_cap,
-                           (int2*)(arena + o_pairs), d_labels, st};
+    const AssignRun run = {d_W, x->mu, (float*)(arena + o_cn), V, d, C, (uint4*)(shared + a_pieces), d_win, (as_uintx4_t*)(shared + a_rounded), (float*)(arena + o_left),
+                           near || sph ? d_nrm : nullptr, (unsigned*)(shared + a_words), (int*)(arena + o_counts), (int*)(shared + a_rows), (int*)(shared + a_list), pair_cap,
+                           (int2*)(shared + a_pairs), d_labels, st};
     int made = 0;                        // column blocks whose best words the labels come from (0: they are there already)
     std::vector<int32_t> seed;
     if (o->h_init_labels) {
