@@ -1,7 +1,7 @@
 // Per-step kernels of the certified sub-vocabulary LM-head path and the entry points that enqueue them.
 //
-//   bound1_kernel / bound_kernel / bound_mfma_kernel + bound_finish_kernel
-//                      U[b,c] = <mu_c,h_b> + R_c ||h_b|| + bmax_c  for 1, 2..4 and more sequences   (Eq. "cluster_bound")
+//   bound_rows_kernel, bound_kernel / bound_mfma_kernel + bound_finish_kernel
+//                      U[b,c] = <mu_c,h_b> + R_c ||h_b|| + bmax_c  for up to four / more sequences   (Eq. "cluster_bound")
 //   round0_kernel      per sequence: shortest prefix of the bound order holding >= max(k,1) rows, next bound, log tail
 //                      mass (Algorithm 1: queue, PopMax); logits of the prefix rows of W' (Algorithm 1: sparse GEMV);
 //                      top-k, log-sum-exp and both certificates, or the plan of the next round
@@ -149,12 +149,6 @@ __device__ __forceinline__ float bound_value(const StepArgs& a, int c, float dot
     return dot + best;
 }
 
-// Block = 8 waves = 8/WPC clusters x WPC column slices (WPC = 1, 2 or 4, chosen so that a wave's slice of the
-// centroid row is at most 8 KB = one batch of eight 128-bit loads per lane), BT sequences per block.
-// Order of requests matters: a wave's loads return in order, so h (needed first, to fill LDS and for ||h||) is
-// requested before the centroid slice, and the slice is in flight while h is staged and the norms are taken.
-// Blocks are dealt round-robin to the 8 XCDs, so group g = (block % 8) * groups_per_xcd + block / 8 keeps
-// every XCD on the same centroid slice step after step.
 #define BOUND_PF 8
 // A "unit" is one 128-bit load of a centroid row: four float32 values, or eight bfloat16 values when the index
 // stores its centroids rounded (MU16).  The matching piece of h is 8 resp. 16 bytes of bf16.
@@ -180,9 +174,9 @@ __device__ __forceinline__ float mu_fma(const uint4& m, HP hrow, int unit, float
     }
 }
 #define BOUND_THREADS 512
-#define BOUND_LDS_MAX (128 * 1024)   // h of up to 8 sequences of d = 8192 in LDS: one block serves all 8, the centroids are read once
+#define BOUND_LDS_MAX (128 * 1024)   // most LDS for the h of four sequences
 #define BOUND_HREG 8       // 128-bit pieces of h per thread: 8 x 512 x 16 B covers the 64 KB that BT sequences may take in LDS
-// 2..4 sequences: h of the block's BT sequences is staged in LDS once, then every wave walks over whole clusters
+// Three or four sequences, bf16 centroids: h of the sequences is staged in LDS once, then every wave walks over whole clusters
 // (cluster = wave index among all waves of the grid, then + their number, ...): a centroid row goes through the wave
 // in chunks of BOUND_PFB 128-bit loads per lane, the next chunk (of this or of the wave's next cluster) always
 // requested before the current one is used, and nothing in the loop waits for another wave.  With more clusters
@@ -190,14 +184,13 @@ __device__ __forceinline__ float mu_fma(const uint4& m, HP hrow, int unit, float
 #ifndef BOUND_PFB
 #define BOUND_PFB 16      // 128-bit loads per lane and chunk of a centroid row (two chunks in flight)
 #endif
-template <int BT, bool MU16>
-__global__ __launch_bounds__(BOUND_THREADS) void bound_kernel(StepArgs a, float* __restrict__ U_out, float* __restrict__ hn_out,
-                                                              int reset_counters) {
+__global__ __launch_bounds__(BOUND_THREADS) void bound_kernel(StepArgs a, float* __restrict__ U_out, float* __restrict__ hn_out, int reset_counters) {
+    constexpr int BT = 4;
+    constexpr bool MU16 = true;
     extern __shared__ uint4 hs4[];
     __shared__ float hn[BT];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int b0 = blockIdx.y * BT;
-    const int nb = min(BT, a.B - b0);
+    const int nb = min(BT, a.B);
     const int nch = a.d >> 3, nq = mu_units<MU16>(a.d), C = a.C;
     const int GW = gridDim.x * (BOUND_THREADS / 64);
     const int nchk = (nq + 64 * BOUND_PFB - 1) / (64 * BOUND_PFB);
@@ -213,7 +206,7 @@ __global__ __launch_bounds__(BOUND_THREADS) void bound_kernel(StepArgs a, float*
         }
     };
     issue(pfA, c, 0);                 // in flight while h is staged
-    const uint4* hsrc = reinterpret_cast<const uint4*>(a.h) + (size_t)b0 * nch;
+    const uint4* hsrc = reinterpret_cast<const uint4*>(a.h);
     for (int base = 0; base < BT * nch; base += BOUND_HREG * BOUND_THREADS) {
         uint4 hreg[BOUND_HREG];
 #pragma unroll
@@ -228,7 +221,7 @@ __global__ __launch_bounds__(BOUND_THREADS) void bound_kernel(StepArgs a, float*
             if (i < BT * nch) hs4[i] = hreg[q];
         }
     }
-    if (reset_counters && blockIdx.x == 0 && blockIdx.y == 0)
+    if (reset_counters && blockIdx.x == 0)
         reset_step_counters(a.counters, a.B, BOUND_THREADS, a.host_history, a.slots, a.B_max);
     __syncthreads();
     for (int s = wave; s < BT; s += BOUND_THREADS / 64) {
@@ -241,7 +234,7 @@ __global__ __launch_bounds__(BOUND_THREADS) void bound_kernel(StepArgs a, float*
         if (lane == 0) hn[s] = sqrtf(acc);
     }
     __syncthreads();
-    if (blockIdx.x == 0 && tid < nb && hn_out) hn_out[b0 + tid] = hn[tid];
+    if (blockIdx.x == 0 && tid < nb && hn_out) hn_out[tid] = hn[tid];
 
     float acc[BT];
 #pragma unroll
@@ -268,7 +261,7 @@ __global__ __launch_bounds__(BOUND_THREADS) void bound_kernel(StepArgs a, float*
 #pragma unroll
             for (int s = 0; s < BT; ++s) {
                 const float t = wave_sum(acc[s]);
-                if (lane == 0 && s < nb) U_out[(size_t)(b0 + s) * C + c] = ncl == 0 ? -INFINITY : bound_value(a, c, t, Rc, bm, hn[s]);
+                if (lane == 0 && s < nb) U_out[(size_t)s * C + c] = ncl == 0 ? -INFINITY : bound_value(a, c, t, Rc, bm, hn[s]);
                 acc[s] = 0.f;
             }
         }
@@ -282,14 +275,21 @@ __global__ __launch_bounds__(BOUND_THREADS) void bound_kernel(StepArgs a, float*
     }
 }
 
-// One sequence (B = 1): no LDS staging at all.  h is 2d bytes that every wave of the device reads, so it comes from
+// BT sequences (1..4).  Block = 8 waves = 8/WPC clusters x WPC column slices (WPC = 1, 2 or 4, chosen so that a wave's slice of the centroid row is one batch of
+// loads per lane, where four slices are enough).  Blocks are dealt round-robin to the 8 XCDs, so group g = (block % 8) * groups_per_xcd + block / 8 keeps
+// every XCD on the same centroid slice step after step.  No LDS staging at all:  h is 2d bytes a sequence that every wave of the device reads, so it comes from
 // L2 / L1 with the same addresses in every block; each wave takes its slice of h straight from global memory next to
 // its centroid slice, and ||h||^2 is the sum of the slices' partial sums of squares (slice order: the same value
 // in every block).
-template <bool MU16>
-__global__ __launch_bounds__(BOUND_THREADS) void bound1_kernel(StepArgs a, float* __restrict__ U_out, float* __restrict__ hn_out,
-                                                               int reset_counters, int groups, int groups_per_xcd, int wpc) {
-    __shared__ float part[BOUND_THREADS / 64], parth[BOUND_THREADS / 64];
+// Units of a centroid row a lane has requested at once: with more than two sequences four, which leaves registers for four sequences' pieces of h for them and for
+// five waves per SIMD (us with four / eight: B = 3, C = 4096, d = 4608 15.5 / 20.9; B = 4, C = 2048, d = 5120 11.6 / 14.0, C = 1024, d = 4096 6.0 / 6.3).
+// Walking over whole clusters with h in LDS took B = 2..4 at C = 1024, d = 4096 6.1 / 7.0 / 7.1 us, this 5.1 / 5.4 / 6.0, at C = 601, d = 2056 (3) 6.9, now 5.1.
+#define BOUND_ROWS_PF(BT) ((BT) > 2 ? 4 : BOUND_PF)
+template <int BT, bool MU16>
+__global__ __launch_bounds__(BOUND_THREADS) void bound_rows_kernel(StepArgs a, float* __restrict__ U_out, float* __restrict__ hn_out,
+                                                                   int reset_counters, int groups, int groups_per_xcd, int wpc) {
+    constexpr int PF = BOUND_ROWS_PF(BT);
+    __shared__ float part[BT][BOUND_THREADS / 64], parth[BT][BOUND_THREADS / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nq = mu_units<MU16>(a.d);
     const int cpb = (BOUND_THREADS / 64) / wpc, cl = wave / wpc, slice = wave - cl * wpc;
@@ -300,60 +300,70 @@ __global__ __launch_bounds__(BOUND_THREADS) void bound1_kernel(StepArgs a, float
     const uint4* mrow = mu_row<MU16>(a, valid ? c : 0);
     typedef typename std::conditional<MU16, uint4, uint2>::type hpiece;   // the piece of h that goes with one unit
     const hpiece* hp = reinterpret_cast<const hpiece*>(a.h);
-    uint4 pf[BOUND_PF];
-    hpiece ph[BOUND_PF];
+    uint4 pf[PF];
+    hpiece ph[BT][PF];
 #pragma unroll
-    for (int j = 0; j < BOUND_PF; ++j) {
+    for (int j = 0; j < PF; ++j) {
         const int i = lo + lane + 64 * j;
         pf[j] = (valid && i < hi) ? mrow[i] : make_uint4(0, 0, 0, 0);
     }
 #pragma unroll
-    for (int j = 0; j < BOUND_PF; ++j) {
-        const int i = lo + lane + 64 * j;
-        ph[j] = i < hi ? hp[i] : hpiece{};
-    }
+    for (int s = 0; s < BT; ++s)
+#pragma unroll
+        for (int j = 0; j < PF; ++j) {
+            const int i = lo + lane + 64 * j;
+            ph[s][j] = i < hi ? hp[(size_t)s * nq + i] : hpiece{};
+        }
     float Rc = 0.f, bm = 0.f;
     int ncl = 0;
-    if (valid && slice == 0 && lane == 0) {
+    if (valid && slice == 0 && lane < BT) {
         Rc = a.R[c];
         bm = a.bmax[c];
         ncl = a.n[c];
     }
     if (reset_counters && blockIdx.x == 0)
         reset_step_counters(a.counters, a.B, BOUND_THREADS, a.host_history, a.slots, a.B_max);
-    float acc = 0.f, hh = 0.f;
-    auto step = [&](const uint4& m, const hpiece& hv) {
-        acc = mu_fma<MU16>(m, &hv, 0, acc);
+    float acc[BT], hh[BT];
+#pragma unroll
+    for (int s = 0; s < BT; ++s) acc[s] = hh[s] = 0.f;
+    auto step = [&](int s, const uint4& m, const hpiece& hv) {
+        acc[s] = mu_fma<MU16>(m, &hv, 0, acc[s]);
         const uint32_t* w = reinterpret_cast<const uint32_t*>(&hv);
 #pragma unroll
         for (int e = 0; e < (int)(sizeof(hpiece) / 4); ++e) {
-            hh = fmaf(bf16_lo(w[e]), bf16_lo(w[e]), hh);
-            hh = fmaf(bf16_hi(w[e]), bf16_hi(w[e]), hh);
+            hh[s] = fmaf(bf16_lo(w[e]), bf16_lo(w[e]), hh[s]);
+            hh[s] = fmaf(bf16_hi(w[e]), bf16_hi(w[e]), hh[s]);
         }
     };
 #pragma unroll
-    for (int j = 0; j < BOUND_PF; ++j) step(pf[j], ph[j]);
+    for (int j = 0; j < PF; ++j)
+#pragma unroll
+        for (int s = 0; s < BT; ++s) step(s, pf[j], ph[s][j]);
 #pragma unroll 4
-    for (int i = lo + lane + 64 * BOUND_PF; i < hi; i += 64) {
+    for (int i = lo + lane + 64 * PF; i < hi; i += 64) {
         const uint4 m = valid ? mrow[i] : make_uint4(0, 0, 0, 0);
-        step(m, hp[i]);
+#pragma unroll
+        for (int s = 0; s < BT; ++s) step(s, m, hp[(size_t)s * nq + i]);
     }
-    acc = wave_sum(acc);
-    hh = wave_sum(hh);
-    if (lane == 0) {
-        part[wave] = acc;
-        parth[wave] = hh;
+#pragma unroll
+    for (int s = 0; s < BT; ++s) {
+        acc[s] = wave_sum(acc[s]);
+        hh[s] = wave_sum(hh[s]);
+        if (lane == 0) {
+            part[s][wave] = acc[s];
+            parth[s][wave] = hh[s];
+        }
     }
     __syncthreads();
-    if (slice == 0 && lane == 0) {
-        float t = part[wave], th = parth[wave];
+    if (slice == 0 && lane < BT) {                           // lane s finishes sequence s
+        float t = part[lane][wave], th = parth[lane][wave];
         for (int q = 1; q < wpc; ++q) {
-            t += part[wave + q];
-            th += parth[wave + q];
+            t += part[lane][wave + q];
+            th += parth[lane][wave + q];
         }
         const float hn = sqrtf(th);
-        if (blockIdx.x == 0 && wave == 0 && hn_out) hn_out[0] = hn;
-        if (valid) U_out[c] = ncl == 0 ? -INFINITY : bound_value(a, c, t, Rc, bm, hn);
+        if (blockIdx.x == 0 && wave == 0 && hn_out) hn_out[lane] = hn;
+        if (valid) U_out[(size_t)lane * a.C + c] = ncl == 0 ? -INFINITY : bound_value(a, c, t, Rc, bm, hn);
     }
 }
 
@@ -3298,7 +3308,7 @@ static int check_pair(const csv_workspace* ws, const csv_index* idx, const void*
 
 // The dynamic-LDS limit of a kernel is one attribute per process and device, shared by every workspace: it is only
 // ever raised, so a workspace created later with smaller needs cannot take away what an earlier one's launches rely on.
-enum { K_ROUND0, K_ROUND0_THRESH, K_ROUND0_PLANS, K_STEP, K_STEP_MANY, K_TAIL, K_RCERT, K_FBPROD, K_FBPRODM /* + levels */, K_FULLMFMA = K_FBPRODM + 4 /* + levels */, K_ALG1 = K_FULLMFMA + 4, K_BOUND0, K_NKERN = K_BOUND0 + 8 };
+enum { K_ROUND0, K_ROUND0_THRESH, K_ROUND0_PLANS, K_STEP, K_STEP_MANY, K_TAIL, K_RCERT, K_FBPROD, K_FBPRODM /* + levels */, K_FULLMFMA = K_FBPRODM + 4 /* + levels */, K_ALG1 = K_FULLMFMA + 4, K_BOUND, K_NKERN };
 static size_t g_lds_limit[CSV_STATIC_MAX_DEVICES][K_NKERN];
 static pthread_mutex_t g_attr_lock = PTHREAD_MUTEX_INITIALIZER;
 #define CSV_STATIC_LDS_MAX 16384     // at least the static shared memory of any kernel here
@@ -3352,54 +3362,45 @@ static int launch_bounds_kernel(const StepArgs& a, float* U, float* hn, int rese
         CSV_LAUNCH_CHECK("bound_finish_kernel");
         return CSV_OK;
     }
-    int bt = 1;
-    while (bt < a.B && bt < 4) bt <<= 1;       // B <= 4 here (more sequences take the MFMA product)
-    while (bt > 1 && (size_t)bt * a.d * 2 > BOUND_LDS_MAX) bt >>= 1;
     const bool m16 = a.mu16 != nullptr;
-    const size_t lds = (size_t)bt * a.d * 2;
-    if (a.B == 1) {
-        const int nq = m16 ? a.d >> 3 : a.d >> 2;     // 128-bit units per centroid row
-        int wpc = 1;
-        while (wpc < 4 && (nq + wpc - 1) / wpc > 64 * BOUND_PF) wpc <<= 1;
-        const int cpb = (BOUND_THREADS / 64) / wpc;
-        const int groups = (a.C + cpb - 1) / cpb;
-        const int gpx = (groups + 7) / 8;
-        if (m16) bound1_kernel<true><<<gpx * 8, BOUND_THREADS, 0, st>>>(a, U, hn, reset, groups, gpx, wpc);
-        else bound1_kernel<false><<<gpx * 8, BOUND_THREADS, 0, st>>>(a, U, hn, reset, groups, gpx, wpc);
-        CSV_LAUNCH_CHECK("bound1_kernel");
+    const int nq = m16 ? a.d >> 3 : a.d >> 2;         // 128-bit units per centroid row
+    int wpc = 1;
+    while (wpc < 4 && (nq + wpc - 1) / wpc > 64 * BOUND_ROWS_PF(a.B)) wpc <<= 1;
+    // Three and four sequences against many long bf16 rows: a wave reads twice and more as many bytes of h as of its centroid, and from the second round of
+    // waves on (4096 at once) reading h from LDS wins (us, from L2 / from LDS: C = 4096, d = 5120 21.7 / 16.5, C = 2048, d = 7168 9.4 / 7.7, C = 1500,
+    // d = 5120 8.6 / 7.1; but C = 1024, d = 8192 6.9 / 7.7, C = 2048, d = 4096 6.4 / 7.5, C = 8192, d = 1024 10.3 / 20.3).
+    const size_t lds = (size_t)4 * a.d * 2;
+    if (m16 && a.B > 2 && wpc > 1 && a.C * wpc > 4096 && lds <= BOUND_LDS_MAX) {
+        int dev = 0, cus = 0;
+        CSV_HIP(hipGetDevice(&dev));
+        CSV_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+        // as many blocks as are resident together (LDS decides), at most one wave per cluster
+        int per_cu = (int)((size_t)(150 * 1024) / (lds + 1024));
+        per_cu = per_cu < 1 ? 1 : (per_cu > 4 ? 4 : per_cu);
+        int gx = (a.C + (BOUND_THREADS / 64) - 1) / (BOUND_THREADS / 64);
+        if (gx > cus * per_cu) gx = cus * per_cu;
+        // more dynamic LDS than the default limit: raise the attribute (only ever upwards)
+        if (lds + 4096 > 65536) CSV_HIP(raise_lds(dev, K_BOUND, (const void*)bound_kernel, BOUND_LDS_MAX));
+        bound_kernel<<<gx, BOUND_THREADS, lds, st>>>(a, U, hn, reset);
+        CSV_LAUNCH_CHECK("bound_kernel");
         return CSV_OK;
     }
-    int dev = 0, cus = 0;
-    CSV_HIP(hipGetDevice(&dev));
-    CSV_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    // as many blocks as are resident together (LDS decides), at most one wave per cluster
-    int per_cu = (int)((size_t)(150 * 1024) / (lds + 1024));
-    per_cu = per_cu < 1 ? 1 : (per_cu > 4 ? 4 : per_cu);
-    int gx = (a.C + (BOUND_THREADS / 64) - 1) / (BOUND_THREADS / 64);
-    if (gx > cus * per_cu) gx = cus * per_cu;
-    dim3 grid(gx, (a.B + bt - 1) / bt);
-    if (lds + 4096 > 65536) {        // more dynamic LDS than the default limit: raise this variant's attribute (only ever upwards)
-        const void* fn = nullptr;
-        switch (bt) {
-            case 2: fn = m16 ? (const void*)bound_kernel<2, true> : (const void*)bound_kernel<2, false>; break;
-            case 4: fn = m16 ? (const void*)bound_kernel<4, true> : (const void*)bound_kernel<4, false>; break;
-            default: fn = m16 ? (const void*)bound_kernel<1, true> : (const void*)bound_kernel<1, false>; break;
-        }
-        const int slot = K_BOUND0 + (bt == 1 ? 0 : bt == 2 ? 1 : bt == 4 ? 2 : 3) * 2 + (m16 ? 1 : 0);
-        CSV_HIP(raise_lds(dev, slot, fn, BOUND_LDS_MAX));
-    }
-#define CSV_BOUND_LAUNCH(BT)                                                                   \
-    do {                                                                                       \
-        if (m16) bound_kernel<BT, true><<<grid, BOUND_THREADS, lds, st>>>(a, U, hn, reset);    \
-        else bound_kernel<BT, false><<<grid, BOUND_THREADS, lds, st>>>(a, U, hn, reset);       \
+    const int cpb = (BOUND_THREADS / 64) / wpc;
+    const int groups = (a.C + cpb - 1) / cpb;
+    const int gpx = (groups + 7) / 8;
+#define CSV_BOUND_ROWS(BT)                                                                                            \
+    do {                                                                                                              \
+        if (m16) bound_rows_kernel<BT, true><<<gpx * 8, BOUND_THREADS, 0, st>>>(a, U, hn, reset, groups, gpx, wpc);   \
+        else bound_rows_kernel<BT, false><<<gpx * 8, BOUND_THREADS, 0, st>>>(a, U, hn, reset, groups, gpx, wpc);      \
     } while (0)
-    switch (bt) {
-        case 1: CSV_BOUND_LAUNCH(1); break;        // 2..4 sequences of rows too long for two of them in LDS
-        case 2: CSV_BOUND_LAUNCH(2); break;
-        default: CSV_BOUND_LAUNCH(4); break;
+    switch (a.B) {
+        case 1: CSV_BOUND_ROWS(1); break;
+        case 2: CSV_BOUND_ROWS(2); break;
+        case 3: CSV_BOUND_ROWS(3); break;
+        default: CSV_BOUND_ROWS(4); break;            // more sequences take the MFMA product
     }
-#undef CSV_BOUND_LAUNCH
-    CSV_LAUNCH_CHECK("bound_kernel");
+#undef CSV_BOUND_ROWS
+    CSV_LAUNCH_CHECK("bound_rows_kernel");
     return CSV_OK;
 }
 

@@ -1,10 +1,10 @@
-"""Cluster bounds of batches around the 64 sequences that one block of the batched product carries."""
+"""Cluster bounds: batches around the 64 sequences that one block of the batched product carries, and the few sequences that go by rows."""
 import numpy as np
 import pytest
 
 import synth
 
-from ._harness import Case
+from ._harness import Case, log
 
 pytestmark = pytest.mark.gpu
 
@@ -24,3 +24,41 @@ def test_batched_bounds_match_float64(B, bf16):
     scale = hn[:, None] * (np.linalg.norm(mu, axis=1) + R)[None, :] + np.abs(bmax)[None, :]
     assert U.shape == want.shape and np.all(np.abs(U - want) <= 1e-5 * scale)
     case.close()
+
+
+# Up to four sequences, a slice of a centroid row per wave: rows of one slice, of two and four, of a slice and a bit, a whole number of batches of
+# loads; clusters that do not fill the last block.  bf16 rows of four sequences on both sides of the 4096 waves from which h goes through LDS.  An entry's error
+# is at most that of a float32 sum of d exact products in lanes of d / 64: (d / 64 + 16) 2^-24 of |mu| |h|, and a few roundings of the sum.
+@pytest.mark.parametrize("C,d,bf16", [(5, 8, False), (75, 520, False), (33, 1032, False), (131, 2056, False), (9, 4104, False), (70, 8192, False),
+                                      (75, 520, True), (33, 4104, True), (1030, 4104, True), (1030, 2056, True), (2050, 2056, True)])
+@pytest.mark.parametrize("B", [1, 2, 3, 4])
+def test_bounds_of_a_few_sequences(B, C, d, bf16):
+    import paper_2511_21702_amd as csv
+    torch = pytest.importorskip("torch")
+    gen = torch.Generator(device="cuda").manual_seed(C + d)
+    V = 2 * C + 1
+    W = (torch.randn(V, d, device="cuda", generator=gen) * (4.0 / d ** 0.5)).to(torch.bfloat16)
+    b = torch.randn(V, device="cuda", generator=gen) * 0.1
+    labels = np.arange(V, dtype=np.int32) % C
+    labels[labels == C // 2] = 0                                       # an empty cluster
+    h = (torch.randn(B, d, device="cuda", generator=gen) * (8.0 / d ** 0.5)).to(torch.bfloat16)
+    log(f"bounds B={B} C={C} d={d} bf16={bf16}")
+    g = csv.csv_build_index(W, b, C, init_labels=labels, centroid_bf16=bf16)
+    ws = csv.CsvWorkspace(g, B, V)
+    U, hn = csv.csv_bounds(ws, g, h)
+    U2, hn2 = torch.empty_like(U), torch.empty_like(hn)
+    csv.csv_bounds_static(g, h, U2, hn2)
+    assert torch.equal(U, U2) and torch.equal(hn, hn2)
+    e = g.export()
+    mu, R, bmax = (np.asarray(e[k], np.float64) for k in ("mu", "R", "bmax"))
+    h64 = h.double().cpu().numpy()
+    n = np.linalg.norm(h64, axis=1)
+    want = h64 @ mu.T + n[:, None] * R[None, :] + bmax[None, :]
+    full = e["n"] > 0
+    tol = ((d / 64 + 16) * 2.0 ** -24) * n[:, None] * (np.linalg.norm(mu, axis=1) + R)[None, :] + 2.0 ** -22 * np.abs(want)
+    got = U.double().cpu().numpy()
+    assert np.isneginf(got[:, ~full]).all() and not full.all()
+    assert (np.abs(got - want)[:, full] <= tol[:, full]).all()
+    assert (np.abs(hn.double().cpu().numpy() - n) <= (d / 64 + 16) * 2.0 ** -24 * n).all()
+    ws.free()
+    g.free()
