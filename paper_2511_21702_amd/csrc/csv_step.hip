@@ -404,6 +404,7 @@ __device__ __forceinline__ void split3_bf16(const float4& x0, const float4& x1, 
 #define BOUND_PIPE 4             // k-blocks (of 32) a wave has requested ahead: 8 KB of float32 centroids
 #endif
 #define BOUND_LDS_KB 48          // most LDS for the h of one K slice (1 KB per k-block and 16 sequences)
+#define BOUND_LDS_KB_MANY 64     // with more than 64 sequences
 __device__ __forceinline__ uint4 keep_if(bool c, const uint4& v) {     // v or zero, component by component (no select between objects in memory)
     return make_uint4(c ? v.x : 0u, c ? v.y : 0u, c ? v.z : 0u, c ? v.w : 0u);
 }
@@ -444,7 +445,7 @@ __global__ __launch_bounds__(512) void bound_mfma_kernel(StepArgs a, float* __re
         }
     };
     // h first (older loads are waited for first), then the centroid requests, which stay in flight across the staging
-    constexpr int HS = (BOUND_LDS_KB * 64 + 511) / 512;           // staged 128-bit pieces per thread at most
+    constexpr int HS = ((NT == 4 ? BOUND_LDS_KB_MANY : BOUND_LDS_KB) * 64 + 511) / 512;           // staged 128-bit pieces per thread at most
     const int items = nchunk * BOUND_PIPE * NT * 64;
     const uint4* hsrc = reinterpret_cast<const uint4*>(a.h);
     uint4 hreg[HS];
@@ -3328,14 +3329,16 @@ static hipError_t raise_lds(int dev, int which, const void* fn, size_t bytes) {
 // slices) fills the device, a whole number of request chunks per slice, a slice's h within BOUND_LDS_KB of LDS, at most
 // BOUND_KS_MAX slices (the partial buffer holds KS x B x C floats).  B decides how many sequence tiles a block carries.
 static int bound_mfma_nt(int B) { return B > 32 ? 4 : (B > 16 ? 2 : 1); }
-static void bound_mfma_plan(int C, int d, int B, int& KS, int& kbs) {
+static void bound_mfma_plan(int C, int d, int B, int& KS, int& kbs, bool many) {
     const int tiles = (C + 15) / 16, groups = (tiles + BOUND_TILES_PER_BLOCK - 1) / BOUND_TILES_PER_BLOCK, nkb = (d + 31) / 32;
-    KS = (BOUND_BLOCK_TARGET + groups - 1) / groups;
+    // many: more than 64 sequences, whose groups of 64 are blocks of their own, in fewer and longer slices: their partial sums are what the launch
+    // writes and the next one reads (us, C = 1024, d = 4096, 256 sequences: 26.1 -> 18.8; C = 2000, d = 5000, 130: 28.7 -> 25.6)
+    KS = (BOUND_BLOCK_TARGET / (many ? (B + 63) / 64 : 1) + groups - 1) / groups;
     if (KS > BOUND_KS_MAX) KS = BOUND_KS_MAX;
     if (KS > nkb) KS = nkb;
     kbs = (nkb + KS - 1) / KS;
     kbs = (kbs + BOUND_PIPE - 1) / BOUND_PIPE * BOUND_PIPE;     // whole chunks
-    const int cap = BOUND_LDS_KB / bound_mfma_nt(B) / BOUND_PIPE * BOUND_PIPE;
+    const int cap = (many ? BOUND_LDS_KB_MANY : BOUND_LDS_KB) / bound_mfma_nt(B) / BOUND_PIPE * BOUND_PIPE;
     if (kbs > cap) kbs = cap;                                   // d <= 8192: 256 k-blocks in at most 32 slices of 8 always fit
     KS = (nkb + kbs - 1) / kbs;
 }
@@ -3344,7 +3347,7 @@ static int launch_bounds_kernel(const StepArgs& a, float* U, float* hn, int rese
     if (a.B >= BOUND_MFMA_MIN_B) {
         const int tiles = (a.C + 15) / 16;
         int KS, kbs;
-        bound_mfma_plan(a.C, a.d, a.B, KS, kbs);
+        bound_mfma_plan(a.C, a.d, a.B, KS, kbs, a.B > 64);
         dim3 grid((tiles + BOUND_TILES_PER_BLOCK - 1) / BOUND_TILES_PER_BLOCK, KS, (a.B + 63) / 64);
         const int nt = bound_mfma_nt(a.B);
         const size_t lds = (size_t)kbs * nt * 1024;
@@ -3655,9 +3658,10 @@ extern "C" int csv_bounds_static(const csv_index* idx, const uint16_t* d_h, int 
     a.V = idx->V; a.d = idx->d; a.C = idx->C;
     a.mu = idx->mu; a.mu16 = idx->mu16; a.R = idx->R; a.bmax = idx->bmax; a.n = idx->n; a.bt = idx->bt; a.bt_m = idx->bt_m; a.ang = idx->ang;
     a.B = B; a.h = d_h;
-    if (B >= BOUND_MFMA_MIN_B) {       // the batched product is the only bound kernel with scratch: KS x B x C partial sums
+    if (B >= BOUND_MFMA_MIN_B) {       // the batched product is the only bound kernel with scratch: KS x B x C partial sums; the limit is that of 64
+                                       // sequences' slices for every batch, also where the launch takes fewer slices or none
         int KS, kbs;
-        bound_mfma_plan(idx->C, idx->d, B, KS, kbs);
+        bound_mfma_plan(idx->C, idx->d, B, KS, kbs, false);
         const size_t need = (size_t)KS * B * idx->C * sizeof(float);
         if (need > CSV_STATIC_SCRATCH_BYTES) {
             csv_set_error("B=%d sequences x C=%d clusters need %zu bytes of partial sums, the static scratch holds %u: "
