@@ -517,6 +517,111 @@ __global__ __launch_bounds__(512) void bound_mfma_kernel(StepArgs a, float* __re
     }
 }
 
+// Up to 16 sequences in one launch: block = 16 clusters and the whole of K, so that nothing has to meet outside the block.  K goes by in chunks of 32 k-blocks,
+// two to each of the 16 waves; h of a chunk lies in LDS in fragment order (places turned by the k group, so that rows can be read from memory in runs of
+// 1 KB and written without bank conflicts), the next chunk's is requested a chunk ahead and stored to the other half; every wave has the centroid values of its next two
+// k-blocks requested.  The waves' sums are added in wave order.
+// Bound by latency, for long rows and many clusters by reading the centroids: C = 4096, d = 5120 in bf16 10.7 us = 3.9 TB/s.  (With chunks of 64 k-blocks, twice the
+// time until the first products, 12.7; with h read from L2 by every wave 13.7-15.5.)
+#define BOUND_TILE_KB 32
+#define BOUND_TILE_LDS (2 * BOUND_TILE_KB * 1024)
+template <bool MU16>
+__global__ __launch_bounds__(1024) void bound_tile_kernel(StepArgs a, float* __restrict__ U_out, float* __restrict__ hn_out, int reset_counters) {
+    extern __shared__ uint4 bound_lds[];
+    constexpr int PER = BOUND_TILE_KB / 16;                  // k-blocks of a chunk per wave = pieces of h a lane stages
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, g = lane >> 4, nch = a.d >> 3, nchunk = (a.d + 32 * BOUND_TILE_KB - 1) / (32 * BOUND_TILE_KB), c0 = blockIdx.x * 16;
+    const size_t crow = (size_t)min(c0 + li, a.C - 1) * a.d;
+    const uint4* ap = MU16 ? reinterpret_cast<const uint4*>(a.mu16 + crow) : reinterpret_cast<const uint4*>(a.mu + crow);
+    const uint4* hp = reinterpret_cast<const uint4*>(a.h) + (size_t)min(wave, a.B - 1) * nch;      // the wave stages one sequence (past B: one whose sums nobody takes)
+    uint4 X[PER][MU16 ? 1 : 2], H[PER];
+    auto request_h = [&](int ch) {
+#pragma unroll
+        for (int q = 0; q < PER; ++q) H[q] = hp[min(ch * 4 * BOUND_TILE_KB + lane + 64 * q, nch - 1)];
+    };
+    auto store_h = [&](int ch) {                             // zeros past d: they meet the centroid row's last values
+        uint4* o = bound_lds + (ch & 1) * BOUND_TILE_KB * 64;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int p = lane + 64 * q;
+            o[p * 16 + ((wave + p) & 15)] = keep_if(ch * 4 * BOUND_TILE_KB + p < nch, H[q]);
+        }
+    };
+    auto request_x = [&](int u, int ch) {                    // the wave's k-blocks lie side by side
+        const int q = min((ch * BOUND_TILE_KB + wave * PER + u) * 4 + g, nch - 1);
+        if constexpr (MU16) {
+            X[u][0] = ap[q];
+        } else {
+            X[u][0] = ap[2 * q];
+            X[u][1] = ap[2 * q + 1];
+        }
+    };
+    request_h(0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) request_x(u, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (reset_counters && blockIdx.x == 0) reset_step_counters(a.counters, a.B, 1024, a.host_history, a.slots, a.B_max);
+    store_h(0);
+    __builtin_amdgcn_sched_barrier(0);
+    request_h(1);
+    lds_barrier();
+    floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
+    float ss = 0.f;
+    for (int ch = 0; ch < nchunk; ++ch) {
+        const uint4* hb = bound_lds + (ch & 1) * BOUND_TILE_KB * 64;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int p = (wave * PER + u) * 4 + g;
+            const uint4 hv = hb[p * 16 + ((li + p) & 15)];
+            ss = dot8_bf16(hv, hv, ss);
+            const bf16x8_t bv = __builtin_bit_cast(bf16x8_t, hv);
+            if constexpr (MU16) {
+                const bf16x8_t xv = __builtin_bit_cast(bf16x8_t, X[u][0]);
+                __builtin_amdgcn_sched_barrier(0);
+                request_x(u, ch + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, xv, acc, 0, 0, 0);
+            } else {
+                uint4 hi, mid, lo;
+                split3_bf16(__builtin_bit_cast(float4, X[u][0]), __builtin_bit_cast(float4, X[u][1]), hi, mid, lo);
+                __builtin_amdgcn_sched_barrier(0);
+                request_x(u, ch + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, __builtin_bit_cast(bf16x8_t, hi), acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, __builtin_bit_cast(bf16x8_t, mid), acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, __builtin_bit_cast(bf16x8_t, lo), acc, 0, 0, 0);
+            }
+        }
+        if (ch + 1 < nchunk) {
+            store_h(ch + 1);                                 // to the half that was read a chunk ago: every wave has passed its barrier
+            __builtin_amdgcn_sched_barrier(0);
+            request_h(ch + 2);
+        }
+        lds_barrier();
+    }
+    // accumulator register r of lane (li, g) is [sequence 4g + r][cluster li]; the squares of sequence li are in its four lanes
+    float* red = reinterpret_cast<float*>(bound_lds);        // [wave][sequence][cluster], then [wave][sequence]
+    float* redh = red + 16 * 256;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[wave * 256 + (4 * g + r) * 16 + li] = acc[r];
+    ss += __shfl_xor(ss, 16, CSV_WAVE);
+    ss += __shfl_xor(ss, 32, CSV_WAVE);
+    if (g == 0) redh[wave * 16 + li] = ss;
+    __syncthreads();
+    const int sq = tid >> 4, c = c0 + (tid & 15);
+    if (sq >= a.B || sq >= 16) return;
+    float u = 0.f, th = 0.f;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        u += red[w * 256 + tid];
+        th += redh[w * 16 + sq];
+    }
+    const float hn = sqrtf(th);
+    if (c0 == 0 && (tid & 15) == 0 && hn_out) hn_out[sq] = hn;
+    if (c < a.C) U_out[(size_t)sq * a.C + c] = a.n[c] == 0 ? -INFINITY : bound_value(a, c, u, a.R[c], a.bmax[c], hn);
+}
+
 // Block (x, b): ||h_b|| (every block of the sequence recomputes it: d values), then for 256 clusters
 // U[b,c] = sum of the K-slice partials (ascending slice) + R_c ||h_b|| + bmax_c.
 __global__ __launch_bounds__(256) void bound_finish_kernel(StepArgs a, const float* __restrict__ P, int KS,
@@ -3309,7 +3414,7 @@ static int check_pair(const csv_workspace* ws, const csv_index* idx, const void*
 
 // The dynamic-LDS limit of a kernel is one attribute per process and device, shared by every workspace: it is only
 // ever raised, so a workspace created later with smaller needs cannot take away what an earlier one's launches rely on.
-enum { K_ROUND0, K_ROUND0_THRESH, K_ROUND0_PLANS, K_STEP, K_STEP_MANY, K_TAIL, K_RCERT, K_FBPROD, K_FBPRODM /* + levels */, K_FULLMFMA = K_FBPRODM + 4 /* + levels */, K_ALG1 = K_FULLMFMA + 4, K_BOUND, K_NKERN };
+enum { K_ROUND0, K_ROUND0_THRESH, K_ROUND0_PLANS, K_STEP, K_STEP_MANY, K_TAIL, K_RCERT, K_FBPROD, K_FBPRODM /* + levels */, K_FULLMFMA = K_FBPRODM + 4 /* + levels */, K_ALG1 = K_FULLMFMA + 4, K_BOUND, K_BOUNDT, K_BOUNDT16, K_NKERN };
 static size_t g_lds_limit[CSV_STATIC_MAX_DEVICES][K_NKERN];
 static pthread_mutex_t g_attr_lock = PTHREAD_MUTEX_INITIALIZER;
 #define CSV_STATIC_LDS_MAX 16384     // at least the static shared memory of any kernel here
@@ -3343,9 +3448,28 @@ static void bound_mfma_plan(int C, int d, int B, int& KS, int& kbs, bool many) {
     KS = (nkb + kbs - 1) / kbs;
 }
 
+// Where the one launch beats the product over K slices and the launch that adds them up (us, two launches / one; B = 16): its blocks are as many as tiles
+// (4096 clusters are one round of them) and each reads its rows alone, so rows must be short or tiles many.  bf16: C = 1024, d = 1024 and f32 9.2 / 6.6, d = 4096
+// 9.4 / 7.9, C = 4096, d = 5120 13.3 / 10.7, but d = 6144 9.6 / 9.9, d = 8192 10.4 / 12.0 and two rounds C = 8192, d = 4096 16.1 / 17.3, d = 1024 9.6 / 7.2.
+// float32: d = 2048 9.8 / 8.6, C = 4096 11.3 / 8.8, but C = 1024, d = 4096 9.3 / 11.8, C = 2048, d = 5120 13.6 / 14.5; many tiles: C = 4096, d = 3000 13.6 / 11.0, d = 4608
+// 17.3 / 16.2, C = 3500, d = 6000 21.4 / 16.3, but d = 4096 16.2 / 20.5 (rows a multiple of 4 KB apart ask for the same memory channels).
+static bool bound_tile_pays(int C, int d, int B, bool m16) {
+    if (B > 16) return false;
+    if (m16) return d <= (C <= 4096 ? 5120 : 2048);
+    return C <= 4096 && (d <= 2048 || (C >= 3072 && d <= 6144 && d % 1024 != 0));
+}
 static int launch_bounds_kernel(const StepArgs& a, float* U, float* hn, int reset, hipStream_t st) {
     if (a.B >= BOUND_MFMA_MIN_B) {
         const int tiles = (a.C + 15) / 16;
+        if (bound_tile_pays(a.C, a.d, a.B, a.mu16 != nullptr)) {
+            int dev = 0;
+            CSV_HIP(hipGetDevice(&dev));
+            CSV_HIP(raise_lds(dev, a.mu16 ? K_BOUNDT16 : K_BOUNDT, a.mu16 ? (const void*)bound_tile_kernel<true> : (const void*)bound_tile_kernel<false>, BOUND_TILE_LDS));
+            if (a.mu16) bound_tile_kernel<true><<<tiles, 1024, BOUND_TILE_LDS, st>>>(a, U, hn, reset);
+            else bound_tile_kernel<false><<<tiles, 1024, BOUND_TILE_LDS, st>>>(a, U, hn, reset);
+            CSV_LAUNCH_CHECK("bound_tile_kernel");
+            return CSV_OK;
+        }
         int KS, kbs;
         bound_mfma_plan(a.C, a.d, a.B, KS, kbs, a.B > 64);
         dim3 grid((tiles + BOUND_TILES_PER_BLOCK - 1) / BOUND_TILES_PER_BLOCK, KS, (a.B + 63) / 64);

@@ -33,6 +33,19 @@ def test_batched_bounds_match_float64(B, bf16):
                                       (75, 520, True), (33, 4104, True), (1030, 4104, True), (1030, 2056, True), (2050, 2056, True)])
 @pytest.mark.parametrize("B", [1, 2, 3, 4])
 def test_bounds_of_a_few_sequences(B, C, d, bf16):
+    _bounds_match_float64(B, C, d, bf16)
+
+
+# Up to 16 sequences in one launch: rows shorter than a chunk of 1024 values, of one, of several and a bit; clusters inside a tile of 16; then shapes on the other
+# side of the rule, which go by K slices.
+@pytest.mark.parametrize("C,d,bf16", [(5, 8, False), (75, 520, False), (33, 1024, False), (131, 1032, False), (16, 2048, False), (3077, 3000, False), (17, 4104, True),
+                                      (40, 5120, True), (4200, 1040, True), (131, 2056, False), (20, 8192, True)])
+@pytest.mark.parametrize("B", [5, 11, 16, 17])
+def test_bounds_of_a_small_batch(B, C, d, bf16):
+    _bounds_match_float64(B, C, d, bf16)
+
+
+def _bounds_match_float64(B, C, d, bf16):
     import paper_2511_21702_amd as csv
     torch = pytest.importorskip("torch")
     gen = torch.Generator(device="cuda").manual_seed(C + d)
