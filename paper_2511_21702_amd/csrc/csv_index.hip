@@ -1383,12 +1383,10 @@ static AssignPlan assign_plan(int V, int C, bool near, int kinds = 3) {
     return best;
 }
 // Whether the rounded centroids come first.  They save two thirds of the exact product, V d C, and cost four launches and the pairs, which do not shrink with
-// C.  Builds of four iterations, exact against rounded first: V = 32000, d = 1024, C = 256 661 / 813 us, C = 512 799 / 786; V = 32000, d = 4096, C = 256
-// 1763 / 1914; V = 64000, d = 2048, C = 384 2137 / 1970; V = 128256, d = 4096, C = 256 4849 / 3939, C = 384 6764 / 6471.
-static bool assign_near_pays(int V, int d, int C) {
-    const double work = (double)V * d * C;
-    return C >= 384 ? work >= 20e9 : C >= 256 && work >= 100e9;
-}
+// C; where most rows stay open (hundreds of seeds in one centre) the look at them is lost.  Builds of four iterations, exact against rounded first: V = 32000,
+// d = 1024, C = 256 661 / 813 us, C = 512 799 / 786; V = 32000, d = 4096, C = 256 1763 / 1914; V = 64000, d = 2048, C = 384 2137 / 1970; V = 128256, d = 4096,
+// C = 384 6764 / 6471, C = 256 4849 / 3939 (but C = 336 with rows left open 5503 / 5598).
+static bool assign_near_pays(int V, int d, int C) { return C >= 384 && (double)V * d * C >= 20e9; }
 struct AssignRun {                       // what an assignment reads and writes, in the build's scratch
     const uint16_t* W;
     const float* mu;

@@ -114,8 +114,13 @@ __device__ __forceinline__ void reset_step_counters(int* counters, int B, int nt
         const unsigned lo = ((old << 1) | (unsigned)(counters[CNT_TAIL_NEEDED] != 0)) & 0xffffu;
         const unsigned hi = (((old >> 16) << 1) | (unsigned)(counters[CNT_FALLBACK] != 0)) & 0x7fffu;
         const int h = (int)(lo | (hi << 16));
+        const int deep = (counters[CNT_DEEP_HISTORY] << 1 | (counters[CNT_DEEP] != 0)) & 0xffff;
         counters[CNT_HISTORY] = h;
-        if (host_history) *host_history = h;
+        counters[CNT_DEEP_HISTORY] = deep;
+        if (host_history) {
+            host_history[0] = h;
+            host_history[1] = deep;
+        }
     }
     __syncthreads();             // called by every thread of one block: the zeroing below must not overtake the reads
     for (int i = threadIdx.x; i < CNT_TILES + rows * B; i += nthreads) {
@@ -419,7 +424,7 @@ __device__ __forceinline__ void lds_barrier() {      // all LDS accesses of the 
 // behind the load.  Every wave has BOUND_PIPE k-blocks of its 16 centroid rows requested ahead; a register buffer is
 // requested again as soon as its values are split.  The last chunk is a copy of the loop body without requests, so
 // that the waits the compiler places are counted at compile time.
-template <int NT, bool MU16>
+template <int NT, bool MU16, bool MANY = false>
 __global__ __launch_bounds__(512) void bound_mfma_kernel(StepArgs a, float* __restrict__ P, int kb_per_slice,
                                                          int reset_counters) {
     extern __shared__ uint4 bound_lds[];
@@ -445,7 +450,7 @@ __global__ __launch_bounds__(512) void bound_mfma_kernel(StepArgs a, float* __re
         }
     };
     // h first (older loads are waited for first), then the centroid requests, which stay in flight across the staging
-    constexpr int HS = ((NT == 4 ? BOUND_LDS_KB_MANY : BOUND_LDS_KB) * 64 + 511) / 512;           // staged 128-bit pieces per thread at most
+    constexpr int HS = ((MANY ? BOUND_LDS_KB_MANY : BOUND_LDS_KB) * 64 + 511) / 512;           // staged 128-bit pieces per thread at most
     const int items = nchunk * BOUND_PIPE * NT * 64;
     const uint4* hsrc = reinterpret_cast<const uint4*>(a.h);
     uint4 hreg[HS];
@@ -3197,34 +3202,35 @@ __device__ __forceinline__ bool grid_barrier(int* counters, int which, int nbloc
 
 // block / nblocks: this block's position among the blocks that run the tail together (all resident).
 template <bool THRESH, bool MANY>
-__device__ __forceinline__ void tail_device(const StepArgs& a, const FullArgs& f, int fallback_only, int block, int nblocks,
+__device__ __forceinline__ void tail_device(const StepArgs& a, const FullArgs& f, int from, int block, int nblocks,
                                             SeqShared& s, GemvShared& gs, int* s_flag) {
     extern __shared__ __align__(16) u64 arena[];
     const int tid = threadIdx.x;
     if (a.counters[CNT_TAIL_NEEDED] == 0) return;      // the common case at small batches: one word, no reduction
-    if (fallback_only && a.counters[CNT_FALLBACK] == 0) return;
+    if (from >= a.max_rounds && a.counters[CNT_FALLBACK] == 0) return;
     // is any sequence waiting for round 0 (a seed prefix too large for the round-0 blocks), for round 1 or for the
     // full product?  Every block reads the same, settled values.
     int mine0 = 0, mine1 = 0;
-    if (tid < a.B) {
-        mine0 = a.counters[CNT_TILES + tid];
-        mine1 = a.counters[CNT_TILES + CSV_MAX_BATCH + tid];
+    if (tid < a.B && from < a.max_rounds) {
+        mine0 = from ? 0 : a.counters[CNT_TILES + tid];
+        mine1 = a.counters[CNT_TILES + (from ? from : 1) * CSV_MAX_BATCH + tid];
     }
     const int n_fb0 = a.counters[CNT_FALLBACK];
-    int tiles0 = block_sum_i(mine0, s.redi);
+    const int tiles0 = block_sum_i(mine0, s.redi);
     int tiles = block_sum_i(mine1, s.redi);
-    if (fallback_only) tiles0 = tiles = 0;      // the rounds ran as launches of their own
     if (tiles0 == 0 && tiles == 0 && n_fb0 == 0) return;
 
     // Rounds: the GEMV over the round's work list, then the certification, which may plan the next round.
     // Round 0 is here only for seed prefixes that the round-0 blocks handed over.
-    for (int r = tiles0 > 0 ? 0 : 1; r < a.max_rounds && !fallback_only; ++r) {
+    const int first = from ? from : tiles0 > 0 ? 0 : 1;
+    for (int r = first; r < a.max_rounds; ++r) {
         if (r > 0) {
-            if (r > 1 || tiles0 > 0) {   // planned by a certification earlier in this kernel: read past the barrier
+            if (r > first) {             // planned by a certification earlier in this kernel: read past the barrier
                 const int mine = tid < a.B ? __hip_atomic_load(&a.counters[CNT_TILES + r * CSV_MAX_BATCH + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
                 tiles = block_sum_i(mine, s.redi);
             }
             if (tiles == 0) break;
+            if (r > 1 && block == 0 && tid == 0) a.counters[CNT_DEEP] = 1;
         }
         gemv_tiles_device(a, r, reinterpret_cast<uint4*>(arena), gs, block, nblocks);
         if (!grid_barrier(a.counters, 2 * r, nblocks, s_flag, a.spin_limit)) return;
@@ -3254,11 +3260,12 @@ __device__ __forceinline__ void tail_device(const StepArgs& a, const FullArgs& f
     }
 }
 
-__global__ __launch_bounds__(TAIL_THREADS) void tail_kernel(StepArgs a, FullArgs f, int fallback_only) {
+// from: the first round it runs, those before were launches of their own (0: as queued; max_rounds: the fallback only)
+__global__ __launch_bounds__(TAIL_THREADS) void tail_kernel(StepArgs a, FullArgs f, int from) {
     __shared__ SeqShared s;
     __shared__ GemvShared gs;
     __shared__ int s_flag;
-    tail_device<true, true>(a, f, fallback_only, blockIdx.x, gridDim.x, s, gs, &s_flag);
+    tail_device<true, true>(a, f, from, blockIdx.x, gridDim.x, s, gs, &s_flag);
 }
 
 // ------------------------------------------------------------------------------------------------ round 0 as a launch
@@ -3324,6 +3331,7 @@ __global__ __launch_bounds__(TAIL_THREADS, 2) void round_gemv_kernel(StepArgs a,
     extern __shared__ __align__(16) u64 arena[];
     __shared__ GemvShared gs;
     if (a.counters[CNT_TAIL_NEEDED] == 0) return;
+    if (r > 1 && blockIdx.x == 0 && threadIdx.x < a.B && a.counters[CNT_TILES + r * CSV_MAX_BATCH + threadIdx.x] != 0) a.counters[CNT_DEEP] = 1;
     gemv_tiles_device(a, r, reinterpret_cast<uint4*>(arena), gs, blockIdx.x, gridDim.x);
 }
 
@@ -3478,11 +3486,13 @@ static int launch_bounds_kernel(const StepArgs& a, float* U, float* hn, int rese
         if (a.mu16) {
             if (nt == 1) bound_mfma_kernel<1, true><<<grid, 512, lds, st>>>(a, a.bound_partial, kbs, reset);
             else if (nt == 2) bound_mfma_kernel<2, true><<<grid, 512, lds, st>>>(a, a.bound_partial, kbs, reset);
-            else bound_mfma_kernel<4, true><<<grid, 512, lds, st>>>(a, a.bound_partial, kbs, reset);
+            else if (a.B <= 64) bound_mfma_kernel<4, true><<<grid, 512, lds, st>>>(a, a.bound_partial, kbs, reset);
+            else bound_mfma_kernel<4, true, true><<<grid, 512, lds, st>>>(a, a.bound_partial, kbs, reset);
         } else {
             if (nt == 1) bound_mfma_kernel<1, false><<<grid, 512, lds, st>>>(a, a.bound_partial, kbs, reset);
             else if (nt == 2) bound_mfma_kernel<2, false><<<grid, 512, lds, st>>>(a, a.bound_partial, kbs, reset);
-            else bound_mfma_kernel<4, false><<<grid, 512, lds, st>>>(a, a.bound_partial, kbs, reset);
+            else if (a.B <= 64) bound_mfma_kernel<4, false><<<grid, 512, lds, st>>>(a, a.bound_partial, kbs, reset);
+            else bound_mfma_kernel<4, false, true><<<grid, 512, lds, st>>>(a, a.bound_partial, kbs, reset);
         }
         CSV_LAUNCH_CHECK("bound_mfma_kernel");
         bound_finish_kernel<<<dim3((a.C + 255) / 256, a.B), 256, 0, st>>>(a, a.bound_partial, KS, U, hn);
@@ -3644,7 +3654,7 @@ extern "C" int csv_workspace_create(const csv_index* idx, int B_max, int K_cap_r
     if (e == hipSuccess) e = hipMemset(ws->counters, 0, CNT_ALLOC * 4);
     if (e == hipSuccess) e = hipHostMalloc((void**)&ws->h_history, 64, hipHostMallocDefault);
     if (e == hipSuccess) {
-        *ws->h_history = 0;
+        ws->h_history[0] = ws->h_history[1] = 0;
         e = hipHostGetDevicePointer((void**)&ws->d_history, ws->h_history, 0);
     }
     if (e == hipSuccess) e = hipMemset(ws->slots, 0xFF, B * CSV_SLOT_ROWS * 8);     // every slot empty
@@ -3886,7 +3896,7 @@ extern "C" int csv_decode_step(csv_workspace* ws, const csv_index* idx, const ui
     // step even at B = 1), the single kernel when it is not (one launch that returns at once instead of seven).
     // Unless the caller fixed the choice, follow the recent steps: the bound kernel keeps a bit per step in a
     // pinned host word, read here without synchronising (it may lag a few steps; either choice is correct).
-    bool split, fb_launches = true;
+    bool split, fb_launches = true, deep = true;
     const unsigned history = (unsigned)*(volatile int*)ws->h_history;
     if (ws->split_min_B > 0) {
         split = B >= ws->split_min_B;
@@ -3895,6 +3905,9 @@ extern "C" int csv_decode_step(csv_workspace* ws, const csv_index* idx, const ui
         // the three fallback phases as launches of their own only while fallbacks occur; otherwise one launch
         // of the single kernel restricted to them, which returns at once when nobody fell back
         fb_launches = (history >> 16) != 0;         // any of the last 15 steps
+        // rounds after round 1 likewise: while none of the last 16 steps had one (and none a fallback), that single kernel takes them, too (a pair of
+        // launches that return at once takes 4-6 us: steps with max_rounds = 4, 203 sequences at C = 294 78.7 -> 69.5 us, 232 at C = 1054 157 -> 139)
+        deep = fb_launches || (((volatile int*)ws->h_history)[1] & 0xffff) != 0;
     }
     // blocks per sequence in round 0: as many as stay resident together (a second wave of blocks would double the
     // kernel's time), at most ROUND0_NB_MAX, and no more than the largest possible seed prefix needs at
@@ -3932,7 +3945,8 @@ extern "C" int csv_decode_step(csv_workspace* ws, const csv_index* idx, const ui
             // than max(k,1) rows before its last cluster, so with small clusters that cannot happen: no launches.
             const long long cap = (long long)nb * (SEQ_THREADS / 64) * ROUND0_ROWS_PER_WAVE;
             const bool may_hand_over = prefix_max > (cap < STAGE_CAP ? cap : STAGE_CAP) || (idx->d >> 3) > ROUND0_HREG * SEQ_THREADS;
-            for (int r = may_hand_over ? 0 : 1; r < max_rounds; ++r) {
+            const int launched = deep ? max_rounds : 2;          // rounds before this one are launches of their own
+            for (int r = may_hand_over ? 0 : 1; r < launched; ++r) {
                 round_gemv_kernel<<<ws->tail_grid, TAIL_THREADS, hl, st>>>(a, r);   // more blocks measured slower
                 CSV_LAUNCH_CHECK("round_gemv_kernel");
                 round_cert_kernel<<<dim3(B, ws->sp_chunks), SEQ_THREADS, cert_lds(ws), st>>>(a, r);
@@ -3951,7 +3965,7 @@ extern "C" int csv_decode_step(csv_workspace* ws, const csv_index* idx, const ui
                 fb_final_kernel<<<B, SEQ_THREADS, (size_t)CAND_OFF + CAND_BYTES, st>>>(a);
                 CSV_LAUNCH_CHECK("fb_final_kernel");
             } else {
-                tail_kernel<<<ws->tail_grid, TAIL_THREADS, ws->tail_lds, st>>>(a, f, 1);
+                tail_kernel<<<ws->tail_grid, TAIL_THREADS, ws->tail_lds, st>>>(a, f, launched);
                 CSV_LAUNCH_CHECK("tail_kernel");
             }
         }
