@@ -184,20 +184,20 @@ __global__ __launch_bounds__(64) void layout_scatter_kernel(const int32_t* __res
 // copy is made once, after the last iteration), in float64.  Block = 4 waves x 512 columns; a wave takes every fourth
 // row, eight rows requested at once; the waves' sums are added in wave order.  A cluster of one chunk is finished here, the
 // chunks of a larger one leave partial sums for centroid_finish_kernel, so a cluster of any size is spread over the device.
-// Bound by reading W: 215 us at V = 128256, d = 4096 = 4.9 TB/s.  (One thread per column going down all rows of a cluster: 1.7 ms at V = 128256, d = 4096 with clusters of
+// Bound by reading W: 208 us at V = 128256, d = 4096 = 5.05 TB/s, the blocks of one chunk side by side (of one column slice 215).  (One thread per column going down all rows of a cluster: 1.7 ms at V = 128256, d = 4096 with clusters of
 // up to 2900 rows, plus 0.38 ms for a gathered copy per iteration.)
 // UNIT (spherical clustering): rows are divided by their norm nrm[token], the sums themselves go to out_sum.
 template <bool UNIT>
 __global__ __launch_bounds__(256) void centroid_chunk_kernel(const uint16_t* __restrict__ W, const int32_t* __restrict__ perm, const int32_t* __restrict__ off,
-                                                             const int32_t* __restrict__ coff, const int32_t* __restrict__ poff, const int2* __restrict__ chunks, int d, int C,
+                                                             const int32_t* __restrict__ coff, const int32_t* __restrict__ poff, const int2* __restrict__ chunks, int d, int C, int nslices,
                                                              const double* __restrict__ nrm, float* __restrict__ mu, double* __restrict__ out_sum,
                                                              double* __restrict__ part) {
     __shared__ double red[4][8][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, chunk = blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, chunk = blockIdx.x / nslices;
     if (chunk >= coff[C]) return;
     const int c = chunks[chunk].x, r0 = chunks[chunk].y;
     const int first = off[c], last = off[c + 1], rows = min(CHUNK_ROWS, last - r0);
-    const int piece = blockIdx.y * 64 + lane, np = d >> 3;
+    const int piece = (blockIdx.x - chunk * nslices) * 64 + lane, np = d >> 3;
     const int mine = (rows - wave + 3) / 4;                  // rows r0 + wave, r0 + wave + 4, ...
     const int token = lane < mine ? perm[r0 + wave + 4 * lane] : 0;
     double acc[8];
@@ -225,9 +225,17 @@ __global__ __launch_bounds__(256) void centroid_chunk_kernel(const uint16_t* __r
 #pragma unroll
         for (int q = 0; q < 8; ++q) add(x[q], tk[q]);
     }
-    for (; i < mine; ++i) {
-        const int tk = __builtin_amdgcn_readlane(token, i);
-        add(w[(size_t)tk * np], tk);
+    if (i < mine) {                                          // the last few together, too: one by one they took as long as all before
+        uint4 x[8];
+        int tk[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            tk[q] = __builtin_amdgcn_readlane(token, min(i + q, mine - 1));
+            x[q] = w[(size_t)tk[q] * np];
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (i + q < mine) add(x[q], tk[q]);
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) red[wave][e][lane] = acc[e];
@@ -1578,13 +1586,14 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
         layout_scan_kernel<<<(C + 63) / 64, 512, 0, st>>>(d_hist, nw, C, x->n);
         layout_offsets_kernel<<<1, 1024, 0, st>>>(x->n, C, x->off, d_coff, d_poff, d_chunks);
         layout_scatter_kernel<<<nw, 64, (size_t)C * 4, st>>>(d_labels, d_hist, x->off, V, C, label_bits, x->perm);
-        const dim3 kgrid(max_chunks, (d + 511) / 512), fgrid(C, (d + 255) / 256);
+        const int nslices = (d + 511) / 512;
+        const dim3 kgrid(max_chunks * nslices), fgrid(C, (d + 255) / 256);
         if (sph) {
-            centroid_chunk_kernel<true><<<kgrid, 256, 0, st>>>(d_W, x->perm, x->off, d_coff, d_poff, d_chunks, d, C, d_nrm, x->mu, d_sums, d_part);
+            centroid_chunk_kernel<true><<<kgrid, 256, 0, st>>>(d_W, x->perm, x->off, d_coff, d_poff, d_chunks, d, C, nslices, d_nrm, x->mu, d_sums, d_part);
             centroid_finish_kernel<true><<<fgrid, 256, 0, st>>>(x->off, d_poff, d, 0, d_part, x->mu, d_sums);
             direction_finish_kernel<<<C, 256, 0, st>>>(d_sums, x->off, d, last ? 1 : 0, x->mu);
         } else {
-            centroid_chunk_kernel<false><<<kgrid, 256, 0, st>>>(d_W, x->perm, x->off, d_coff, d_poff, d_chunks, d, C, nullptr, x->mu, nullptr, d_part);
+            centroid_chunk_kernel<false><<<kgrid, 256, 0, st>>>(d_W, x->perm, x->off, d_coff, d_poff, d_chunks, d, C, nslices, nullptr, x->mu, nullptr, d_part);
             centroid_finish_kernel<false><<<fgrid, 256, 0, st>>>(x->off, d_poff, d, last ? 1 : 0, d_part, x->mu, nullptr);
         }
         if (hipGetLastError() != hipSuccess) { csv_set_error("launch of the centroid kernels failed"); return fail(CSV_EHIP); }
