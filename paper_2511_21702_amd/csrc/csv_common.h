@@ -43,17 +43,15 @@ enum { ST_ACTIVE = 0, ST_DONE = 1, ST_FALLBACK = 2, ST_INVALID = 3 };
 // of sequence b in round r's work list; [CNT_CHUNKS + r*CSV_MAX_BATCH + b] chunk blocks of round r's certification
 // that have published their partial results; [CNT_ARRIVE + b] blocks of the round-0 kernel that have finished their
 // share of sequence b's seed rows; [CNT_R0_DONE] sequences whose round 0 is settled (certified, planned, handed over
-// or invalid): what the blocks that run the tail inside the round-0 launch wait for; [CNT_DEEP] some sequence has a round after round 1.
+// or invalid): what the blocks that run the tail inside the round-0 launch wait for.
 // All are zeroed by the bound kernel at the start of a step.
-enum { CNT_FALLBACK = 0, CNT_ABORT = 1, CNT_TAIL_NEEDED = 2, CNT_R0_DONE = 3, CNT_DEEP = 4, CNT_BARRIER = 16, CNT_TILES = 64, CNT_CHUNKS = 64 + CSV_MAX_ROUNDS * CSV_MAX_BATCH,
+enum { CNT_FALLBACK = 0, CNT_ABORT = 1, CNT_TAIL_NEEDED = 2, CNT_R0_DONE = 3, CNT_BARRIER = 16, CNT_TILES = 64, CNT_CHUNKS = 64 + CSV_MAX_ROUNDS * CSV_MAX_BATCH,
        CNT_ARRIVE = 64 + 2 * CSV_MAX_ROUNDS * CSV_MAX_BATCH, CNT_TOTAL = 64 + (2 * CSV_MAX_ROUNDS + 1) * CSV_MAX_BATCH,
        // not reset: bit i = whether the step i steps back needed anything after round 0 (kept behind the reset range)
        CNT_HISTORY = CNT_TOTAL,
        // not reset either: set when a step gave up while logits were still on their way through the round-0 slots
        // (the next step's bound kernel then refills the slots with the "empty" pattern before anything reads them)
-       CNT_SLOTS_DIRTY = CNT_TOTAL + 1,
-       // nor this: bit i = whether the step i steps back had a round after round 1
-       CNT_DEEP_HISTORY = CNT_TOTAL + 2, CNT_ALLOC = CNT_TOTAL + 16 };
+       CNT_SLOTS_DIRTY = CNT_TOTAL + 1, CNT_ALLOC = CNT_TOTAL + 16 };
 
 // A cluster's position in the bound order is carried by one 64-bit key: monotone image of U_c in the high word,
 // ~c in the low word.  Larger key = larger bound, equal bounds = smaller cluster id first.  Empty clusters have key 0.
@@ -89,7 +87,9 @@ struct csv_workspace {
     int round0_capacity;               // blocks of the round-0 kernel that are resident together
     int split_min_B;                   // > 0: batches of at least this many sequences run the tail as one launch per
                                        // phase; 0: decided per step from the recent steps' history
-    int* h_history;                    // two pinned host words the bound kernel copies the history to (read without a sync)
+    int* h_history;                    // two pinned host words (read without a sync): the history, which the bound kernel copies here; set where the tail
+                                       // kernel met a round that the host had not launched
+    int deep_hold;                     // steps that still launch the rounds after round 1 because of that
     int* d_history;                    // the same words as the device sees them
     size_t tail_lds;                   // its dynamic LDS
     size_t fused_lds;                  // dynamic LDS of the launch that holds round 0 and the tail together

@@ -114,13 +114,8 @@ __device__ __forceinline__ void reset_step_counters(int* counters, int B, int nt
         const unsigned lo = ((old << 1) | (unsigned)(counters[CNT_TAIL_NEEDED] != 0)) & 0xffffu;
         const unsigned hi = (((old >> 16) << 1) | (unsigned)(counters[CNT_FALLBACK] != 0)) & 0x7fffu;
         const int h = (int)(lo | (hi << 16));
-        const int deep = (counters[CNT_DEEP_HISTORY] << 1 | (counters[CNT_DEEP] != 0)) & 0xffff;
         counters[CNT_HISTORY] = h;
-        counters[CNT_DEEP_HISTORY] = deep;
-        if (host_history) {
-            host_history[0] = h;
-            host_history[1] = deep;
-        }
+        if (host_history) *host_history = h;
     }
     __syncthreads();             // called by every thread of one block: the zeroing below must not overtake the reads
     for (int i = threadIdx.x; i < CNT_TILES + rows * B; i += nthreads) {
@@ -399,8 +394,8 @@ __device__ __forceinline__ void split3_bf16(const float4& x0, const float4& x1, 
 }
 
 #define BOUND_TILES_PER_BLOCK 8   // waves of a block: each owns 16 clusters, all share the block's K slice (and its h in LDS)
-#define BOUND_MFMA_MIN_B 5       // from this many sequences on the MFMA product is faster than the vector kernel, whose reads of h
-                                 // from LDS (eight sequences: 128 bytes per lane for 16 bytes of a centroid) bound it: 15 vs 23 us at B = 8
+#define BOUND_MFMA_MIN_B 5       // from this many sequences on the matrix cores: a lane of the vector kernels reads h of every sequence for each piece of a
+                                 // centroid (eight sequences: 128 bytes for 16, 23 us against 15 at C = 2048, d = 5120)
 #ifndef BOUND_BLOCK_TARGET
 #define BOUND_BLOCK_TARGET 256   // (groups of cluster tiles x K slices) aimed at: one block per compute unit (64..2048 swept)
 #endif
@@ -3207,11 +3202,11 @@ __device__ __forceinline__ void tail_device(const StepArgs& a, const FullArgs& f
     extern __shared__ __align__(16) u64 arena[];
     const int tid = threadIdx.x;
     if (a.counters[CNT_TAIL_NEEDED] == 0) return;      // the common case at small batches: one word, no reduction
-    if (from >= a.max_rounds && a.counters[CNT_FALLBACK] == 0) return;
+    if (from == CSV_MAX_ROUNDS && a.counters[CNT_FALLBACK] == 0) return;
     // is any sequence waiting for round 0 (a seed prefix too large for the round-0 blocks), for round 1 or for the
     // full product?  Every block reads the same, settled values.
     int mine0 = 0, mine1 = 0;
-    if (tid < a.B && from < a.max_rounds) {
+    if (tid < a.B && from < CSV_MAX_ROUNDS) {
         mine0 = from ? 0 : a.counters[CNT_TILES + tid];
         mine1 = a.counters[CNT_TILES + (from ? from : 1) * CSV_MAX_BATCH + tid];
     }
@@ -3230,7 +3225,7 @@ __device__ __forceinline__ void tail_device(const StepArgs& a, const FullArgs& f
                 tiles = block_sum_i(mine, s.redi);
             }
             if (tiles == 0) break;
-            if (r > 1 && block == 0 && tid == 0) a.counters[CNT_DEEP] = 1;
+            if (from && block == 0 && tid == 0) a.host_history[1] = 1;      // the host launches these rounds for the next steps
         }
         gemv_tiles_device(a, r, reinterpret_cast<uint4*>(arena), gs, block, nblocks);
         if (!grid_barrier(a.counters, 2 * r, nblocks, s_flag, a.spin_limit)) return;
@@ -3260,7 +3255,7 @@ __device__ __forceinline__ void tail_device(const StepArgs& a, const FullArgs& f
     }
 }
 
-// from: the first round it runs, those before were launches of their own (0: as queued; max_rounds: the fallback only)
+// from: the first round it runs, those before were launches of their own (0: as queued; CSV_MAX_ROUNDS: the fallback only)
 __global__ __launch_bounds__(TAIL_THREADS) void tail_kernel(StepArgs a, FullArgs f, int from) {
     __shared__ SeqShared s;
     __shared__ GemvShared gs;
@@ -3331,7 +3326,6 @@ __global__ __launch_bounds__(TAIL_THREADS, 2) void round_gemv_kernel(StepArgs a,
     extern __shared__ __align__(16) u64 arena[];
     __shared__ GemvShared gs;
     if (a.counters[CNT_TAIL_NEEDED] == 0) return;
-    if (r > 1 && blockIdx.x == 0 && threadIdx.x < a.B && a.counters[CNT_TILES + r * CSV_MAX_BATCH + threadIdx.x] != 0) a.counters[CNT_DEEP] = 1;
     gemv_tiles_device(a, r, reinterpret_cast<uint4*>(arena), gs, blockIdx.x, gridDim.x);
 }
 
@@ -3818,6 +3812,7 @@ extern "C" int csv_full_logits(csv_workspace* ws, const csv_index* idx, const ui
     return launch_full(idx, d_h, ws->all_list, B, d_logits, idx->V, 1, ws->fb_logits, (hipStream_t)stream);
 }
 
+#define DEEP_HOLD 256
 extern "C" int csv_decode_step(csv_workspace* ws, const csv_index* idx, const uint16_t* d_h, int B,
                                const csv_step_params* p, const csv_step_out* o, void* stream) {
     int rc = check_pair(ws, idx, d_h, B);
@@ -3905,9 +3900,16 @@ extern "C" int csv_decode_step(csv_workspace* ws, const csv_index* idx, const ui
         // the three fallback phases as launches of their own only while fallbacks occur; otherwise one launch
         // of the single kernel restricted to them, which returns at once when nobody fell back
         fb_launches = (history >> 16) != 0;         // any of the last 15 steps
-        // rounds after round 1 likewise: while none of the last 16 steps had one (and none a fallback), that single kernel takes them, too (a pair of
-        // launches that return at once takes 4-6 us: steps with max_rounds = 4, 203 sequences at C = 294 78.7 -> 69.5 us, 232 at C = 1054 157 -> 139)
-        deep = fb_launches || (((volatile int*)ws->h_history)[1] & 0xffff) != 0;
+        // Rounds after round 1 likewise: that single kernel takes them, too, unless it met one lately, and says so in the second pinned word (a pair of launches
+        // that return at once takes 4-6 us: steps with max_rounds = 4, 203 sequences at C = 294 78.7 -> 69.5 us, 232 at C = 1054 157 -> 139; a round
+        // inside it costs two grid barriers, so it is tried again after DEEP_HOLD steps only).
+        volatile int* met = ws->h_history + 1;
+        if (*met) {
+            *met = 0;
+            ws->deep_hold = DEEP_HOLD;
+        }
+        deep = fb_launches || ws->deep_hold > 0;
+        if (split && max_rounds > 2 && ws->deep_hold > 0) --ws->deep_hold;
     }
     // blocks per sequence in round 0: as many as stay resident together (a second wave of blocks would double the
     // kernel's time), at most ROUND0_NB_MAX, and no more than the largest possible seed prefix needs at
@@ -3965,7 +3967,7 @@ extern "C" int csv_decode_step(csv_workspace* ws, const csv_index* idx, const ui
                 fb_final_kernel<<<B, SEQ_THREADS, (size_t)CAND_OFF + CAND_BYTES, st>>>(a);
                 CSV_LAUNCH_CHECK("fb_final_kernel");
             } else {
-                tail_kernel<<<ws->tail_grid, TAIL_THREADS, ws->tail_lds, st>>>(a, f, launched);
+                tail_kernel<<<ws->tail_grid, TAIL_THREADS, ws->tail_lds, st>>>(a, f, launched < max_rounds ? launched : CSV_MAX_ROUNDS);
                 CSV_LAUNCH_CHECK("tail_kernel");
             }
         }
