@@ -8,6 +8,8 @@ from ._harness import Case
 
 pytestmark = pytest.mark.gpu
 
+torch = pytest.importorskip("torch")
+
 
 # several rows per wave of round 0, the widest rows, seed prefixes of one and of several clusters,
 # indexes around 1024 and 4096 clusters, prefixes of more than 256 rows, plans that open up to 512 clusters (a
@@ -24,4 +26,34 @@ def test_round_plans_match_the_oracle(V, d, C, B, k, eps, comb, noise, mix, spli
     case.ws.set_tail_split(split)
     t = case.run_steps(case.hidden(), k, eps, V, comb, f"plans V={V} d={d} C={C} B={B}", max_rounds=4)
     assert not t.mismatch, "\n".join(t.mismatch[:5])
+    case.close()
+
+
+def test_later_rounds_in_every_launch_form():
+    """Steps with a round after round 1 and no fallback, repeated: first the single tail kernel, then rounds 0 and 1 as launches with the tail kernel for
+    the rest, then (that kernel has met a round) all rounds as launches.  Every form gives the bits of the fixed one-launch-per-phase form."""
+    r = synth.small_recipe("ladder-forms", V=6000, d=136, C=60, B=1, steps=60, k=8, eps=2e-3, h_mode="mix", sizes="zipf", row_noise=2.0)
+    case = Case(r, seed=21, K_cap=6000, want_W64=False)
+    csv, dh = case.csv, case.csv.bits_to_device(case.hidden())
+
+    def step(ws, s, K_max):
+        buf = csv.make_step_buffers(case.gidx, 1, r.k, r.eps, K_max, max_rounds=6, delta_clusters=2, relax=True)
+        csv.csv_decode_step(ws, case.gidx, dh[s], buf)
+        torch.cuda.synchronize()
+        return [x.cpu() for x in (buf.ids, buf.logits, buf.lse, buf.flags, buf.n_rows, buf.n_clusters, buf.rounds)]
+
+    case.ws.set_tail_split(1)
+    late = []
+    for K_max in (600, 1500, 3000, 4500):
+        for s in range(60):
+            want = step(case.ws, s, K_max)
+            if int(want[6][0]) > 2 and not int(want[3][0]) & csv.FLAG_FALLBACK:
+                late.append((s, K_max, want))
+    assert late, "no step with a later round and no fallback among the inputs"
+    for s, K_max, want in late[:6]:
+        ws = csv.CsvWorkspace(case.gidx, 1, 6000)                  # no history: the step is the single kernel first
+        for i in range(12):
+            got = step(ws, s, K_max)
+            assert all(torch.equal(x, y) for x, y in zip(got, want)), (s, K_max, i)
+        ws.free()
     case.close()
