@@ -689,7 +689,8 @@ __global__ __launch_bounds__(AS_THREADS) void assign_exact_kernel(const uint16_t
 
 // Centroids rounded to bf16 (nearest even) in fragment order, out[(kb * CT + ct) * 64 + lane], lane = (cluster li of the tile, k
 // group g); zeros past C and past d.  With them cn[c] = ||mu_c||^2 and left[c], what a score against the rounded centroid can be off by per unit of ||W_i||: 2 (||mu_c -
-// bf16(mu_c)|| + 2^-17 ||mu_c||), the second term for the float32 sums; sums in float64.  (A centroid that is not finite is nobody's nearest by cn alone: left = 0.)
+// bf16(mu_c)|| + 2^-17 ||mu_c||), the second term for the float32 sums; sums in float64.  (A centroid that rounding takes out of range has no finite
+// score: left = 0.  One with a value that is not finite: left is not a number.)
 // unit != 0 (spherical clustering): every direction counts as of length one, so the arg-min is the largest cosine.
 // One block per tile of 16 clusters, a k-block per wave at a time.  Also empties the lists.
 __global__ __launch_bounds__(1024) void round_centroids_kernel(const float* __restrict__ mu, int d, int C, int CT, int nkb, int unit, as_uintx4_t* __restrict__ out,
@@ -728,7 +729,7 @@ __global__ __launch_bounds__(1024) void round_centroids_kernel(const float* __re
         }
     cn[ct * 16 + threadIdx.x] = unit ? 1.f : (float)nn;
     const double off = 2.0 * (sqrt(rr) + 0x1p-17 * sqrt(nn)) * (1.0 + 1e-6);
-    left[ct * 16 + threadIdx.x] = nn + off < (double)INFINITY ? (float)off : 0.f;
+    left[ct * 16 + threadIdx.x] = nn < (double)INFINITY ? (off < (double)INFINITY ? (float)off : 0.f) : NAN;
 }
 
 // The three smallest of a set of words, ascending.
@@ -767,8 +768,9 @@ __device__ __forceinline__ Low3 low3_trade(bool odd, const Low3& first, const Lo
 // V = 128256, d = 4096, C = 1024 (256 x 256 tiles): 0.80 ms = 1.35 PFLOP/s with the three best, 0.86 with the best and the norms; the product alone 0.77,
 // without the two halves 0.91, with W by 64-byte pieces 0.85, through registers 1.10 ms; without any requests in the loop it would take 0.61-0.64 ms.
 // FINAL: the centroids are bf16 values (rows of W, the first assignment's), so the scores are exact; the best (distance key, cluster) of a row over the
-// block's columns goes to win[column block * V + row] as assign_exact_kernel leaves it (a score that is not finite counts as none of a number, which is what
-// zero pieces make of a row with infinities).  norms: ||W_i||, a little more than that, for the assignments to come.
+// block's columns goes to win[column block * V + row] as assign_exact_kernel leaves it: there the zero pieces make "not a number" of every score of a row with
+// a value that is not finite.  So where a score is not finite, the block looks whether the row itself is (a sum may overflow, too, and minus infinity is the
+// nearest).  norms: ||W_i||, a little more than that, for the assignments to come.
 template <int MT, int NT, bool FINAL>
 __global__ __launch_bounds__(AS_THREADS) void assign_near_kernel(const uint16_t* __restrict__ W, const int32_t* __restrict__ order, const as_uintx4_t* __restrict__ Bs,
                                                                  const float* __restrict__ cn, int V, int d, int C, int CT,
@@ -884,6 +886,14 @@ __global__ __launch_bounds__(AS_THREADS) void assign_near_kernel(const uint16_t*
     float norm[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) norm[t] = c0 + 16 * t < C ? cn[c0 + 16 * t] : INFINITY;        // past C: in nobody's reach
+    float off[NT];
+    bool odd_c[NT];                                          // the centroid is not finite: FINAL, a seed row, nobody's nearest
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const float x = c0 + 16 * t < C ? left[c0 + 16 * t] : 0.f;
+        odd_c[t] = x != x;
+        off[t] = odd_c[t] ? 0.f : x;
+    }
     if constexpr (FINAL) {
         if (norms && bn == 0) {
 #pragma unroll
@@ -894,16 +904,42 @@ __global__ __launch_bounds__(AS_THREADS) void assign_near_kernel(const uint16_t*
             }
         }
         unsigned long long* best = reinterpret_cast<unsigned long long*>(as_lds);        // [2 MT 16 rows][4]
+        int* odd = reinterpret_cast<int*>(best + 2 * MT * 16 * 4);                        // per row: it has a value that is not finite; then: look for such
+        if (tid <= 2 * MT * 16) odd[tid] = 0;
+        __syncthreads();
+        bool look = false;
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) look = look || (c0 + 16 * t < C && !(fabsf(norm[t] - 2.f * acc[m][t][r]) < INFINITY));
+        if (look) odd[2 * MT * 16] = 1;
+        __syncthreads();
+        if (odd[2 * MT * 16]) {
+            for (int r = wave; r < 2 * MT * 16 && row0 + r < V; r += AS_THREADS / 64) {
+                const as_uintx4_t* w = reinterpret_cast<const as_uintx4_t*>(W + (size_t)(row0 + r) * d);         // order is NULL here
+                bool any = false;
+                for (int q = lane; q < nq; q += 64) {
+                    const as_uintx4_t x = w[q];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) any = any || (x[e] & 0x7f80u) == 0x7f80u || (x[e] & 0x7f800000u) == 0x7f800000u;
+                }
+                if (__any(any) && lane == 0) odd[r] = 1;
+            }
+            __syncthreads();
+        }
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 unsigned bk = 0xffffffffu;
                 int bc = 0x7fffffff;
+                const int none = odd[(wm * MT + m) * 16 + 4 * g + r];
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
                     const float v = norm[t] - 2.f * acc[m][t][r];
-                    const unsigned kx = c0 + 16 * t >= C ? 0xffffffffu : fabsf(v) < INFINITY ? fkey(v + 0.0f) : 0xffc00000u;
+                    const unsigned kx = c0 + 16 * t >= C ? 0xffffffffu : none || odd_c[t] ? 0xffc00000u : fkey(v + 0.0f);
                     if (kx < bk) {                           // tiles in ascending cluster order: a tie keeps the smaller id
                         bk = kx;
                         bc = c0 + 16 * t;
@@ -924,9 +960,6 @@ __global__ __launch_bounds__(AS_THREADS) void assign_near_kernel(const uint16_t*
             const int p = min(row0 + tid, V - 1);
             wnorm[tid] = (float)norms[order ? order[p] : p];
         }
-        float off[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) off[t] = c0 + 16 * t < C ? left[c0 + 16 * t] : 0.f;
         __syncthreads();
 #pragma unroll
         for (int m = 0; m < MT; ++m) {

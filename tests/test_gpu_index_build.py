@@ -201,3 +201,26 @@ def test_first_assignment_from_rows_then_rounded_centroids():
     e = g.export()
     g.free()
     assert sorted(e["perm"].tolist()) == list(range(V)) and e["n"].sum() == V
+
+
+@pytest.mark.parametrize("seed_value", [4.0, np.inf])
+def test_sums_that_overflow_still_find_the_nearest(seed_value):
+    """Finite rows whose products with a seed row overflow float32: minus infinity is the nearest, plus infinity farther than every finite score.  A row with
+    a value that is not finite is nearest to none (the smallest id), a seed row with one is nobody's nearest."""
+    import paper_2511_21702_amd as csv
+    V, d, C = 700, 264, 5
+    W = np.zeros((V, d), np.float32)
+    W[0, 0], W[1, 0], W[2, 1], W[4, 2] = 1e19, -1e19, 1.0, 8.0                   # seeds; ||1e19||^2 is finite
+    W[3, 3], W[3, 4] = seed_value, 1.0
+    kind = np.arange(V) % 4
+    kind[:C] = -1
+    W[kind == 0, 0], W[kind == 1, 0], W[kind == 2, 1], W[kind == 3, 2] = 1e20, -1e20, 2.0, 7.0
+    W[100, 9], W[101, 260] = -np.inf, np.nan
+    want = np.choose(np.maximum(kind, 0), [0, 1, 2, 4])
+    want[:C] = [0, 1, 2, 3 if np.isfinite(seed_value) else 0, 4]
+    want[100:102] = 0
+    log(f"sums that overflow, seed {seed_value}")
+    g = csv.csv_build_index(csv.bits_to_device(synth.f32_to_bf16_bits(W)), None, C, init_rows=np.arange(C, dtype=np.int32), iters=0)
+    got = _labels(g.export())
+    g.free()
+    assert np.array_equal(got, want), np.flatnonzero(got != want)[:8]
