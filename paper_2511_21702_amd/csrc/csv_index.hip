@@ -690,7 +690,7 @@ __global__ __launch_bounds__(AS_THREADS) void assign_exact_kernel(const uint16_t
 // Centroids rounded to bf16 (nearest even) in fragment order, out[(kb * CT + ct) * 64 + lane], lane = (cluster li of the tile, k
 // group g); zeros past C and past d.  With them cn[c] = ||mu_c||^2 and left[c], what a score against the rounded centroid can be off by per unit of ||W_i||: 2 (||mu_c -
 // bf16(mu_c)|| + 2^-17 ||mu_c||), the second term for the float32 sums; sums in float64.  (A centroid that rounding takes out of range has no finite
-// score: left = 0.  One with a value that is not finite: left is not a number.)
+// score: left = 0.  One with a value that is not finite, which counts as zero here: left is not a number.)
 // unit != 0 (spherical clustering): every direction counts as of length one, so the arg-min is the largest cosine.
 // One block per tile of 16 clusters, a k-block per wave at a time.  Also empties the lists.
 __global__ __launch_bounds__(1024) void round_centroids_kernel(const float* __restrict__ mu, int d, int C, int CT, int nkb, int unit, as_uintx4_t* __restrict__ out,
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(1024) void round_centroids_kernel(const float* __re
             const float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const uint32_t u = __float_as_uint(v[e]), r = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
+                const uint32_t u = __float_as_uint(v[e]), r = (u & 0x7f800000u) == 0x7f800000u ? 0u : (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
                 const double whole = (double)v[e], rest = whole - (double)__uint_as_float(r);
                 nn = fma(whole, whole, nn);
                 rr = fma(rest, rest, rr);
@@ -887,7 +887,7 @@ __global__ __launch_bounds__(AS_THREADS) void assign_near_kernel(const uint16_t*
 #pragma unroll
     for (int t = 0; t < NT; ++t) norm[t] = c0 + 16 * t < C ? cn[c0 + 16 * t] : INFINITY;        // past C: in nobody's reach
     float off[NT];
-    bool odd_c[NT];                                          // the centroid is not finite: FINAL, a seed row, nobody's nearest
+    bool odd_c[NT];                                          // the centroid is not finite: FINAL, a seed row, nobody's nearest; else in everybody's reach
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const float x = c0 + 16 * t < C ? left[c0 + 16 * t] : 0.f;
@@ -960,6 +960,8 @@ __global__ __launch_bounds__(AS_THREADS) void assign_near_kernel(const uint16_t*
             const int p = min(row0 + tid, V - 1);
             wnorm[tid] = (float)norms[order ? order[p] : p];
         }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) norm[t] = odd_c[t] ? -INFINITY : norm[t];
         __syncthreads();
 #pragma unroll
         for (int m = 0; m < MT; ++m) {

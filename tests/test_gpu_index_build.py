@@ -224,3 +224,40 @@ def test_sums_that_overflow_still_find_the_nearest(seed_value):
     got = _labels(g.export())
     g.free()
     assert np.array_equal(got, want), np.flatnonzero(got != want)[:8]
+
+
+def _both_ways(W, labels, C, iters, scale=1.0):
+    """Labels of the rows of W after `iters` iterations from the given labels, found with rounded centroids first and with the exact product alone: the head
+    once over is too small for the former, the same rows twice over, whose clusters have the same means, are not.  Bit for bit the same."""
+    import paper_2511_21702_amd as csv
+    V, d = W.shape
+    assert C >= 384 and V * d * C < 20e9 <= 2 * V * d * C                         # assign_near_pays of the library
+    out = []
+    for w, l in ((W, labels), (torch.cat([W, W]), np.concatenate([labels, labels]))):
+        g = csv.csv_build_index(w, None, C, init_labels=l, iters=iters)
+        out.append(_labels(g.export()))
+        g.free()
+    assert np.array_equal(out[1][:V], out[1][V:])
+    bad = np.flatnonzero(out[0] != out[1][:V])
+    assert bad.size == 0, (bad.size, bad[:8], out[0][bad[:8]], out[1][bad[:8]])
+    return out[0]
+
+
+def _planted(V, d, C, rng, gen, centre_of=lambda labels: labels, labels=None):
+    """Rows around the centres that centre_of gives their labels; every cluster has a row.  (W bf16 on the device, labels)"""
+    if labels is None:
+        labels = rng.integers(0, C, V).astype(np.int32)
+        labels[:C] = np.arange(C)
+    centers = torch.randn(C, d, device="cuda", generator=gen) * (4.0 / d ** 0.5)
+    noise = torch.randn(V, d, device="cuda", generator=gen) * (0.05 / d ** 0.5)
+    return (centers[torch.from_numpy(centre_of(labels)).cuda().long()] + noise).to(torch.bfloat16).contiguous(), labels
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_a_centroid_that_is_not_finite_either_way(value):
+    V, d, C = 24000, 520, 1500
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    W, labels = _planted(V, d, C, np.random.default_rng(11), gen)
+    W[7000, 13] = value
+    log(f"a centroid of {value}")
+    _both_ways(W, labels, C, 1)
