@@ -469,9 +469,9 @@ __global__ __launch_bounds__(256) void radius_finish_kernel(const float* __restr
 // Lloyd assignment: labels[i] = argmin_c ||W_i - mu_c||^2, ties to the smaller cluster id.
 // ||W_i - mu_c||^2 = ||W_i||^2 - 2 <W_i,mu_c> + ||mu_c||^2 and the first term does not depend on c, so the work is the
 // dense contraction [V x d] . [d x C].  W is bf16, the centroids are float32: split exactly into three bf16 pieces, three MFMAs
-// per k-block give a float32-exact product (assign_exact_kernel), at three times the matrix work of bf16 centroids.
-// One piece settles nearly every row: with mu_c rounded to bf16 a score is off by at most 2 ||W_i|| ||mu_c - bf16(mu_c)||, and only
-// centroids within twice that of the best can be the nearest.  So, where there is enough work to pay for the passes
+// per k-block give exact products (assign_exact_kernel), at three times the matrix work of bf16 centroids.
+// One piece settles nearly every row: with mu_c rounded to bf16 a score is off by at most 2 ||W_i|| ||mu_c - bf16(mu_c)|| and what the float32 sums
+// differ by (round_centroids_kernel), and only centroids within twice that of the best can be the nearest.  So, where there is enough work to pay for the passes
 // (assign_near_pays): round_centroids_kernel rounds the centroids and measures what the rounding left out; assign_near_kernel scores
 // all pairs with the rounded ones and keeps, per row and group of clusters, the three best; assign_pick_kernel labels the rows with one
 // centroid in reach and lists the others' pairs, which assign_pairs_kernel scores exactly; rows with many in reach, or
@@ -688,8 +688,13 @@ __global__ __launch_bounds__(AS_THREADS) void assign_exact_kernel(const uint16_t
 }
 
 // Centroids rounded to bf16 (nearest even) in fragment order, out[(kb * CT + ct) * 64 + lane], lane = (cluster li of the tile, k
-// group g); zeros past C and past d.  With them cn[c] = ||mu_c||^2 and left[c], what a score against the rounded centroid can be off by per unit of ||W_i||: 2 (||mu_c -
-// bf16(mu_c)|| + 2^-17 ||mu_c||), the second term for the float32 sums; sums in float64.  (A centroid that rounding takes out of range has no finite
+// group g); zeros past C and past d.  With them cn[c] = ||mu_c||^2 and left[c], what a score with the rounded centroid can differ by from the exact product's
+// per unit of ||W_i||: 2 (||mu_c - bf16(mu_c)|| + (0.501 d + 64) 2^-24 ||mu_c||).  The second term is for the float32 sums of both:  an MFMA adds its 32 products
+// to the accumulator in four groups of eight, each rounded to nearest (measured: off by 4 2^-24 of the accumulator at most, which is reached); no partial sum
+// is larger than ||W_i|| ||mu_c||, and there are d/8 such roundings with one piece (of a centroid up to 1 + 2^-8 times as long), 3 d/8 with three.  Inside a group,
+// products are cut off where the bits of the largest end: at most 16 2^-24 of the sum of |products| in all, for either way (4 seen).  The other 32: the
+// norm of W_i in float32 and the scores' own last operations (in proportion to cn[c] only where that is less than about 2 ||W_i|| ||mu_c||: a centroid farther
+// out is in nobody's reach, unless it is the best: assign_pick_kernel adds 2^-20 of it).  Sums in float64.  (A centroid that rounding takes out of range has no finite
 // score: left = 0.  One with a value that is not finite, which counts as zero here: left is not a number.)
 // unit != 0 (spherical clustering): every direction counts as of length one, so the arg-min is the largest cosine.
 // One block per tile of 16 clusters, a k-block per wave at a time.  Also empties the lists.
@@ -728,7 +733,7 @@ __global__ __launch_bounds__(1024) void round_centroids_kernel(const float* __re
             rr += red[1][w][threadIdx.x + 16 * q];
         }
     cn[ct * 16 + threadIdx.x] = unit ? 1.f : (float)nn;
-    const double off = 2.0 * (sqrt(rr) + 0x1p-17 * sqrt(nn)) * (1.0 + 1e-6);
+    const double off = 2.0 * (sqrt(rr) + (0.501 * d + 64.0) * 0x1p-24 * sqrt(nn)) * (1.0 + 1e-6);
     left[ct * 16 + threadIdx.x] = nn < (double)INFINITY ? (off < (double)INFINITY ? (float)off : 0.f) : NAN;
 }
 

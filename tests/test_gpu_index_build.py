@@ -261,3 +261,30 @@ def test_a_centroid_that_is_not_finite_either_way(value):
     W[7000, 13] = value
     log(f"a centroid of {value}")
     _both_ways(W, labels, C, 1)
+
+
+def test_sums_that_drift_apart():
+    """Products that move a float32 sum by a little less than half a unit each with the centroid's bf16 pieces and by a little more with the rounded centroid:
+    d / 8 units apart in the end, which outweighs all else that the rounding leaves out.  The exact product's label is found all the same."""
+    V, d, C = 3000, 16384, 384
+    W = torch.zeros(V, d)
+    W[:, 0] = 1.0
+    labels = np.zeros(V, np.int32)
+    x = torch.full((d,), 2.0 ** -7)
+    x[:8] = 0.0
+    x[:2] = 1.0
+    # centroid 0: a quarter above the bf16 value 2^-20 by three quarters of its last bit, so that a group of eight products with x adds 2^-24 (the tie: 1 stays
+    # 1) and 0.75 2^-31 (lost) by pieces, 2^-24 (1 + 2^-7) rounded (1 goes up by 2^-23)
+    W[0:4, 8:] = 2.0 ** -20 * (1 + 2.0 ** -7)
+    W[3, 8:] = 2.0 ** -20
+    W[4:8, 1] = 2.0 ** -14                                                       # centroid 1: exactly representable, a score lower by 2^-13 than 0's
+    labels[4:8] = 1
+    W[8:208], W[8:108] = -3.0 * x, x                                             # the rows in question, from a cluster with mean -x
+    labels[8:208] = 2
+    rest = torch.arange(208, V)
+    labels[208:] = 3 + (np.arange(208, V) - 208) % (C - 3)
+    W[rest, 0] = 0.0
+    W[rest, 8 + torch.from_numpy(labels[208:]).long()] = 8.0                     # far away
+    log("sums that drift apart")
+    got = _both_ways(W.to(torch.bfloat16).cuda(), labels, C, 1)
+    assert (got[8:108] == 1).all()                                               # by pieces; the float64 sum lies between the two
