@@ -512,20 +512,23 @@ __device__ __forceinline__ unsigned row16_min_u(unsigned v) {
     return v;
 }
 
+// ||mu_c||^2.  The sum is that of round_centroids_kernel: 512 partial sums, value k to the partial sum k % 512, which meet as a binary
+// tree, neighbours first.
 // unit != 0 (spherical clustering): every direction counts as of length one, so the arg-min is the largest cosine
-__global__ __launch_bounds__(256) void centroid_norm_kernel(const float* __restrict__ mu, int d, int unit, float* __restrict__ cn) {
-    __shared__ double red[4];
+__global__ __launch_bounds__(512) void centroid_norm_kernel(const float* __restrict__ mu, int d, int unit, float* __restrict__ cn) {
+    __shared__ double red[8];
     const int c = blockIdx.x, tid = threadIdx.x;
     if (unit) {
         if (tid == 0) cn[c] = 1.f;
         return;
     }
     double acc = 0.0;
-    for (int j = tid; j < d; j += 256) acc += (double)mu[(size_t)c * d + j] * (double)mu[(size_t)c * d + j];
-    acc = wave_sum_d(acc);
+    for (int j = tid; j < d; j += 512) acc = fma((double)mu[(size_t)c * d + j], (double)mu[(size_t)c * d + j], acc);
+#pragma unroll
+    for (int o = 1; o < CSV_WAVE; o <<= 1) acc += __shfl_xor(acc, o, CSV_WAVE);
     if ((tid & 63) == 0) red[tid >> 6] = acc;
     __syncthreads();
-    if (tid == 0) cn[c] = (float)((red[0] + red[1]) + (red[2] + red[3]));
+    if (tid == 0) cn[c] = (float)(((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7])));
 }
 
 // The three bf16 pieces of every centroid value in fragment order: out[((kb * CT + ct) * 3 + piece) * 64 + lane], lane =
@@ -697,13 +700,14 @@ __global__ __launch_bounds__(AS_THREADS) void assign_exact_kernel(const uint16_t
 // out is in nobody's reach, unless it is the best: assign_pick_kernel adds 2^-20 of it).  Sums in float64.  (A centroid that rounding takes out of range has no finite
 // score: left = 0.  One with a value that is not finite, which counts as zero here: left is not a number.)
 // unit != 0 (spherical clustering): every direction counts as of length one, so the arg-min is the largest cosine.
-// One block per tile of 16 clusters, a k-block per wave at a time.  Also empties the lists.
+// One block per tile of 16 clusters, a k-block per wave at a time; cn is summed in the order of centroid_norm_kernel, so that a score has the same bits
+// whichever of the two made its norm.  Also empties the lists.
 __global__ __launch_bounds__(1024) void round_centroids_kernel(const float* __restrict__ mu, int d, int C, int CT, int nkb, int unit, as_uintx4_t* __restrict__ out,
                                                               float* __restrict__ cn, float* __restrict__ left, int* __restrict__ counts) {
-    __shared__ double red[2][16][64];
+    __shared__ double red[2][16][16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ct = blockIdx.x, c = ct * 16 + (lane & 15), g = lane >> 4;
     if (ct == 0 && threadIdx.x < 3) counts[threadIdx.x] = 0;
-    double nn = 0.0, rr = 0.0;
+    double n8[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, rr = 0.0;
     for (int kb = wave; kb < nkb; kb += 16) {
         const int k = kb * 32 + g * 8;
         as_uintx4_t x = {0, 0, 0, 0};
@@ -715,23 +719,35 @@ __global__ __launch_bounds__(1024) void round_centroids_kernel(const float* __re
             for (int e = 0; e < 8; ++e) {
                 const uint32_t u = __float_as_uint(v[e]), r = (u & 0x7f800000u) == 0x7f800000u ? 0u : (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
                 const double whole = (double)v[e], rest = whole - (double)__uint_as_float(r);
-                nn = fma(whole, whole, nn);
+                n8[e] = fma(whole, whole, n8[e]);
                 rr = fma(rest, rest, rr);
                 x[e >> 1] |= e & 1 ? r : r >> 16;
             }
         }
         out[((size_t)kb * CT + ct) * 64 + lane] = x;
     }
-    red[0][wave][lane] = nn;
-    red[1][wave][lane] = rr;
+    double nn = ((n8[0] + n8[1]) + (n8[2] + n8[3])) + ((n8[4] + n8[5]) + (n8[6] + n8[7]));
+#pragma unroll
+    for (int o = 16; o < 64; o <<= 1) {
+        nn += __shfl_xor(nn, o, CSV_WAVE);
+        rr += __shfl_xor(rr, o, CSV_WAVE);
+    }
+    if (g == 0) {
+        red[0][wave][lane] = nn;
+        red[1][wave][lane] = rr;
+    }
     __syncthreads();
     if (threadIdx.x >= 16 || ct * 16 + threadIdx.x >= C) return;
-    nn = rr = 0.0;
-    for (int w = 0; w < 16; ++w)
-        for (int q = 0; q < 4; ++q) {
-            nn += red[0][w][threadIdx.x + 16 * q];
-            rr += red[1][w][threadIdx.x + 16 * q];
-        }
+    double part[16];
+#pragma unroll
+    for (int w = 0; w < 16; ++w) part[w] = red[0][w][threadIdx.x];
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1)
+#pragma unroll
+        for (int w = 0; w < 16; w += 2 * o) part[w] += part[w + o];
+    nn = part[0];
+    rr = 0.0;
+    for (int w = 0; w < 16; ++w) rr += red[1][w][threadIdx.x];
     cn[ct * 16 + threadIdx.x] = unit ? 1.f : (float)nn;
     const double off = 2.0 * (sqrt(rr) + (0.501 * d + 64.0) * 0x1p-24 * sqrt(nn)) * (1.0 + 1e-6);
     left[ct * 16 + threadIdx.x] = nn < (double)INFINITY ? (off < (double)INFINITY ? (float)off : 0.f) : NAN;
@@ -1474,7 +1490,7 @@ static int round_centroids(const AssignPlan& p, const AssignRun& r, int unit) {
     return CSV_OK;
 }
 static int assign_exact(const AssignPlan& p, const AssignRun& r, int unit) {
-    centroid_norm_kernel<<<r.C, 256, 0, r.st>>>(r.mu, r.d, unit, r.cn);
+    centroid_norm_kernel<<<r.C, 512, 0, r.st>>>(r.mu, r.d, unit, r.cn);
     CSV_LAUNCH_CHECK("centroid_norm_kernel");
     const int nkb = (r.d + 31) / 32;
     split_centroids_kernel<<<dim3(p.CT, (nkb + 3) / 4), 256, 0, r.st>>>(r.mu, r.d, r.C, p.CT, nkb, nullptr, r.pieces);

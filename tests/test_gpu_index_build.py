@@ -288,3 +288,20 @@ def test_sums_that_drift_apart():
     log("sums that drift apart")
     got = _both_ways(W.to(torch.bfloat16).cuda(), labels, C, 1)
     assert (got[8:108] == 1).all()                                               # by pieces; the float64 sum lies between the two
+
+
+def test_a_centroid_norm_that_rounds_by_the_order_of_its_sum():
+    """||mu||^2 = 1 + 2^-24 and six terms of 2^-54, which in some orders are lost one by one in float64 and in others lift the sum over the float32 tie.  The
+    score of centroid 0 is -1 or -1 + 2^-23, of centroid 1 exactly -1: the label must not depend on which kernel took the norm."""
+    V, d, C = 24000, 520, 1500
+    W = torch.zeros(V, d)
+    labels = (np.arange(V) % C).astype(np.int32)
+    far = torch.arange(V)
+    W[far, 8 + torch.from_numpy(labels % 512).long()] = 8.0 * (1 + torch.from_numpy(labels // 512).float())
+    W[labels == 0] = 0.0
+    W[labels == 1] = 0.0
+    W[labels == 0, 0] = W[labels == 1, 0] = 1.0
+    W[labels == 0, 1] = 2.0 ** -12
+    W[labels == 0, 2:8] = 2.0 ** -27
+    log("a norm that rounds by the order of its sum")
+    _both_ways(W.to(torch.bfloat16).cuda(), labels, C, 1)
