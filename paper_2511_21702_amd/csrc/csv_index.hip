@@ -921,6 +921,7 @@ __global__ __launch_bounds__(AS_THREADS) void assign_near_kernel(const uint16_t*
             for (int i = 0; i < NM; ++i) {                   // lane (li, g) holds a quarter of row li's squares
                 const float x = ss[i] + __shfl_xor(ss[i], 16, CSV_WAVE), y = x + __shfl_xor(x, 32, CSV_WAVE);
                 const int row = row0 + (wm * MT + wn * NM + i) * 16 + li;
+                // (up to d = 2^16 the sum, d / 8 steps in float32 to a lane, is short of less than that)
                 if (g == 0 && row < V) norms[row] = sqrt((double)y) * (1.0 + 0x1p-10);
             }
         }

@@ -116,11 +116,11 @@ def _nearest(W, mu, labels, tol):
     assert (over <= tol * W.norm(dim=1) * mu.norm(dim=1).max()).all(), over.max().item()
 
 
-# Heads large enough for the rounded centroids to come first (384 clusters, V d C of 20e9): 256 x 256 and 128 x 256 tiles, d a multiple of 64 and
-# not, V and C inside a tile.  "shared": a planted centre's rows are dealt to one to three clusters, whose centroids then differ in the noise, and some clusters
-# hold two centres (pairs); "crowd": one centre's rows are dealt to 90 clusters besides (whole groups and rows for all centroids); "alike": all rows
-# equal (given up: every score ties, the smallest id wins).  Two scores that float32 sums of exact products can tell apart are told apart right: a sum's error
-# is at most (d / 8 + 16) 2^-24 ||row|| ||mu||, 2^-15 at d = 4096; a third of that at the most has been seen.
+# Heads large enough for the rounded centroids to come first (384 clusters, V d C of 20e9), in most of which they are given up at the first look, so that the
+# exact product makes the labels: 256 x 256 and 128 x 256 tiles, d a multiple of 64 and not, V and C inside a tile.  "shared": a planted centre's rows are
+# dealt to one to three clusters, whose centroids then differ in the noise, and some clusters hold two centres; "crowd": one centre's rows are dealt to 90
+# clusters besides; "alike": all rows equal (every score ties, the smallest id wins).  Two scores that float32 sums of exact products can tell apart are
+# told apart right: within the error of a sum with d / 8 roundings to 2^-24 (the exact product has 3 d / 8; a third of the tolerance at the most has been seen).
 @pytest.mark.parametrize("V,d,C,spherical", [(70001, 264, 1200, False), (70001, 264, 1200, True), (16000, 3200, 400, False), (45003, 1096, 500, False)])
 @pytest.mark.parametrize("kind", ["shared", "crowd", "alike"])
 def test_rounded_centroids_find_the_nearest(V, d, C, kind, spherical):
@@ -226,15 +226,16 @@ def test_sums_that_overflow_still_find_the_nearest(seed_value):
     assert np.array_equal(got, want), np.flatnonzero(got != want)[:8]
 
 
-def _both_ways(W, labels, C, iters, scale=1.0):
-    """Labels of the rows of W after `iters` iterations from the given labels, found with rounded centroids first and with the exact product alone: the head
+def _both_ways(W, labels, C, iters, spherical=False):
+    """Labels of the rows of W after `iters` iterations from the given labels (None: from the first C rows), found with rounded centroids first and with the exact product alone: the head
     once over is too small for the former, the same rows twice over, whose clusters have the same means, are not.  Bit for bit the same."""
     import paper_2511_21702_amd as csv
     V, d = W.shape
     assert C >= 384 and V * d * C < 20e9 <= 2 * V * d * C                         # assign_near_pays of the library
     out = []
-    for w, l in ((W, labels), (torch.cat([W, W]), np.concatenate([labels, labels]))):
-        g = csv.csv_build_index(w, None, C, init_labels=l, iters=iters)
+    for n in (1, 2):
+        start = {"init_rows": np.arange(C, dtype=np.int32)} if labels is None else {"init_labels": np.tile(labels, n)}
+        g = csv.csv_build_index(torch.cat([W] * n), None, C, iters=iters, spherical=spherical, **start)
         out.append(_labels(g.export()))
         g.free()
     assert np.array_equal(out[1][:V], out[1][V:])
@@ -305,3 +306,67 @@ def test_a_centroid_norm_that_rounds_by_the_order_of_its_sum():
     W[labels == 0, 2:8] = 2.0 ** -27
     log("a norm that rounds by the order of its sum")
     _both_ways(W.to(torch.bfloat16).cuda(), labels, C, 1)
+
+
+def _second_look(W, labels, C, spherical, copies):
+    """What the first look at the rounded scores finds, in float64: rows by the centroids in reach, pairs, and the cost that decides whether it is given up."""
+    V, d = W.shape
+    x, lab = W.double(), torch.from_numpy(labels).cuda().long()
+    norm = x.norm(dim=1)
+    rows = x / norm[:, None] if spherical else x
+    mu = torch.zeros(C, d, dtype=torch.float64, device="cuda").index_add_(0, lab, rows)
+    mu = (mu / mu.norm(dim=1, keepdim=True) if spherical else mu / torch.bincount(lab, minlength=C)[:, None]).float().double()
+    near = mu.float().to(torch.bfloat16).double()
+    left = 2.0 * ((mu - near).norm(dim=1) + (0.501 * d + 64.0) * 2.0 ** -24 * mu.norm(dim=1))       # round_centroids_kernel of the library
+    low = (1.0 if spherical else (mu * mu).sum(1)) - 2.0 * x @ near.T - norm[:, None] * left
+    reach = low <= (low + 2.0 * norm[:, None] * left).min(1, keepdim=True).values
+    pad = torch.nn.functional.pad(reach, (0, -C % 64)).reshape(V, -1, 64).sum(2)                     # groups of 64 clusters
+    size = torch.full((pad.shape[1],), 64, device="cuda")
+    size[-1] -= -C % 64
+    whole = (pad >= 3).any(1)
+    total = torch.where(pad >= 3, size, pad).sum(1)
+    n = {"settled": (total == 1) & ~whole, "few": (total > 1) & (total <= 16) & ~whole, "many": (total > 16) & (total <= 160) & ~whole,
+         "whole": whole & (total <= 160), "wide": total > 160}                                       # AS_PAIRS_CHEAP, AS_PAIRS_ROW
+    n = {k: copies * int(v.sum()) for k, v in n.items()}
+    V *= copies
+    cap = min(2 * V, V * C // 512)
+    few, other = (copies * int(total[m].sum()) for m in ((total > 1) & (total <= 16) & ~whole, whole & (total <= 160) | (total > 16) & (total <= 160)))
+    listed = n["wide"] + max(0, few + other - cap) / 2        # a row that finds the list full has two pairs at least
+    cost = 0.4 + 6.5e9 / (V * d * C) + 100.0 * min(few + other, cap) / (V * C) + 1.15 * listed / V
+    return n, few, cap, cost
+
+
+# Rows with more than one centroid in reach, found by the exact scores of pairs, of whole groups and of rows with all centroids: the labels are those of the
+# exact product, bit for bit.  "few": pairs of clusters, in one group of 64 and in two, share a centre; "many": twenty clusters do, two of a group at most;
+# "whole": three of a group do; "wide": two hundred do (rows for all centroids); "full": more pairs than their list holds (the rest of the rows for all
+# centroids).  The scratch of the shape with 4096 clusters does not fit into the index's copy of W.
+@pytest.mark.parametrize("V,d,C,kind,spherical", [
+    (24000, 1064, 750, "few", False), (24000, 1064, 750, "few", True), (24000, 1064, 750, "many", False), (24000, 1064, 750, "whole", False),
+    (24000, 1064, 750, "wide", False), (6000, 8192, 400, "few", False), (6000, 8192, 400, "wide", False), (25000, 1992, 400, "full", False),
+    (18000, 264, 4096, "few", False), (18000, 264, 4096, "wide", False)])
+def test_rows_that_take_a_second_look(V, d, C, kind, spherical):
+    import paper_2511_21702_amd as csv
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    rng = np.random.default_rng(d)
+    labels, centre = None, np.arange(C)
+    if kind == "few":
+        centre[1:32:8], centre[64:96] = centre[0:32:8], centre[0:32]
+    elif kind == "many":
+        centre[:640].reshape(10, 64)[:, :2] = 0
+    elif kind == "whole":
+        centre[[1, 2, 65, 66]] = [0, 0, 64, 64]
+    elif kind == "wide":
+        centre[:200] = 0
+        small = np.repeat(np.arange(200, dtype=np.int32), 4)
+        labels = np.concatenate([small, 200 + np.arange(V - small.size, dtype=np.int32) % (C - 200)])
+    else:
+        centre[1:int(0.42 * C):2] = centre[0:int(0.42 * C):2]
+    W, labels = _planted(V, d, C, rng, gen, lambda l: centre[l], labels)
+    n, pairs, cap, cost = _second_look(W, labels, C, spherical, 2)
+    log(f"second look V={V} d={d} C={C} {kind} spherical={spherical}: {n}, {pairs} pairs of {cap}, cost {cost:.2f}")
+    assert cost < 0.81 and n["settled"] > V / 2                                   # the rounded centroids are kept (given up: 0.85)
+    assert n[{"full": "few"}.get(kind, kind)] > 100 and (pairs > 1.02 * cap) == (kind == "full")
+    if C == 4096:
+        assert C // 256 * 48 > 2 * d                                              # words a row / its share of the copy of W, bytes
+    for iters in (1, 2):
+        _both_ways(W, labels, C, iters, spherical)
