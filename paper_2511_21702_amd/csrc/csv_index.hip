@@ -772,6 +772,21 @@ __device__ __forceinline__ Low3 low3_trade(bool odd, const Low3& first, const Lo
     return low3_merge(keep, low3_move<CTRL>(give));
 }
 
+// The row tiles of a launch.  The first assignment with rounded centroids looks at a sample of them first: part 1, one tile of every `every`, at changing
+// places among them; part 2, the others; part 0, all.
+struct AssignRows {
+    int part, every, tiles;              // tiles: of all rows
+    __host__ __device__ int count() const {
+        const int sample = (tiles + every - 1) / every;
+        return part == 0 ? tiles : part == 1 ? sample : tiles - sample;
+    }
+    __device__ int tile(int i) const {
+        if (part == 0) return i;
+        const int e = part == 1 ? i : i / (every - 1), k = i - e * (every - 1), at = min(e * 11 % every, tiles - 1 - e * every);
+        return e * every + (part == 1 ? at : k < at ? k : k + 1);
+    }
+};
+
 // Score word of a (row, cluster) pair: the monotone key of the score with the cluster's place in its group in the low AS_ID_BITS bits.
 #define AS_ID_BITS 6
 #define AS_ID_MASK 63u
@@ -795,7 +810,7 @@ __device__ __forceinline__ Low3 low3_trade(bool odd, const Low3& first, const Lo
 template <int MT, int NT, bool FINAL>
 __global__ __launch_bounds__(AS_THREADS) void assign_near_kernel(const uint16_t* __restrict__ W, const int32_t* __restrict__ order, const as_uintx4_t* __restrict__ Bs,
                                                                  const float* __restrict__ cn, int V, int d, int C, int CT,
-                                                                 int ncol, int ntot, const float* __restrict__ left, double* __restrict__ norms, unsigned* __restrict__ words, unsigned long long* __restrict__ win) {
+                                                                 int ncol, AssignRows rows, const float* __restrict__ left, double* __restrict__ norms, unsigned* __restrict__ words, unsigned long long* __restrict__ win) {
     extern __shared__ as_uintx4_t as_lds[];
     constexpr int ASZ = 2 * MT * 128, BSZ = 4 * NT * 64;                                  // 16-byte pieces per stage of W, of the centroids
     constexpr int AP = ASZ / AS_THREADS, BP = BSZ / AS_THREADS, AH = AP / 2, OPEN = 2 * (AH + BP);
@@ -806,8 +821,8 @@ __global__ __launch_bounds__(AS_THREADS) void assign_near_kernel(const uint16_t*
     // blocks are dealt round-robin to the eight XCDs: each gets a contiguous run of tiles, columns fastest, so that the
     // blocks that share rows of W and the centroids of a k-block sit behind one L2
     const int tile = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    if (tile >= ntot) return;
-    const int bn = tile % ncol, row0 = tile / ncol * (2 * MT * 16);
+    if (tile >= rows.count() * ncol) return;
+    const int bn = tile % ncol, row0 = rows.tile(tile / ncol) * (2 * MT * 16);
     const int nq = d >> 3, nst = (d + 63) >> 6, nkb = 2 * nst;
     const int piece = (lane & 7) ^ (lane >> 3);              // of the eight of a line; rows go to LDS by eights, so lane >> 3 is the row's low bits
     const as_uintx4_t* ap[AP];
@@ -1019,7 +1034,9 @@ __global__ __launch_bounds__(AS_THREADS) void assign_near_kernel(const uint16_t*
 // smallest upper bound.  One centroid in reach: the label.  Else the label is ~(a place in rows) until the place's win word holds the nearest: the row's
 // pairs with the centroids in reach are listed (all of a group whose third is in reach), or, where they are more than AS_PAIRS_ROW, or more than
 // the list holds, or the reach is not finite, the place itself is.  Whole groups and more than AS_PAIRS_CHEAP
-// pairs are listed only while less than an eighth of the list is in use: on heads with many such rows the exact product is the cheaper way.
+// pairs are listed only while less than an eighth of the list is in use: on heads with many such rows the exact product is the cheaper way.  (The blocks of a
+// launch mostly run together and see an empty list; those of part 2 see the sample's pairs, which were found to be few enough: no such limit.)
+// most: pairs that the list may hold so far, for a sample its share.
 // counts: {rows, pairs, rows for all centroids}.  64 rows per block, four threads per row; a block takes its places and pairs in one piece, so
 // that pairs of neighbours in the row order, which share centroids, are neighbours in the list.
 // Bound by reading the words: V = 128256, C = 1024 in 30 us.
@@ -1028,12 +1045,13 @@ __global__ __launch_bounds__(AS_THREADS) void assign_near_kernel(const uint16_t*
 #define AS_PAIRS_SHARE 2      // the list holds that many pairs per row of W, or C / 512 of them: a pair takes as long as 100 columns of the exact product
 __global__ __launch_bounds__(256) void assign_pick_kernel(const int32_t* __restrict__ order, const float* __restrict__ cn, const float* __restrict__ left,
                                                           const double* __restrict__ nrm, const unsigned* __restrict__ words, int ngroups, int group, int V, int C,
-                                                          int cap, int32_t* __restrict__ labels, int* __restrict__ counts, int* __restrict__ rows,
+                                                          AssignRows tiles, int tile_rows, int most, int cap, int32_t* __restrict__ labels, int* __restrict__ counts, int* __restrict__ rows,
                                                           unsigned long long* __restrict__ win, int2* __restrict__ pairs, int* __restrict__ list) {
     __shared__ float s_lim[4][64];
     __shared__ int s_cnt[4][64], s_one[4][64], s_place[64], s_pair[64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, row = min((int)blockIdx.x * 64 + lane, V - 1);
-    const bool mine = blockIdx.x * 64 + lane < V;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, per_tile = tile_rows >> 6;
+    const int at = tiles.tile(blockIdx.x / per_tile) * tile_rows + (blockIdx.x % per_tile) * 64 + lane, row = min(at, V - 1);
+    const bool mine = at < V;
     const int token = order ? order[row] : row;
     const float wr = (float)nrm[token];
     float lim = INFINITY;
@@ -1085,7 +1103,7 @@ __global__ __launch_bounds__(256) void assign_pick_kernel(const int32_t* __restr
         }
         const bool settled = finite && total == 1 && one >= 0;
         const int used = __builtin_amdgcn_readfirstlane(counts[1]);
-        bool few = mine && !settled && finite && total <= AS_PAIRS_ROW && ((one >= 0 && total <= AS_PAIRS_CHEAP) || used < cap >> 3);
+        bool few = mine && !settled && finite && total <= AS_PAIRS_ROW && ((one >= 0 && total <= AS_PAIRS_CHEAP) || used < (tiles.part == 2 ? most : most >> 3));
         int upto = few ? total : 0;                          // inclusive sum over the lanes
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -1101,7 +1119,7 @@ __global__ __launch_bounds__(256) void assign_pick_kernel(const int32_t* __restr
         }
         place0 = __builtin_amdgcn_readfirstlane(place0);
         pair0 = __builtin_amdgcn_readfirstlane(pair0);
-        if (pair0 > cap - npairs) {                          // the list is full: what is left of it holds no pairs
+        if (pair0 > most - npairs) {                         // the list is full (of the sample's share of it): these places of it hold no pairs
             for (int i = pair0 + lane; i < cap && i < pair0 + npairs; i += 64) pairs[i] = make_int2(0, -1);
             few = false;
         }
@@ -1122,9 +1140,9 @@ __global__ __launch_bounds__(256) void assign_pick_kernel(const int32_t* __restr
     }
     __syncthreads();
     if (s_place[lane] < 0) return;
-    int at = s_pair[lane] + s_cnt[wave][lane];
+    int next = s_pair[lane] + s_cnt[wave][lane];
     reached([&](int c, int n) {
-        for (int i = 0; i < n; ++i) pairs[at++] = make_int2(s_place[lane], c + i);
+        for (int i = 0; i < n; ++i) pairs[next++] = make_int2(s_place[lane], c + i);
     });
 }
 
@@ -1478,10 +1496,10 @@ static int launch_exact(const AssignPlan& p, const AssignRun& r) {
     return CSV_OK;
 }
 template <int MT, int NT, bool FINAL>
-static int launch_near(const AssignPlan& p, const AssignRun& r, const int32_t* order) {
+static int launch_near(const AssignPlan& p, const AssignRun& r, const int32_t* order, const AssignRows& rows) {
     constexpr int lds = (3 * 2 * MT * 128 + 4 * 4 * NT * 64) * 16;
     CSV_HIP(hipFuncSetAttribute((const void*)assign_near_kernel<MT, NT, FINAL>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-    assign_near_kernel<MT, NT, FINAL><<<(p.ntot + 7) / 8 * 8, AS_THREADS, lds, r.st>>>(r.W, order, r.rounded, r.cn, r.V, r.d, r.C, p.CT, p.ncol, p.ntot, r.left, r.nrm, r.words, r.win);
+    assign_near_kernel<MT, NT, FINAL><<<(rows.count() * p.ncol + 7) / 8 * 8, AS_THREADS, lds, r.st>>>(r.W, order, r.rounded, r.cn, r.V, r.d, r.C, p.CT, p.ncol, rows, r.left, r.nrm, r.words, r.win);
     CSV_LAUNCH_CHECK("assign_near_kernel");
     return CSV_OK;
 }
@@ -1502,27 +1520,41 @@ static int assign_exact(const AssignPlan& p, const AssignRun& r, int unit) {
 static int assign_first(const AssignPlan& p, const AssignRun& r) {
     const int rc = round_centroids(p, r, 0);
     if (rc) return rc;
-    return p.kind == 0 ? launch_near<8, 4, true>(p, r, nullptr) : p.kind == 1 ? launch_near<4, 4, true>(p, r, nullptr) : launch_near<4, 2, true>(p, r, nullptr);
+    const AssignRows all = {0, 2, p.ntot / p.ncol};
+    return p.kind == 0 ? launch_near<8, 4, true>(p, r, nullptr, all) : p.kind == 1 ? launch_near<4, 4, true>(p, r, nullptr, all) : launch_near<4, 2, true>(p, r, nullptr, all);
 }
-// order: the rows by the clusters so far.  give_up: looked at once the rounded scores are in, at the cost of a wait; set, and no labels made, where they
-// leave so many rows for the exact product that it is cheaper over all rows.
+// order: the rows by the clusters so far.  give_up: looked at once the rounded scores of a sample of the rows are in (of all, where those are few tiles), at
+// the cost of a wait; set, and no labels made, where they leave so many rows for the exact product that it is cheaper over all rows.  Builds of skewed heads,
+// us without any look / looking at all rows / at the sample: V = 26000, d = 800, C = 1024, 2 iterations 660 / 690 / 660; V = 40000, d = 1024, C = 512, 4 iterations
+// 1050 / 1080 / 1050.
 static int assign_near(const AssignPlan& p, const AssignRun& r, int unit, const int32_t* order, bool* give_up) {
     int rc = round_centroids(p, r, unit);
     if (rc) return rc;
-    rc = p.kind == 0 ? launch_near<8, 4, false>(p, r, order) : launch_near<4, 4, false>(p, r, order);
-    if (rc) return rc;
-    assign_pick_kernel<<<(r.V + 63) / 64, 256, 0, r.st>>>(order, r.cn, r.left, r.nrm, r.words, p.ncol * 4, p.nt * 16, r.V, r.C, r.cap, r.labels, r.counts, r.rows,
-                                                          r.win, r.pairs, r.list);
-    CSV_LAUNCH_CHECK("assign_pick_kernel");
-    if (give_up) {
-        int n[3] = {0, 0, 0};
-        CSV_HIP(hipMemcpyAsync(n, r.counts, 12, hipMemcpyDeviceToHost, r.st));
-        CSV_HIP(hipStreamSynchronize(r.st));
-        // in passes of the exact product over all rows: the rounded scores and the look through them; 30 us of launches; a pair takes as long as 100
-        // columns of a row; listed rows go through smaller tiles
-        const double work = (double)r.V * r.d * r.C;
-        *give_up = 0.4 + 6.5e9 / work + 100.0 * std::min(n[1], r.cap) / ((double)r.V * r.C) + 1.15 * n[2] / r.V > 0.85;
-        if (*give_up) return CSV_OK;
+    const int tiles = p.ntot / p.ncol, tile_rows = p.kind == 0 ? 256 : 128;
+    // the sample: as few tiles as take, with the others in a launch of their own, no more rounds over the compute units than all in one launch
+    auto rounds = [&](int t) { return (t * p.ncol + 255) / 256; };
+    int every = 16;
+    while (every > 1 && rounds((tiles + every - 1) / every) + rounds(tiles - (tiles + every - 1) / every) > rounds(tiles)) --every;
+    for (int part = give_up && tiles >= 32 && every > 1 ? 1 : 0; part < 3; ++part) {
+        const AssignRows rows = {part, every, tiles};
+        const double share = (double)rows.count() / tiles;
+        const int most = part == 1 ? (int)(r.cap * share) : r.cap;       // pairs so far
+        rc = p.kind == 0 ? launch_near<8, 4, false>(p, r, order, rows) : launch_near<4, 4, false>(p, r, order, rows);
+        if (rc) return rc;
+        assign_pick_kernel<<<rows.count() * (tile_rows / 64), 256, 0, r.st>>>(order, r.cn, r.left, r.nrm, r.words, p.ncol * 4, p.nt * 16, r.V, r.C, rows, tile_rows, most, r.cap, r.labels,
+                                                                              r.counts, r.rows, r.win, r.pairs, r.list);
+        CSV_LAUNCH_CHECK("assign_pick_kernel");
+        if (give_up && part < 2) {
+            int n[3] = {0, 0, 0};
+            CSV_HIP(hipMemcpyAsync(n, r.counts, 12, hipMemcpyDeviceToHost, r.st));
+            CSV_HIP(hipStreamSynchronize(r.st));
+            // in passes of the exact product over all rows: the rounded scores and the look through them; 30 us of launches; a pair takes as long as 100
+            // columns of a row; listed rows go through smaller tiles
+            const double work = (double)r.V * r.d * r.C, V = r.V * share;
+            *give_up = 0.4 + 6.5e9 / work + 100.0 * std::min(n[1], most) / (V * r.C) + 1.15 * n[2] / V > 0.85;
+            if (*give_up) return CSV_OK;
+        }
+        if (part == 0) break;
     }
     assign_pairs_kernel<<<1024, 256, 0, r.st>>>(r.W, r.mu, r.cn, r.d, r.cap, r.counts, r.pairs, r.rows, r.win);
     CSV_LAUNCH_CHECK("assign_pairs_kernel");
