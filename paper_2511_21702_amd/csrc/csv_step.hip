@@ -3436,18 +3436,33 @@ static hipError_t raise_lds(int dev, int which, const void* fn, size_t bytes) {
 // slices) fills the device, a whole number of request chunks per slice, a slice's h within BOUND_LDS_KB of LDS, at most
 // BOUND_KS_MAX slices (the partial buffer holds KS x B x C floats).  B decides how many sequence tiles a block carries.
 static int bound_mfma_nt(int B) { return B > 32 ? 4 : (B > 16 ? 2 : 1); }
-static void bound_mfma_plan(int C, int d, int B, int& KS, int& kbs, bool many) {
+static void bound_mfma_plan(int C, int d, int B, int& KS, int& kbs, bool many, bool m16 = false) {
     const int tiles = (C + 15) / 16, groups = (tiles + BOUND_TILES_PER_BLOCK - 1) / BOUND_TILES_PER_BLOCK, nkb = (d + 31) / 32;
-    // many: more than 64 sequences, whose groups of 64 are blocks of their own, in fewer and longer slices: their partial sums are what the launch
-    // writes and the next one reads (us, C = 1024, d = 4096, 256 sequences: 26.1 -> 18.8; C = 2000, d = 5000, 130: 28.7 -> 25.6)
-    KS = (BOUND_BLOCK_TARGET / (many ? (B + 63) / 64 : 1) + groups - 1) / groups;
+    KS = (BOUND_BLOCK_TARGET + groups - 1) / groups;
     if (KS > BOUND_KS_MAX) KS = BOUND_KS_MAX;
     if (KS > nkb) KS = nkb;
     kbs = (nkb + KS - 1) / KS;
     kbs = (kbs + BOUND_PIPE - 1) / BOUND_PIPE * BOUND_PIPE;     // whole chunks
-    const int cap = (many ? BOUND_LDS_KB_MANY : BOUND_LDS_KB) / bound_mfma_nt(B) / BOUND_PIPE * BOUND_PIPE;
+    const int cap = BOUND_LDS_KB / bound_mfma_nt(B) / BOUND_PIPE * BOUND_PIPE;
     if (kbs > cap) kbs = cap;                                   // d <= 8192: 256 k-blocks in at most 32 slices of 8 always fit
     KS = (nkb + kbs - 1) / kbs;
+    if (!many) return;
+    // More than 64 sequences, whose groups of 64 are blocks of their own: of the slice lengths that need no more slices than that, the one that costs least.
+    // A block takes 0.5 us per k-block of float32 centroids, 0.25 of bf16, in as many rounds over the compute units as the blocks make; partial sums, which
+    // the launch writes and the next one reads, 2.2 us a million (fitted to 90 plans; over 110 shapes, B = 65..256, the choice is 0.4 % slower than the
+    // best on average, 5 % at most).  us with the slices of 64 sequences / always the longest / now: C = 1024, d = 4096, 256 sequences 26.8 / 18.9 / 19.1,
+    // 130 18.7 / 20.1 / 17.3; C = 3614, d = 2184, 65 22.3 / 23.7 / 20.8; bf16 C = 2000, d = 5000, 72 15.0 / 16.4 / 15.0, 150 20.4 / 18.3 / 18.3.
+    const int most = KS;
+    double best = 0.0;
+    for (int len = BOUND_PIPE; len <= BOUND_LDS_KB_MANY / bound_mfma_nt(B); len += BOUND_PIPE) {
+        const int n = (nkb + len - 1) / len, rounds = (groups * n * ((B + 63) / 64) + BOUND_BLOCK_TARGET - 1) / BOUND_BLOCK_TARGET;
+        const double cost = rounds * len * (m16 ? 0.25 : 0.5) + 2.2e-6 * n * B * C;
+        if (n <= most && (best == 0.0 || cost <= best)) {
+            best = cost;
+            KS = n;
+            kbs = len;
+        }
+    }
 }
 
 // Where the one launch beats the product over K slices and the launch that adds them up (us, two launches / one; B = 16): its blocks are as many as tiles
@@ -3473,7 +3488,7 @@ static int launch_bounds_kernel(const StepArgs& a, float* U, float* hn, int rese
             return CSV_OK;
         }
         int KS, kbs;
-        bound_mfma_plan(a.C, a.d, a.B, KS, kbs, a.B > 64);
+        bound_mfma_plan(a.C, a.d, a.B, KS, kbs, a.B > 64, a.mu16 != nullptr);
         dim3 grid((tiles + BOUND_TILES_PER_BLOCK - 1) / BOUND_TILES_PER_BLOCK, KS, (a.B + 63) / 64);
         const int nt = bound_mfma_nt(a.B);
         const size_t lds = (size_t)kbs * nt * 1024;
