@@ -152,7 +152,8 @@ def main() -> int:
         print(json.dumps({"metric": "offline k-means index build", "config": {"workload": f"{r.name}: V={r.V} d={r.d} C={r.C}"},
                           "lloyd_iterations": args.kmeans, "assignments": args.kmeans + 1, "seconds": sec,
                           "distance_product_TFLOPs_useful": flops / sec / 1e12,
-                          "note": "whole build: every assignment (MFMA distance product, three bf16 pieces per float32 centroid value), "
+                          "note": "whole build: every assignment (MFMA distance product: seed rows as they are; centroids as three bf16 "
+                                  "pieces per float32 value, or rounded to bf16 first and the exact scores where that leaves a choice), "
                                   "layout, row gather, centroid means; then radii and metadata",
                           "empty_clusters": int((e["n"] == 0).sum()), "largest_cluster": int(e["n"].max()), "purity_vs_planted": float(purity)}))
         return 0
@@ -336,7 +337,8 @@ def main() -> int:
         tot = float(np.median([a.elapsed_time(b) for a, b in evs])) - base
         return tot * 1e3
 
-    bound_name = "bound_rows_kernel" if r.B <= 4 else "bound_mfma_kernel + bound_finish_kernel"
+    # three and four sequences with bf16 centroids, and more: one of several kernels by C and d
+    bound_name = "bound_rows_kernel" if r.B <= (2 if args.bf16_centroids else 4) else "cluster bounds"
     bound_warm_us = time_bounds(200)
     flush_buf = torch.empty(768 << 20, dtype=torch.uint8, device="cuda").zero_()
     bound_cold_us = time_bounds(30, flush_buf)

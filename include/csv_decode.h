@@ -265,7 +265,10 @@ int csv_workspace_set_spin_limit(csv_workspace* ws, int polls);
  * least two of the last eight needed the tail (a device-side bit history mirrored to pinned host memory and read
  * without synchronising, so it may lag a few steps).  min_batch > 0 fixes the choice: batches of at least min_batch
  * sequences use per-phase launches, smaller ones the single kernel (a value above CSV_MAX_BATCH: always the single
- * kernel; 1: always per-phase).  Results do not depend on the choice.
+ * kernel; 1: always per-phase).  Results do not depend on the choice.  Within the per-phase form, rounds after round 1 and the
+ * fallback are launches only while recent steps had some; otherwise one kernel covers them and returns at once.
+ * A step captured into a graph keeps the form that it had when it was captured, for every replay: where the steps to
+ * come differ from those before the capture, fix the choice first (1 where later rounds or fallbacks are common).
  */
 int csv_workspace_set_tail_split(csv_workspace* ws, int min_batch);
 

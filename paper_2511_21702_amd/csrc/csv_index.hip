@@ -184,8 +184,8 @@ __global__ __launch_bounds__(64) void layout_scatter_kernel(const int32_t* __res
 // copy is made once, after the last iteration), in float64.  Block = 4 waves x 512 columns; a wave takes every fourth
 // row, eight rows requested at once; the waves' sums are added in wave order.  A cluster of one chunk is finished here, the
 // chunks of a larger one leave partial sums for centroid_finish_kernel, so a cluster of any size is spread over the device.
-// Bound by reading W: 208 us at V = 128256, d = 4096 = 5.05 TB/s, the blocks of one chunk side by side (of one column slice 215).  (One thread per column going down all rows of a cluster: 1.7 ms at V = 128256, d = 4096 with clusters of
-// up to 2900 rows, plus 0.38 ms for a gathered copy per iteration.)
+// Bound by reading W: V = 128256, d = 4096 in 208 us = 5.05 TB/s, with the blocks of one chunk side by side.  (With those of one column slice side by side
+// 215 us; one thread per column going down all rows of a cluster 1.7 ms with clusters of up to 2900 rows, and 0.38 ms for a gathered copy per iteration.)
 // UNIT (spherical clustering): rows are divided by their norm nrm[token], the sums themselves go to out_sum.
 template <bool UNIT>
 __global__ __launch_bounds__(256) void centroid_chunk_kernel(const uint16_t* __restrict__ W, const int32_t* __restrict__ perm, const int32_t* __restrict__ off,

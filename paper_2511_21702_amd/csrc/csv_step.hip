@@ -1,7 +1,8 @@
 // Per-step kernels of the certified sub-vocabulary LM-head path and the entry points that enqueue them.
 //
-//   bound_rows_kernel, bound_kernel / bound_mfma_kernel + bound_finish_kernel
-//                      U[b,c] = <mu_c,h_b> + R_c ||h_b|| + bmax_c  for up to four / more sequences   (Eq. "cluster_bound")
+//   bound_rows_kernel, bound_kernel / bound_tile_kernel / bound_mfma_kernel + bound_finish_kernel
+//                      U[b,c] = <mu_c,h_b> + R_c ||h_b|| + bmax_c  for up to four sequences / up to 16 with short rows or many
+//                      clusters / more                                                          (Eq. "cluster_bound")
 //   round0_kernel      per sequence: shortest prefix of the bound order holding >= max(k,1) rows, next bound, log tail
 //                      mass (Algorithm 1: queue, PopMax); logits of the prefix rows of W' (Algorithm 1: sparse GEMV);
 //                      top-k, log-sum-exp and both certificates, or the plan of the next round
@@ -3465,11 +3466,16 @@ static void bound_mfma_plan(int C, int d, int B, int& KS, int& kbs, bool many, b
     }
 }
 
-// Where the one launch beats the product over K slices and the launch that adds them up (us, two launches / one; B = 16): its blocks are as many as tiles
-// (4096 clusters are one round of them) and each reads its rows alone, so rows must be short or tiles many.  bf16: C = 1024, d = 1024 and f32 9.2 / 6.6, d = 4096
-// 9.4 / 7.9, C = 4096, d = 5120 13.3 / 10.7, but d = 6144 9.6 / 9.9, d = 8192 10.4 / 12.0 and two rounds C = 8192, d = 4096 16.1 / 17.3, d = 1024 9.6 / 7.2.
-// float32: d = 2048 9.8 / 8.6, C = 4096 11.3 / 8.8, but C = 1024, d = 4096 9.3 / 11.8, C = 2048, d = 5120 13.6 / 14.5; many tiles: C = 4096, d = 3000 13.6 / 11.0, d = 4608
-// 17.3 / 16.2, C = 3500, d = 6000 21.4 / 16.3, but d = 4096 16.2 / 20.5 (rows a multiple of 4 KB apart ask for the same memory channels).
+// Where the one launch beats the product over K slices and the launch that adds them up: its blocks are as many as tiles (4096 clusters are one
+// round of them on 256 compute units) and each reads its rows alone, so rows must be short or tiles many.  us, two launches / one, B = 16:
+// bf16, d = 1024: C = 1024 9.2 / 6.6, C = 8192 9.6 / 7.2; d = 4096: C = 1024 9.4 / 7.9, C = 4096 11.5 / 8.6, but C = 8192 16.1 / 17.3;
+//   d = 5120: C = 1024 8.9 / 8.8, C = 2048 9.6 / 8.8, C = 4096 13.0 / 10.8; d = 5376 (a sixth chunk): C = 1024 8.9 / 9.8, C = 2048 9.7 / 10.0; the line
+//   is theirs: C = 2304 and more would gain up to d = 7168 (C = 2560, d = 6144 11.0 / 10.3, C = 4096, d = 7168 15.3 / 13.2, but d = 8192 16.4 / 18.9);
+//   more than 4096 clusters: C = 5000, d = 2048 9.6 / 9.5, d = 2304 9.9 / 11.2.
+// float32, d = 2048: C = 256 9.5 / 8.1, C = 1024 10.0 / 8.1, C = 4096 11.2 / 8.8; d = 2304: C = 1024 9.8 / 9.9; d = 4096: C = 1024 9.3 / 11.8;
+//   d = 5120: C = 2048 13.9 / 14.6; many tiles: C = 3072, d = 3072 13.2 / 10.9, C = 3072, d = 6144 17.7 / 16.7, d = 6400 18.1 / 18.7,
+//   C = 4096, d = 4608 17.4 / 16.3, but d = 4096 16.1 / 20.5 (rows 16 KB apart ask for the same memory channels).  The line keeps clear of all
+//   rows a multiple of 4 KB apart, though those of 12, 20 and 24 KB would gain (C = 4096, d = 5120 18.7 / 16.8).
 static bool bound_tile_pays(int C, int d, int B, bool m16) {
     if (B > 16) return false;
     if (m16) return d <= (C <= 4096 ? 5120 : 2048);
