@@ -45,7 +45,28 @@ def test_bounds_of_a_small_batch(B, C, d, bf16):
     _bounds_match_float64(B, C, d, bf16)
 
 
-def _bounds_match_float64(B, C, d, bf16):
+def _slices(C, d, B, bf16):
+    """(length, number) of the K slices of more than 64 sequences, and the most there may be: bound_mfma_plan of the library."""
+    groups, nkb = -(-C // 128), -(-d // 32)
+    n = min(-(-256 // groups), 32, nkb)
+    most = -(-nkb // min(-(-nkb // (4 * n)) * 4, 12))
+    plans = [(-(-groups * -(-nkb // k) * -(-B // 64) // 256) * k * (0.25 if bf16 else 0.5) + 2.2e-6 * -(-nkb // k) * B * C, -k) for k in (4, 8, 12, 16)
+             if -(-nkb // k) <= most]
+    k = -min(plans)[1]
+    return k, -(-nkb // k), most
+
+
+# More than 64 sequences: slices of 4, 8, 12 and 16 k-blocks, whole and partial last ones, as many as may be and fewer.  The slices' sums are added in
+# float32, too, so the tolerance is that of the other batches.
+@pytest.mark.parametrize("C,d,B,bf16,length", [(75, 8, 65, False, 4), (301, 1000, 70, False, 4), (1024, 4096, 65, False, 8), (260, 8192, 100, False, 8),
+                                               (1031, 4104, 67, True, 12), (500, 4104, 200, False, 12), (1024, 4096, 256, False, 16), (1000, 4000, 250, True, 16)])
+def test_bounds_of_many_sequences_by_slice_length(C, d, B, bf16, length):
+    k, n, most = _slices(C, d, B, bf16)
+    assert k == length and n <= most
+    _bounds_match_float64(B, C, d, bf16, static=most * B * C * 4 <= 8 << 20)     # what csv_bounds_static has room for
+
+
+def _bounds_match_float64(B, C, d, bf16, static=True):
     import paper_2511_21702_amd as csv
     torch = pytest.importorskip("torch")
     gen = torch.Generator(device="cuda").manual_seed(C + d)
@@ -60,8 +81,12 @@ def _bounds_match_float64(B, C, d, bf16):
     ws = csv.CsvWorkspace(g, B, V)
     U, hn = csv.csv_bounds(ws, g, h)
     U2, hn2 = torch.empty_like(U), torch.empty_like(hn)
-    csv.csv_bounds_static(g, h, U2, hn2)
-    assert torch.equal(U, U2) and torch.equal(hn, hn2)
+    if static:
+        csv.csv_bounds_static(g, h, U2, hn2)
+        assert torch.equal(U, U2) and torch.equal(hn, hn2)
+    else:
+        with pytest.raises(csv.CsvError):
+            csv.csv_bounds_static(g, h, U2, hn2)
     e = g.export()
     mu, R, bmax = (np.asarray(e[k], np.float64) for k in ("mu", "R", "bmax"))
     h64 = h.double().cpu().numpy()
