@@ -814,7 +814,7 @@ __global__ __launch_bounds__(AS_THREADS) void assign_near_kernel(const uint16_t*
     extern __shared__ as_uintx4_t as_lds[];
     constexpr int ASZ = 2 * MT * 128, BSZ = 4 * NT * 64;                                  // 16-byte pieces per stage of W, of the centroids
     constexpr int AP = ASZ / AS_THREADS, BP = BSZ / AS_THREADS, AH = AP / 2, OPEN = 2 * (AH + BP);
-    static_assert(AP * AS_THREADS == ASZ && BP * AS_THREADS == BSZ && AP % 2 == 0 && (OPEN == 8 || OPEN == 6 || OPEN == 4), "staging layout");
+    static_assert(AP * AS_THREADS == ASZ && BP * AS_THREADS == BSZ && AP % 2 == 0 && (OPEN == 8 || OPEN == 6), "staging layout");
     as_uintx4_t* ldb = as_lds + 3 * ASZ;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, g = lane >> 4, wm = wave >> 2, wn = wave & 3;
@@ -847,8 +847,7 @@ __global__ __launch_bounds__(AS_THREADS) void assign_near_kernel(const uint16_t*
     };
     auto wait_open = [&]() {                                 // all requests but the last two k-blocks' have arrived
         if constexpr (OPEN == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-        else if constexpr (OPEN == 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
     };
     auto barrier = [&]() {
         __builtin_amdgcn_sched_barrier(0);
@@ -1444,17 +1443,16 @@ static int gather(csv_index* x, const uint16_t* d_W, const float* d_b, hipStream
 
 // Which tile a block of the assignment computes: the one whose rounds over the compute units cost least.  Per k-block of the exact
 // product a 256 x 256 tile takes 3072 cycles of a SIMD's matrix core, a 128 x 256 tile 1536 (with 1464 of LDS traffic), and two
-// 128 x 128 tiles, which share a compute unit, 1792 of LDS traffic between them; of the product with rounded centroids 1024 (matrix core
-// and LDS), 704 and 1024 (LDS).
+// 128 x 128 tiles, which share a compute unit, 1792 of LDS traffic between them; of the product with bf16 centroids 1024 (matrix core
+// and LDS) and 704 (LDS), while two 128 x 128 tiles would take 1024, never less than one of 256 x 256.
 struct AssignPlan {
     int kind, nt, ncol, CT, ntot;
 };
-// kinds: how many of the tiles there are (assign_near_kernel with words has two: the third is never the cheapest where it is used)
-static AssignPlan assign_plan(int V, int C, bool near, int kinds = 3) {
-    static const struct { int mt, nt, per_cu, exact, near; } kind[3] = {{8, 4, 1, 3072, 1024}, {4, 4, 1, 1536, 704}, {4, 2, 2, 1792, 1024}};
+static AssignPlan assign_plan(int V, int C, bool near) {
+    static const struct { int mt, nt, per_cu, exact, near; } kind[3] = {{8, 4, 1, 3072, 1024}, {4, 4, 1, 1536, 704}, {4, 2, 2, 1792, 0}};
     AssignPlan best = {0, 0, 0, 0, 0};
     long long cost = 0;
-    for (int i = 0; i < kinds; ++i) {
+    for (int i = 0; i < (near ? 2 : 3); ++i) {
         const int bm = 2 * kind[i].mt * 16, bn = 4 * kind[i].nt * 16;
         const int ncol = (C + bn - 1) / bn, ntot = (V + bm - 1) / bm * ncol, at_once = 256 * kind[i].per_cu;
         const long long c = (long long)((ntot + at_once - 1) / at_once) * (near ? kind[i].near : kind[i].exact);
@@ -1521,7 +1519,7 @@ static int assign_first(const AssignPlan& p, const AssignRun& r) {
     const int rc = round_centroids(p, r, 0);
     if (rc) return rc;
     const AssignRows all = {0, 2, p.ntot / p.ncol};
-    return p.kind == 0 ? launch_near<8, 4, true>(p, r, nullptr, all) : p.kind == 1 ? launch_near<4, 4, true>(p, r, nullptr, all) : launch_near<4, 2, true>(p, r, nullptr, all);
+    return p.kind == 0 ? launch_near<8, 4, true>(p, r, nullptr, all) : launch_near<4, 4, true>(p, r, nullptr, all);
 }
 // order: the rows by the clusters so far.  give_up: looked at once the rounded scores of a sample of the rows are in (of all, where those are few tiles), at
 // the cost of a wait; set, and no labels made, where they leave so many rows for the exact product that it is cheaper over all rows.  Builds of skewed heads,
@@ -1585,7 +1583,7 @@ extern "C" int csv_build_index(const uint16_t* d_W, const float* d_b, int V, int
     const int nkb = (d + 31) / 32, nw = (V + LAY_TOKENS - 1) / LAY_TOKENS, max_chunks = V / CHUNK_ROWS + C;
     // first: the centroids are rows of W and one bf16 piece is exact; may_near: the centroids rounded come first
     const bool first = !o->h_init_labels && !o->spherical, may_near = o->iters > 0 && assign_near_pays(V, d, C);
-    const AssignPlan fp = assign_plan(V, C, true, may_near ? 2 : 3), ap = assign_plan(V, C, false);
+    const AssignPlan fp = assign_plan(V, C, true), ap = assign_plan(V, C, false);
     bool near = may_near;                // until an assignment shows that most rows are out of its reach
     char* arena = nullptr;
     size_t used = 0;

@@ -203,12 +203,12 @@ def test_first_assignment_from_rows_then_rounded_centroids():
     assert sorted(e["perm"].tolist()) == list(range(V)) and e["n"].sum() == V
 
 
-@pytest.mark.parametrize("seed_value", [4.0, np.inf])
-def test_sums_that_overflow_still_find_the_nearest(seed_value):
+@pytest.mark.parametrize("V,seed_value", [(700, 4.0), (700, np.inf), (40000, 4.0)])                # 128 and 256 rows a tile
+def test_sums_that_overflow_still_find_the_nearest(V, seed_value):
     """Finite rows whose products with a seed row overflow float32: minus infinity is the nearest, plus infinity farther than every finite score.  A row with
     a value that is not finite is nearest to none (the smallest id), a seed row with one is nobody's nearest."""
     import paper_2511_21702_amd as csv
-    V, d, C = 700, 264, 5
+    d, C = 264, 5
     W = np.zeros((V, d), np.float32)
     W[0, 0], W[1, 0], W[2, 1], W[4, 2] = 1e19, -1e19, 1.0, 8.0                   # seeds; ||1e19||^2 is finite
     W[3, 3], W[3, 4] = seed_value, 1.0
